@@ -174,7 +174,7 @@ def _inputs(case, seed):
         s = 1.2 + 0.02 * rng.uniform()
         g.update(phase=_spinodal(shape, 0.15, seed),
                  mats=[M.neohooke(5.0, 20.0), M.lce(1.0, 2.0, 100.0, **(LCE_FULL if full else {}))],
-                 Fbar=M.uniaxial_lce(s), rho=(20.0, 10.0, 60.0), mu_ref=1.6,
+                 Fbar=M.uniaxial_lce(s), rho=(20.0, 20.0, 60.0), mu_ref=1.6,
                  directors=_grains(shape, 200, seed + 7))
     elif case["geometry"] == "laminate":
         # layers normal to x1, compressed along x3
@@ -465,30 +465,45 @@ def _local_lce(A, mat, rho, n_prev):
     mua, beta, kap = mat["mu"] * mat["a"] ** (1.0 / 3.0), 1.0 / mat["a"] - 1.0, mat["kappa"]
     d = [mua * (1 + beta) + rho, mua + rho, mua + rho]
     f = [torch.maximum(x, a[0] / 16) for x in a]
+    scale = (f[0] * f[1] * f[2]) ** (-1.0 / 3.0)  # start at volume one
+    f = [x * scale for x in f]
 
     def h(f):
         J = f[0] * f[1] * f[2]
         v = 0.5 * kap * (J - 1) ** 2
         for i in range(3):
             v = v + 0.5 * d[i] * f[i] ** 2 - rho * a[i] * f[i]
-        return torch.where(J > 0, v, torch.full_like(v, math.inf))
+        return torch.where(torch.minimum(torch.minimum(f[0], f[1]), f[2]) > 0, v,
+                           torch.full_like(v, math.inf))
+
+    def solve(o, g):
+        det = (o[0][0] * (o[1][1] * o[2][2] - o[1][2] ** 2)
+               - o[0][1] * (o[0][1] * o[2][2] - o[1][2] * o[0][2])
+               + o[0][2] * (o[0][1] * o[1][2] - o[1][1] * o[0][2]))
+        x = []
+        for k in range(3):
+            q = [[(-g[i] if j == k else o[i][j]) for j in range(3)] for i in range(3)]
+            x.append((q[0][0] * (q[1][1] * q[2][2] - q[1][2] * q[2][1])
+                      - q[0][1] * (q[1][0] * q[2][2] - q[1][2] * q[2][0])
+                      + q[0][2] * (q[1][0] * q[2][1] - q[1][1] * q[2][0])) / det)
+        pd = (o[0][0] > 0) & (o[0][0] * o[1][1] - o[0][1] ** 2 > 0) & (det > 0)
+        return x, pd
 
     for _ in range(30):
         J = f[0] * f[1] * f[2]
         c = [f[1] * f[2], f[0] * f[2], f[0] * f[1]]
         g = [d[i] * f[i] - rho * a[i] + kap * (J - 1) * c[i] for i in range(3)]
-        o = [[kap * c[i] * c[j] + (d[i] if i == j else kap * (J - 1) * f[3 - i - j])
-              for j in range(3)] for i in range(3)]
-        det = (o[0][0] * (o[1][1] * o[2][2] - o[1][2] ** 2) - o[0][1] * (o[0][1] * o[2][2] - o[1][2] * o[0][2])
-               + o[0][2] * (o[0][1] * o[1][2] - o[1][1] * o[0][2]))
-        x = []
-        for k in range(3):
-            q = [[(-g[i] if j == k else o[i][j]) for j in range(3)] for i in range(3)]
-            x.append((q[0][0] * (q[1][1] * q[2][2] - q[1][2] * q[2][1]) - q[0][1] * (q[1][0] * q[2][2] - q[1][2] * q[2][0])
-                      + q[0][2] * (q[1][0] * q[2][1] - q[1][1] * q[2][0])) / det)
+        # Newton's step, or where the Hessian is not positive definite the one
+        # without its indefinite part
+        gn = [[kap * c[i] * c[j] + (d[i] if i == j else 0.0) for j in range(3)] for i in range(3)]
+        full = [[gn[i][j] + (0.0 if i == j else kap * (J - 1) * f[3 - i - j]) for j in range(3)]
+                for i in range(3)]
+        x, pd = solve(full, g)
+        y, _ = solve(gn, g)
+        x = [torch.where(pd, p, q) for p, q in zip(x, y)]
         t, h0 = torch.ones_like(J), h(f)
-        for _ in range(8):
-            ok = h([f[i] + t * x[i] for i in range(3)]) <= h0 + 1e-9 * (1 + h0.abs())
+        for _ in range(12):
+            ok = h([f[i] + t * x[i] for i in range(3)]) <= h0 + 1e-14 * (1 + h0.abs())
             t = torch.where(ok, t, 0.5 * t)
         f = [f[i] + t * x[i] for i in range(3)]
     n = torch.stack(U[0])
