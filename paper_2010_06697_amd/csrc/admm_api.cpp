@@ -108,7 +108,37 @@ size_t du_bytes(int n1, int n2, int n3, bool fp64) {
   return fp64 ? 0 : align_up(3 * (size_t)n1 * n2 * n3 * sizeof(float), 256);
 }
 
-int rows_per_block(int n1) { return std::max(1, kThreads / n1); }
+// x1-lines per workgroup of the per-voxel kernels: the count that fills its
+// waves best, the larger of equals (48: 4 lines in 192 threads rather than 5
+// in 256; 162: one line in 192)
+int wave_threads(int points) { return (points + 63) / 64 * 64; }
+int rows_per_block(int n1) {
+  int best = 1;
+  for (int r = 1; r * n1 <= kThreads; ++r)
+    if (r * n1 * wave_threads(best * n1) >= best * n1 * wave_threads(r * n1)) best = r;
+  return best;
+}
+
+// Planes per segment of the column tilings: kZSeg, halved while the cell's ny
+// x2 groups would give fewer than `target` workgroups. A plane of k_update
+// costs about 4 us of latency however few workgroups run, so a small cell
+// walking 16 planes leaves the chip idle: 16^3 double 66 us on one workgroup
+// (8 us at one plane each), 36 x 48 x 72 double 92 -> 12 us, 64^3 float
+// 43 -> 17 us, 96 x 192 x 54 double 107 -> 60 us. Longer walks read fewer
+// planes of u twice, which pays once the chip is full.
+//   kPartTarget: planes per residual partial. It depends on the cell alone, so
+//     that a cell's sums keep their order, and their bits, in any batch.
+//   kWalkTarget: workgroups of the whole context below which walks shorten
+//     (2048; a walk is at least one part): 16 cells of edges 32 to 96 walk 16
+//     planes (update 335 us; 400 to 490 us at the parts' own lengths).
+//   kMeanTarget: the mean-stress and null-mode sums, whose 18 or 24 block sums
+//     per workgroup weigh more than the walk (96^3: 71 us at 512, 100 at 256).
+constexpr int kPartTarget = 2048, kWalkTarget = 2048, kMeanTarget = 512;
+int planes_per_segment(int ny, int n3, int target) {
+  int z = kZSeg;
+  while (z > 1 && ny * ((n3 + z - 1) / z) < target) z /= 2;
+  return z;
+}
 
 // x1-lines per workgroup of the x1 transforms, for about `points` points per
 // workgroup (more lines keep more of the workgroup busy in every radix stage;
@@ -262,14 +292,18 @@ struct admm_ctx {
   EventTimer *timer = nullptr;
   // captured iteration sequences, one per convergence-test mode: `iters`
   // iterations recorded on cap_stream, replayed on `stream`
+  // (a third for the end of an admm_step whose last update writes F and Lambda)
   struct Graph {
     hipGraphExec_t exec = nullptr;
     int iters = 0;
-  } graph[2];
+  } graph[3];
   hipStream_t cap_stream = nullptr;
   // per-cell workgroup counts of the x2 / x3 passes depend on the tile widths
   std::vector<int> blk_h;
   int xpoints = 0;  // points per workgroup of the x1 transforms
+  // exact local step, no LCE phase: iterations run implicitly (RveDesc::Ai);
+  // the single-part entry points read and write F and Lambda
+  bool implicit = false;
 };
 
 namespace {
@@ -297,6 +331,7 @@ int snapshot_step(admm_ctx *c) {
 int upload_states(admm_ctx *c, int q_cur = 0) {
   for (auto &s : c->state_h) {
     s.at_rho = 0.0;  // Step 1 reads the caller's fields
+    s.implicit = 0;
     s.n_retry = 0;   // (no retry bit survives a retry pass)
     s.q_cur = q_cur;  // and Step 2 too, unless told otherwise
   }
@@ -392,7 +427,7 @@ bool tile_ok(const admm_ctx *c, int axis, int B) {
 }
 
 // tile widths of the x2 / x3 passes: workgroup prefix tables (blk_h holds
-// the x, y, z, u, f and i tables, n_rve + 1 entries each), grid sizes, upload.
+// the x, y, z, u, f, i, p, m and v tables, n_rve + 1 entries each), grid sizes, upload.
 // Under kTileCol16 an axis's workgroups take 16 columns each of the
 // flattened (x3, m1) or (m2, m1) set.
 static_assert(kTileCol16 == ADMM_TILE_REG16, "tile width of the register-resident pass");
@@ -416,7 +451,8 @@ int set_tiles(admm_ctx *c, int ty, int tz) {
       bz[r + 1] = bz[r] + (D.n2 * D.m1 + cw - 1) / cw;
       pz = std::max(pz, reg_points(c->fp64, D.n3));
     } else {
-      bz[r + 1] = bz[r] + (D.n2 * D.m1s + tz - 1) / tz;
+      const int w = c->L.plane ? plane_tile(c->fp64, c->L.n2max, tz) : tz;
+      bz[r + 1] = bz[r] + ((c->L.plane ? 1 : D.n2) * D.m1s + w - 1) / w;
     }
   }
   c->L.col256_y = c->L.col256_z = true;
@@ -487,10 +523,23 @@ int launch(admm_ctx *c, Part part, const IterParams &ip) {
   return e == hipSuccess ? ADMM_OK : ADMM_EHIP;
 }
 
-int one_iteration(admm_ctx *c, const IterParams &ip) {
+// last: the call's final iteration (known for admm_step only): where
+// iterations are implicit, its update writes F and Lambda
+int one_iteration(admm_ctx *c, const IterParams &ip, bool last) {
+  c->A.implicit = c->implicit ? (last ? 2 : 1) : 0;
   int rc = launch(c, Part::Local, ip);
   if (rc == ADMM_OK) rc = launch(c, Part::Project, ip);
   if (rc == ADMM_OK) rc = launch(c, Part::Update, ip);
+  c->A.implicit = 0;
+  return rc;
+}
+
+// before iterations of a call; implicit ones (and the float form) solve for
+// corrections of u, whose null modes Step 2 would keep
+int strip_null(admm_ctx *c, const IterParams &ip) {
+  c->A.implicit = c->implicit ? 1 : 0;
+  const int rc = launch(c, Part::StripNull, ip);
+  c->A.implicit = 0;
   return rc;
 }
 
@@ -499,7 +548,7 @@ int one_iteration(admm_ctx *c, const IterParams &ip) {
 // iteration state lives in device memory, so the graph stays valid across
 // calls. Capture needs a stream of its own (the caller's may be the null
 // stream); the graph is then launched on the caller's stream.
-int build_graph(admm_ctx *c, const IterParams &ip, int k, admm_ctx::Graph &g) {
+int build_graph(admm_ctx *c, const IterParams &ip, int k, bool last, admm_ctx::Graph &g) {
   if (g.exec) {
     (void)hipGraphExecDestroy(g.exec);
     g.exec = nullptr;
@@ -513,7 +562,7 @@ int build_graph(admm_ctx *c, const IterParams &ip, int k, admm_ctx::Graph &g) {
   if (hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
     rc = ADMM_EHIP;
   } else {
-    for (int it = 0; it < k && rc == ADMM_OK; ++it) rc = one_iteration(c, ip);
+    for (int it = 0; it < k && rc == ADMM_OK; ++it) rc = one_iteration(c, ip, last && it + 1 == k);
     if (hipStreamEndCapture(c->cap_stream, &graph) != hipSuccess) rc = ADMM_EHIP;
   }
   c->L.stream = saved;
@@ -527,17 +576,22 @@ int build_graph(admm_ctx *c, const IterParams &ip, int k, admm_ctx::Graph &g) {
 }
 
 // n iterations: whole graphs of check_every iterations, the rest launched
-// kernel by kernel (also everything while profiling)
-int run_iterations(admm_ctx *c, const IterParams &ip, int n) {
+// kernel by kernel (also everything while profiling). last: the call ends
+// with them.
+int run_iterations(admm_ctx *c, const IterParams &ip, int n, bool last) {
   const int k = c->params.check_every;
+  last = last && c->implicit;
   int done = 0, rc = ADMM_OK;
   if (c->params.use_graph && !c->timer && k >= 2 && n >= k) {
-    admm_ctx::Graph &g = c->graph[ip.test_conv ? 1 : 0];
-    if (!g.exec || g.iters != k) rc = build_graph(c, ip, k, g);
-    for (; rc == ADMM_OK && done + k <= n; done += k)
-      if (hipGraphLaunch(g.exec, c->stream) != hipSuccess) rc = ADMM_EHIP;
+    while (rc == ADMM_OK && done + k <= n) {
+      const bool end = last && done + k == n;
+      admm_ctx::Graph &g = c->graph[end ? 2 : (ip.test_conv ? 1 : 0)];
+      if (!g.exec || g.iters != k) rc = build_graph(c, ip, k, end, g);
+      if (rc == ADMM_OK && hipGraphLaunch(g.exec, c->stream) != hipSuccess) rc = ADMM_EHIP;
+      done += k;
+    }
   }
-  for (; rc == ADMM_OK && done < n; ++done) rc = one_iteration(c, ip);
+  for (; rc == ADMM_OK && done < n; ++done) rc = one_iteration(c, ip, last && done + 1 == n);
   return rc;
 }
 
@@ -924,12 +978,16 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
 
   // descriptors and workgroup prefix tables
   const int B = tile_b(fp64);
+  // plane strain: the pass along x2 has few lines, so the narrowest tile
+  bool plane = true;
+  for (int r = 0; r < n_rve; ++r) plane = plane && rves[r].n[2] == 1;
+  const int Bz = plane ? B / 4 : B;
   c->desc_h.resize(n_rve);
-  std::vector<int> bx(n_rve + 1), by(n_rve + 1), bz(n_rve + 1), bu(n_rve + 1), bf(n_rve + 1),
-      bi(n_rve + 1);
-  bx[0] = by[0] = bz[0] = bu[0] = bf[0] = 0;
+  std::vector<int> bv(n_rve + 1, 0), bx(n_rve + 1), by(n_rve + 1), bz(n_rve + 1), bu(n_rve + 1), bf(n_rve + 1),
+      bi(n_rve + 1), bp(n_rve + 1), bm(n_rve + 1);
+  bx[0] = by[0] = bz[0] = bu[0] = bf[0] = bi[0] = bp[0] = bm[0] = 0;
   size_t spec_off = 0;
-  int n2max = 0, n3max = 0, lds_x = 0;
+  int n2max = 0, n3max = 0, lds_x = 0, thr_u = 64;
   for (int r = 0; r < n_rve; ++r) {
     const admm_rve &R = rves[r];
     RveDesc &D = c->desc_h[r];
@@ -965,17 +1023,32 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     spec_off += spec_bytes(D.n1, D.n2, D.n3, fp64);
     D.du = fp64 ? nullptr : static_cast<char *>(c->workspace) + spec_off;
     spec_off += du_bytes(D.n1, D.n2, D.n3, fp64);
-    const int nrows = D.n2 * D.n3;
+    const int nrows = D.n2 * D.n3, ny = (D.n2 + D.rows - 1) / D.rows;
+    D.zpart = planes_per_segment(ny, D.n3, kPartTarget);
+    D.zmean = planes_per_segment(ny, D.n3, kMeanTarget);
+    bp[r + 1] = bp[r] + ny * ((D.n3 + D.zpart - 1) / D.zpart);
+    bm[r + 1] = bm[r] + ny * ((D.n3 + D.zmean - 1) / D.zmean);
+    bv[r + 1] = bv[r] + (int)((D.V + kThreads - 1) / kThreads);
+    thr_u = std::max(thr_u, wave_threads(D.rows * D.n1));
     bx[r + 1] = bx[r] + (nrows + D.rows - 1) / D.rows;
     bf[r + 1] = bf[r] + (nrows + D.rows_f - 1) / D.rows_f;
     bi[r + 1] = bi[r] + (3 * nrows + 31) / 32;
     by[r + 1] = by[r] + D.n3 * ((D.m1 + B - 1) / B);
-    bz[r + 1] = bz[r] + (D.n2 * D.m1s + B - 1) / B;
-    bu[r + 1] = bu[r] + ((D.n2 + D.rows - 1) / D.rows) *
-                            ((D.n3 + kZSeg - 1) / kZSeg);
+    bz[r + 1] = bz[r] + ((plane ? 1 : D.n2) * D.m1s + Bz - 1) / Bz;
     n2max = std::max(n2max, D.n2);
     n3max = std::max(n3max, D.n3);
     lds_x = std::max(lds_x, 2 * ((3 * D.rows_f + 1) / 2) * D.n1);
+  }
+  c->implicit = !any_lce && !any_ext && !(p.local_ratio > 0.0) && !(p.local_fraction > 0.0);
+  // planes a workgroup of the update walks, over the context's cells (one part
+  // each in explicit iterations)
+  for (int walk = kZSeg;; walk /= 2) {
+    for (int r = 0; r < n_rve; ++r) {
+      RveDesc &D = c->desc_h[r];
+      D.zseg = std::max(walk, D.zpart);
+      bu[r + 1] = bu[r] + ((D.n2 + D.rows - 1) / D.rows) * ((D.n3 + D.zseg - 1) / D.zseg);
+    }
+    if (walk == 1 || (c->implicit && bu[n_rve] >= kWalkTarget)) break;
   }
   // the spectra's padding columns stay zero: no kernel writes them but the
   // x3 pass, which maps zero to zero there
@@ -986,7 +1059,26 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   // update forms it (9 floats) and det F - 1 of the local step's warm start
   // (one float), read by the next local step at the same penalty instead of
   // the stencil gradient of u, Lambda and F
-  if (!fp64 && !any_ext) {
+  // Implicit iterations instead (exact local step, no LCE phase, both forms):
+  // A - I twice, F - A and one float; the double form also its correction du
+  // (the float form's lies in the workspace).
+  if (c->implicit) {
+    const size_t s = fp64 ? 8 : 4, per = 27 * s + 4 + (fp64 ? 3 * s : 0);
+    size_t tot = 0;
+    for (const RveDesc &D : c->desc_h) tot += align_up(per * (size_t)D.V, 256);
+    INIT_TRY(hipMalloc(&c->at_d, tot));
+    size_t off = 0;
+    for (RveDesc &D : c->desc_h) {
+      char *base = static_cast<char *>(c->at_d) + off;
+      const size_t f = 9 * (size_t)D.V * s;
+      D.Ai[0] = base;
+      D.Ai[1] = base + f;
+      D.Qi = base + 2 * f;
+      if (fp64) D.du = base + 3 * f;
+      D.Wi = reinterpret_cast<float *>(base + (per - 4) * (size_t)D.V);
+      off += align_up(per * (size_t)D.V, 256);
+    }
+  } else if (!fp64 && !any_ext) {
     const size_t per = any_lce ? 9 : 19;
     size_t tot = 0;
     for (const RveDesc &D : c->desc_h) tot += per * (size_t)D.V;
@@ -1004,13 +1096,19 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   c->L.any_lce = any_lce;
   c->L.lce_kind = any_ext ? 2 : (any_lce ? 1 : 0);
   c->L.any_frank = any_frank;
+  c->L.any_at = c->desc_h[0].At != nullptr;
   c->L.any_free = false;
   c->L.stream = c->stream;
   c->L.nblk_x = bx[n_rve];
   c->L.nblk_y = by[n_rve];
   c->L.nblk_z = bz[n_rve];
-  c->L.tile_y = c->L.tile_z = B;
+  c->L.tile_y = B;
+  c->L.tile_z = Bz;
+  c->L.plane = plane;
   c->L.nblk_u = bu[n_rve];
+  c->L.nblk_m = bm[n_rve];
+  c->L.nblk_v = bv[n_rve];
+  c->L.thr_u = thr_u;
   c->L.nblk_f = bf[n_rve];
   c->L.nblk_i = bi[n_rve];
   {
@@ -1054,7 +1152,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   }
   INIT_TRY(hipMalloc(&c->desc_d, sizeof(RveDesc) * n_rve));
   INIT_TRY(hipMemcpy(c->desc_d, c->desc_h.data(), sizeof(RveDesc) * n_rve, hipMemcpyHostToDevice));
-  INIT_TRY(hipMalloc(&c->blk_d, sizeof(int) * 6 * (n_rve + 1)));
+  INIT_TRY(hipMalloc(&c->blk_d, sizeof(int) * 9 * (n_rve + 1)));
   std::vector<int> &blk_h = c->blk_h;
   blk_h.clear();
   blk_h.insert(blk_h.end(), bx.begin(), bx.end());
@@ -1063,6 +1161,9 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   blk_h.insert(blk_h.end(), bu.begin(), bu.end());
   blk_h.insert(blk_h.end(), bf.begin(), bf.end());
   blk_h.insert(blk_h.end(), bi.begin(), bi.end());
+  blk_h.insert(blk_h.end(), bp.begin(), bp.end());
+  blk_h.insert(blk_h.end(), bm.begin(), bm.end());
+  blk_h.insert(blk_h.end(), bv.begin(), bv.end());
   INIT_TRY(hipMemcpy(c->blk_d, blk_h.data(), sizeof(int) * blk_h.size(), hipMemcpyHostToDevice));
 
   std::vector<Material> mh(n_mat);
@@ -1077,19 +1178,19 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   INIT_TRY(hipMalloc(&c->mats_d, sizeof(Material) * n_mat));
   INIT_TRY(hipMemcpy(c->mats_d, mh.data(), sizeof(Material) * n_mat, hipMemcpyHostToDevice));
 
-  INIT_TRY(hipMalloc(&c->partials_d, sizeof(double4) * (size_t)c->L.nblk_x));
-  INIT_TRY(hipMalloc(&c->partials18_d, sizeof(double) * 18 * (size_t)c->L.nblk_u));
+  INIT_TRY(hipMalloc(&c->partials_d, sizeof(double4) * (size_t)bp[n_rve]));
+  INIT_TRY(hipMalloc(&c->partials18_d, sizeof(double) * 18 * (size_t)c->L.nblk_m));
   INIT_TRY(hipMalloc(&c->mean_d, sizeof(double) * 18 * n_rve));
   INIT_TRY(hipMalloc(&c->hist_d, sizeof(double) * 3 * (size_t)c->hist_cap * n_rve));
   INIT_TRY(hipMalloc(&c->lpart_d, sizeof(double2) * (size_t)c->L.nblk_x));
   INIT_TRY(hipMalloc(&c->fpart_d, sizeof(double) * 9 * (size_t)c->L.nblk_x));
-  INIT_TRY(hipMalloc(&c->newton_part_d, sizeof(int2) * (size_t)c->L.nblk_x));
-  INIT_TRY(hipMemset(c->newton_part_d, 0, sizeof(int2) * (size_t)c->L.nblk_x));
+  INIT_TRY(hipMalloc(&c->newton_part_d, sizeof(int2) * (size_t)bp[n_rve]));
+  INIT_TRY(hipMemset(c->newton_part_d, 0, sizeof(int2) * (size_t)bp[n_rve]));
   INIT_TRY(hipMalloc(&c->retry_d, sizeof(unsigned) * (kThreads / 32) * (size_t)c->L.nblk_x));
   INIT_TRY(hipMemset(c->retry_d, 0, sizeof(unsigned) * (kThreads / 32) * (size_t)c->L.nblk_x));
-  if (!fp64) {
-    INIT_TRY(hipMalloc(&c->nullpart_d, sizeof(double) * 24 * (size_t)c->L.nblk_u));
-    INIT_TRY(hipMalloc(&c->nullc_d, sizeof(double) * 24 * (size_t)n_rve));
+  if (!fp64 || c->implicit) {  // cells whose Step 2 solves for corrections
+    INIT_TRY(hipMalloc(&c->nullpart_d, sizeof(double) * 25 * (size_t)c->L.nblk_m));
+    INIT_TRY(hipMalloc(&c->nullc_d, sizeof(double) * 25 * (size_t)n_rve));
   }
 
   c->state_h.assign(n_rve, RveState{});
@@ -1118,6 +1219,9 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   A.blk_u = c->blk_d + 3 * (n_rve + 1);
   A.blk_f = c->blk_d + 4 * (n_rve + 1);
   A.blk_i = c->blk_d + 5 * (n_rve + 1);
+  A.blk_p = c->blk_d + 6 * (n_rve + 1);
+  A.blk_m = c->blk_d + 7 * (n_rve + 1);
+  A.blk_v = c->blk_d + 8 * (n_rve + 1);
   A.mats = c->mats_d;
   A.tw = c->tw_d;
   A.partials = c->partials_d;
@@ -1291,8 +1395,8 @@ int admm_step(admm_ctx *ctx, int32_t n_iter, double *r_p, double *r_d, double *r
   int rc = activate_all(ctx);
   if (rc != ADMM_OK) return rc;
   const IterParams ip = iter_params(ctx, 0);
-  if (n_iter > 0) rc = launch(ctx, Part::StripNull, ip);
-  if (rc == ADMM_OK) rc = run_iterations(ctx, ip, n_iter);
+  if (n_iter > 0) rc = strip_null(ctx, ip);
+  if (rc == ADMM_OK) rc = run_iterations(ctx, ip, n_iter, true);
   if (rc != ADMM_OK) return rc;
   rc = settle(ctx);
   if (rc != ADMM_OK) return rc;
@@ -1311,15 +1415,19 @@ int admm_solve(admm_ctx *ctx, int32_t *iters_out, int32_t *status_out) {
   if (rc != ADMM_OK) return rc;
   const IterParams ip = iter_params(ctx, 1);
   const int every = ctx->params.check_every;
-  rc = launch(ctx, Part::StripNull, ip);
+  rc = strip_null(ctx, ip);
   if (rc != ADMM_OK) return rc;
   for (;;) {
     bool any = false;
     for (const auto &s : ctx->state_h) any = any || s.active;
     if (!any) break;
-    rc = run_iterations(ctx, ip, every);
+    rc = run_iterations(ctx, ip, every, false);
     if (rc != ADMM_OK) return rc;
     rc = download_states(ctx);
+    if (rc != ADMM_OK) return rc;
+  }
+  if (ctx->implicit) {
+    rc = launch(ctx, Part::Explicit, ip);
     if (rc != ADMM_OK) return rc;
   }
   rc = settle(ctx);
@@ -1456,7 +1564,9 @@ int admm_autotune(admm_ctx *ctx, int32_t reps, admm_tuning *out) {
     // step's F - A where the context holds it (the spectra and correction
     // it computes are scratch, overwritten by the next iteration)
     rc = upload_states(ctx, ctx->at_d ? 1 : 0);
+    ctx->A.implicit = ctx->implicit ? 1 : 0;
     if (rc == ADMM_OK) rc = tune(ctx, reps, out);
+    ctx->A.implicit = 0;
     ctx->state_h = saved;
     const int rc2 = upload_states(ctx);
     if (rc == ADMM_OK) rc = rc2;

@@ -57,6 +57,10 @@ struct RveDesc {
   long long S;              // complex entries of one spectral component
   int rows;                 // x1-lines per workgroup of the per-voxel kernels
   int rows_f;               // x1-lines per workgroup of the x1 transforms
+  int zseg;                 // planes a workgroup of the update walks
+  int zpart;                // planes per residual partial (divides zseg)
+  int zmean;                // planes per workgroup of the mean-stress and
+                            // null-mode sums
   int m1s;                  // row stride of the half spectra (m1 rounded up to 32
                             // bytes, so that every column tile starts on a sector)
   FastDiv f_n1, f_n2, f_m1, f_rows_f;  // the same as divisors
@@ -83,6 +87,13 @@ struct RveDesc {
   void *Q;                  // float form without the full LCE model's terms:
                             // F - A of the last local pass (9V float), whose
                             // D_h^T is Step 2's defect; else null
+  // Implicit iterations (exact local step, no LCE phase; both forms): A - I
+  // of Step 1 (9V, ping-pong with u), F - A (9V) and warm_code of the warm
+  // start (V float); du holds the correction. Null where the context has
+  // none.
+  void *Ai[2];
+  void *Qi;
+  float *Wi;
 };
 
 // per-cell iteration state, updated on the device
@@ -97,7 +108,8 @@ struct RveState {
   int newton_fail;   // local solves that hit the Newton cap
   int domain_err;    // set when det F <= 0 or NaN met
   int local_done;    // inexact local step: r_l reached its target (or the pass cap)
-  int pad1;
+  int implicit;      // 1: F and Lambda of this cell are held as A, F - A and
+                     // du (see k_update_i); every state upload clears it
   unsigned long long newton_iters;  // Newton iterations summed over voxels and iterations
   double rl;         // local residual after the last inexact pass
   double Ebar[9];       // <F> - I of the current iterate (free components move)
@@ -112,7 +124,7 @@ struct RveState {
                         // k_finalize and by every state upload
   double best_merit;    // divergence watch: smallest merit of the load step
   double ref_merit;     // divergence watch: merit at ref_iter
-  double at_rho;        // penalty RveDesc::At was formed with by the last
+  double at_rho;        // penalty RveDesc::At (Ai) was formed with by the last
                         // update (0: not formed in this call; reset by every
                         // state upload, so fields the caller wrote in between
                         // are read afresh)
@@ -139,7 +151,7 @@ __host__ __device__ inline bool divergence_watch(double rp, double rd, double to
   return stall > 0 && it - ref_iter >= stall;
 }
 
-constexpr int kZSeg = 16;  // planes per workgroup of the update tiling (k_update walks them)
+constexpr int kZSeg = 16;  // most planes per workgroup of the update tiling (k_update walks them)
 // tile width that selects the register-resident x2 / x3 pass of length 256
 // (16 columns per workgroup, 16 points per thread, one LDS exchange per
 // transform); open to an axis when every cell's length along it is 256

@@ -124,14 +124,16 @@ __device__ __forceinline__ void chunk_order(int b, int ny, int nz, int &yg, int 
   zb = ch * kZChunk + rem - yg * zl;
 }
 
-// (x2, first x3) of workgroup b of a cell in the update / mean-stress tiling:
-// R x1-lines (one x2 group) on kZSeg consecutive planes, x2 group fastest
-// (the workgroups of neighbouring x2 groups run side by side)
-__device__ __forceinline__ void column_tile(const RveDesc &D, int b, int row, int &x2, int &z0) {
+// (x2, first x3) of workgroup b of a cell in the tiling of the update (seg =
+// D.zseg) and of the mean-stress and null-mode sums (seg = D.zmean): R
+// x1-lines (one x2 group) on seg consecutive planes, x2 group fastest (the
+// workgroups of neighbouring x2 groups run side by side)
+__device__ __forceinline__ void column_tile(const RveDesc &D, int seg, int b, int row, int &x2,
+                                            int &z0) {
   const int ny = (D.n2 + D.rows - 1) / D.rows;
   const int zb = b / ny;
   x2 = (b - zb * ny) * D.rows + row;
-  z0 = zb * kZSeg;
+  z0 = zb * seg;
 }
 
 // deterministic sum of NV doubles over the workgroup; result valid in thread 0
@@ -213,6 +215,39 @@ constexpr bool kClosedOnly = MODE == kLocalExact && kDefect<T> && LK == 0;
 // update formed it at this penalty (RveDesc::At)
 template <typename T, int LK, int MODE>
 constexpr bool kFullPass = kDefect<T> && LK <= 1 && (MODE == kLocalExact || MODE == kLocalFirst);
+
+// Newton statistics of a local-step workgroup whose first line is `line`:
+// summed per workgroup and added to one slot of the update's parts (atomics
+// from every wave on one address per cell serialised the kernel's tail)
+__device__ __forceinline__ void newton_stats(const KernelArgs &a, const RveDesc &D, int r, int line,
+                                             int n_fail, int n_its) {
+  __shared__ int wsum[2 * (kThreads / 64)];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    n_fail += __shfl_xor(n_fail, off, 64);
+    n_its += __shfl_xor(n_its, off, 64);
+  }
+  const int t = threadIdx.x, wave = t >> 6, nw = (blockDim.x + 63) >> 6;
+  if ((t & 63) == 0) {
+    wsum[wave] = n_fail;
+    wsum[nw + wave] = n_its;
+  }
+  __syncthreads();
+  if (t == 0) {
+    int f = 0, s = 0;
+    for (int w = 0; w < nw; ++w) {
+      f += wsum[w];
+      s += wsum[nw + w];
+    }
+    // the update folds the counts of the slot that holds this workgroup's
+    // first line into its residual partials (a few workgroups share a slot,
+    // so these atomics do not contend)
+    const int x3 = fdiv(line, D.f_n2), x2 = line - x3 * D.n2;
+    const int slot = a.blk_p[r] + (x3 / D.zpart) * ((D.n2 + D.rows - 1) / D.rows) + x2 / D.rows;
+    if (f) atomicAdd(&a.newton_part[slot].x, f);
+    if (s) atomicAdd(&a.newton_part[slot].y, s);
+  }
+}
 
 // LK: 0 no LCE phase, 1 the ideal LCE, 2 some term of the full LCE model
 // (non-ideality, Frank, dissipation) or the dissipation of F
@@ -385,8 +420,13 @@ __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass
         // rotations, where the objective is only rho-stiff and Newton's
         // stopping test would accept it) is finished by one full Newton step.
         rc = -3;
-        if (MODE == kLocalExact)
-          rc = neo_closed<T>(E, At, jw, m.mu, m.lam, rho, cap, 1e-5);
+        if (MODE == kLocalExact) {
+          double Qd[9];
+          rc = neo_closed<T>(Qd, At, jw, m.mu, m.lam, rho, cap, 1e-5);
+          if (rc >= 0)
+#pragma unroll
+            for (int c = 0; c < 9; ++c) E[c] = (T)((double)At[c] + Qd[c]);
+        }
         if (kClosedOnly<T, LK, MODE>) {
           if (rc == -3) {
             atomicOr(&retry[t >> 5], 1u << (t & 31));
@@ -440,34 +480,46 @@ __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass
     if (t == 0) a.lpart[blk] = make_double2(lsum[0], lsum[1]);
     __syncthreads();
   }
-  // Newton statistics: summed per workgroup and added to one slot of the
-  // update kernel's tiling (atomics from every wave on one address per cell
-  // serialised the kernel's tail)
-  __shared__ int wsum[2 * (kThreads / 64)];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) {
-    n_fail += __shfl_xor(n_fail, off, 64);
-    n_its += __shfl_xor(n_its, off, 64);
-  }
-  const int wave = t >> 6, nw = (blockDim.x + 63) >> 6;
-  if ((t & 63) == 0) {
-    wsum[wave] = n_fail;
-    wsum[nw + wave] = n_its;
-  }
+  newton_stats(a, D, r, b * R, n_fail, n_its);
+}
+
+// The exact step's second pass: tile(blk) on every logical workgroup in which
+// the first pass left a voxel (its bits are cleared afterwards)
+template <typename F> __device__ __forceinline__ void retry_scan(const KernelArgs &a, int nblk, F tile) {
+  // nothing left over in any cell (the usual case): one round trip
+  __shared__ int any_cell;
+  if (threadIdx.x == 0) any_cell = 0;
   __syncthreads();
-  if (t == 0) {
-    int f = 0, s = 0;
-    for (int w = 0; w < nw; ++w) {
-      f += wsum[w];
-      s += wsum[nw + w];
+  for (int r = threadIdx.x; r < a.n_rve; r += blockDim.x)
+    if (a.state[r].n_retry) any_cell = 1;
+  __syncthreads();
+  if (!any_cell) return;
+  // this workgroup's logical workgroups are blockIdx.x, blockIdx.x +
+  // gridDim.x, ... (as in a later inexact pass); each thread looks at one
+  // of them, kThreads per round, and the marked ones are solved one after
+  // the other, their bits cleared once every thread has read its own
+  __shared__ int list[kThreads];
+  __shared__ int cnt;
+  for (int k0 = 0; blockIdx.x + k0 * gridDim.x < nblk; k0 += kThreads) {
+    if (threadIdx.x == 0) cnt = 0;
+    __syncthreads();
+    const int lb = blockIdx.x + (k0 + (int)threadIdx.x) * gridDim.x;
+    if (lb < nblk) {
+      const int blk = xcd_remap(lb, nblk);
+      const uint4 *w = reinterpret_cast<const uint4 *>(a.retry_mask + (size_t)blk * (kThreads / 32));
+      const uint4 w0 = w[0], w1 = w[1];
+      if (w0.x | w0.y | w0.z | w0.w | w1.x | w1.y | w1.z | w1.w) list[atomicAdd(&cnt, 1)] = blk;
     }
-    // the update workgroup whose tile holds this workgroup's first line
-    // folds the counts into its residual partials (a few workgroups share a
-    // slot, so these atomics do not contend)
-    const int g = b * R, x2 = g % n2, x3 = g / n2;
-    const int slot = a.blk_u[r] + (x3 / kZSeg) * ((n2 + R - 1) / R) + x2 / R;
-    if (f) atomicAdd(&a.newton_part[slot].x, f);
-    if (s) atomicAdd(&a.newton_part[slot].y, s);
+    __syncthreads();
+    const int n = cnt;
+    for (int q = 0; q < n; ++q) {
+      const int blk = list[q];
+      tile(blk);
+      __syncthreads();
+      if (threadIdx.x < kThreads / 32) a.retry_mask[(size_t)blk * (kThreads / 32) + threadIdx.x] = 0u;
+      __syncthreads();
+    }
+    __syncthreads();  // every thread has read cnt before the next round resets it
   }
 }
 
@@ -484,41 +536,7 @@ void k_local(KernelArgs a, IterParams ip, int pass, int nblk) {
     return;
   }
   if (MODE == kLocalRetry) {
-    // nothing left over in any cell (the usual case): one round trip
-    __shared__ int any_cell;
-    if (threadIdx.x == 0) any_cell = 0;
-    __syncthreads();
-    for (int r = threadIdx.x; r < a.n_rve; r += blockDim.x)
-      if (a.state[r].n_retry) any_cell = 1;
-    __syncthreads();
-    if (!any_cell) return;
-    // this workgroup's logical workgroups are blockIdx.x, blockIdx.x +
-    // gridDim.x, ... (as in a later inexact pass); each thread looks at one
-    // of them, kThreads per round, and the marked ones are solved one after
-    // the other, their bits cleared once every thread has read its own
-    __shared__ int list[kThreads];
-    __shared__ int cnt;
-    for (int k0 = 0; blockIdx.x + k0 * gridDim.x < nblk; k0 += kThreads) {
-      if (threadIdx.x == 0) cnt = 0;
-      __syncthreads();
-      const int lb = blockIdx.x + (k0 + (int)threadIdx.x) * gridDim.x;
-      if (lb < nblk) {
-        const int blk = xcd_remap(lb, nblk);
-        const uint4 *w = reinterpret_cast<const uint4 *>(a.retry_mask + (size_t)blk * (kThreads / 32));
-        const uint4 w0 = w[0], w1 = w[1];
-        if (w0.x | w0.y | w0.z | w0.w | w1.x | w1.y | w1.z | w1.w) list[atomicAdd(&cnt, 1)] = blk;
-      }
-      __syncthreads();
-      const int n = cnt;
-      for (int q = 0; q < n; ++q) {
-        const int blk = list[q];
-        local_tile<T, LK, MODE>(a, ip, pass, blk);
-        __syncthreads();
-        if (threadIdx.x < kThreads / 32) a.retry_mask[(size_t)blk * (kThreads / 32) + threadIdx.x] = 0u;
-        __syncthreads();
-      }
-      __syncthreads();  // every thread has read cnt before the next round resets it
-    }
+    retry_scan(a, nblk, [&](int blk) { local_tile<T, LK, MODE>(a, ip, pass, blk); });
     return;
   }
   for (int lb = blockIdx.x; lb < nblk; lb += gridDim.x) {
@@ -526,6 +544,226 @@ void k_local(KernelArgs a, IterParams ip, int pass, int nblk) {
     local_tile<T, LK, MODE>(a, ip, pass, blk);
     __syncthreads();  // LDS of this tile read before the next one writes it
   }
+}
+
+// ----------------------------------------------------------------------------
+// Implicit iterations (exact local step, no LCE phase). Between the first
+// local step of a call and its end neither F nor Lambda is stored: with
+//   A = I + Ebar + D_h u_i + Lambda_i / rho   (Step 1's data)      Ai[cur]
+//   Q = F_{i+1} - A                            (Step 1's result)   Qi
+//   du = u_{i+1} - u_i,  D_h^T D_h du = D_h^T Q (Step 2)            du
+// Step 3 is Lambda_{i+1} = rho (D_h du + dEbar - Q), and the next Step 1's
+// data A + (F_{i+1} terms cancel) = I + Ebar + D_h u_{i+1} + Lambda_{i+1}/rho
+// needs Q, du and u alone. Every kernel is bound by memory traffic: this drops
+// F from the local step's stores and the update's loads, and Lambda from both
+// of the update's, for one more load of A (bytes per voxel, float / double:
+// local 77 / 153 against 113 / 241, divergence 48 / 96 against 48 / 168,
+// update 172 / 316 against 208 / 264).
+// Where the penalty changed since A was formed, Step 1 forms it again from u,
+// du and Q.
+// ----------------------------------------------------------------------------
+
+// The closed form's point of a neo-Hookean voxel, as F - A; in the double form
+// (about 1e-12 along rotations) finished by one full Newton step. Returns as
+// neo_closed.
+template <typename T>
+__device__ __forceinline__ int closed_point(double *Q, const T *At, float jw, const Material &m,
+                                            const NeoHooke<T> &M, double rho, int cap) {
+  int rc = neo_closed<T>(Q, At, jw, m.mu, m.lam, rho, cap, 1e-5);
+  if (!kDefect<T> && rc >= 0) {
+    T E[9];
+#pragma unroll
+    for (int c = 0; c < 9; ++c) E[c] = (T)((double)At[c] + Q[c]);
+    rc = newton_polish<T, T>(E, At, M, (T)rho) ? rc + 1 : -3;
+#pragma unroll
+    for (int c = 0; c < 9; ++c) Q[c] = (double)E[c] - (double)At[c];
+  }
+  return rc;
+}
+
+// KIND: the first pass, which leaves the voxels without a closed form to the
+// second (kRetryI), or solves them itself (kInlineI)
+enum ImplicitLocal { kFirstI = 0, kRetryI = 1, kInlineI = 2 };
+
+template <typename T, int KIND>
+__device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterParams &ip, int blk) {
+  constexpr bool RETRY = KIND == kRetryI;
+  const int r = find_rve(a.blk_v, a.n_rve, blk);
+  const RveDesc &D = a.desc[r];
+  RveState *st = a.state + r;
+  if (!st->active) return;
+  const int b = blk - a.blk_v[r], t = threadIdx.x;
+  const int V = (int)D.V, idx = b * kThreads + t;
+  int n_fail = 0, n_its = 0;
+  unsigned *retry = a.retry_mask + (size_t)blk * (kThreads / 32);
+  const bool mine = idx < V && (!RETRY || ((retry[t >> 5] >> (t & 31)) & 1u));
+  if (mine) {
+    const double rho = st->rho, ar = st->at_rho;
+    const int cur = st->cur;
+    const auto Ag = global_view(static_cast<T *>(D.Ai[cur]));
+    const auto Qg = global_view(static_cast<T *>(D.Qi));
+    T At[9];
+    float jw = 0.0f;
+    if (RETRY || ar == rho) {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) At[c] = Ag[c * V + idx];
+      if (!RETRY) jw = global_view(D.Wi)[idx];
+    } else {
+      const int n1 = D.n1, n2 = D.n2, n3 = D.n3;
+      const int row = fdiv(idx, D.f_n1), x1 = idx - row * n1;
+      const int x3 = fdiv(row, D.f_n2), x2 = row - x3 * n2;
+      const Stencil sn = stencil(n1, n2, n3, x1, x2, x3);
+      double g[9];
+      grad_u(global_view(static_cast<const double *>(D.u[cur])), V, sn, g);
+      if (ar > 0.0) {
+        // formed at another penalty: Lambda from du and Q, which the last
+        // iteration left, as its update would have stored it
+        const double irho = 1.0 / rho;
+        double gb[9];
+        grad_u(global_view(static_cast<const T *>(D.du)), V, sn, gb);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+          const double s = gb[c] + (st->Ebar[c] - st->Ebar_prev[c]) - (double)Qg[c * V + idx];
+          At[c] = (T)(g[c] + st->Ebar[c] + (double)(T)(ar * s) * irho);
+        }
+        jw = global_view(D.Wi)[idx];
+      } else {  // the first local step of a call: the caller's fields
+        const auto Eg = global_view(static_cast<const T *>(D.E));
+        const auto Lg = global_view(static_cast<const T *>(D.Lam));
+        const double irho = 1.0 / rho;
+        T E[9];
+#pragma unroll
+        for (int c = 0; c < 9; ++c) {
+          E[c] = Eg[c * V + idx];
+          At[c] = (T)(g[c] + st->Ebar[c] + (double)Lg[c * V + idx] * irho);
+        }
+        jw = warm_code(warm_jm1(E));
+      }
+#pragma unroll
+      for (int c = 0; c < 9; ++c) Ag[c * V + idx] = At[c];
+    }
+    // the warm start F - I, for the nine-component Newton and where no point
+    // is found: the previous iterate, Q + A of that iteration, or the caller's
+    const auto warm = [&](T *E) {
+      if (st->implicit) {
+        const auto Ap = global_view(static_cast<const T *>(D.Ai[1 - cur]));
+#pragma unroll
+        for (int c = 0; c < 9; ++c) E[c] = (T)((double)Qg[c * V + idx] + (double)Ap[c * V + idx]);
+      } else {
+        const auto Eg = global_view(static_cast<const T *>(D.E));
+#pragma unroll
+        for (int c = 0; c < 9; ++c) E[c] = Eg[c * V + idx];
+      }
+    };
+    const int ph = global_view(D.phase)[idx];
+    int rc = -4;
+    bool newton_ran = false;  // (its last iterate is kept where it gave up)
+    double Q[9];
+    if (ph < a.n_mat) {
+      const Material m = a.mats[ph];
+      NeoHooke<T> M;
+      M.mu = (T)m.mu;
+      M.lam = (T)m.lam;
+      if (!RETRY) rc = closed_point<T>(Q, At, jw, m, M, rho, ip.newton_max);
+      if (KIND == kFirstI && rc == -3) {
+        atomicOr(&retry[t >> 5], 1u << (t & 31));
+        atomicAdd(&st->n_retry, 1);
+      }
+      if (RETRY || (KIND == kInlineI && rc == -3)) {
+        T E[9];
+        warm(E);
+        rc = newton<T, T>(E, At, M, (T)rho, ip.newton_max, ip.gtol, ip.step_tol);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) Q[c] = (double)E[c] - (double)At[c];
+        newton_ran = true;
+      }
+      n_its = rc >= 0 ? rc : (rc == -3 ? 0 : ip.newton_max);
+      n_fail = rc == -1;
+      if (rc == -2) atomicOr(&st->domain_err, 1);
+    } else {
+      atomicOr(&st->domain_err, 2);  // invalid phase index
+    }
+    if (rc != -3) {
+      if (rc < 0 && !newton_ran) {  // no point: F stays as it was
+        T E[9];
+        warm(E);
+#pragma unroll
+        for (int c = 0; c < 9; ++c) Q[c] = (double)E[c] - (double)At[c];
+      }
+#pragma unroll
+      for (int c = 0; c < 9; ++c) Qg[c * V + idx] = (T)Q[c];
+      if (a.implicit == 2) {
+        // the call's last iteration: F itself, which A + Q as stored would
+        // give to A's rounding only
+        const auto Eo = global_view(static_cast<T *>(D.E));
+#pragma unroll
+        for (int c = 0; c < 9; ++c) Eo[c * V + idx] = (T)((double)At[c] + Q[c]);
+      }
+    }
+  }
+  if (!RETRY && t == 0) st->q_cur = 1;  // (every workgroup stores the same flag)
+  newton_stats(a, D, r, fdiv(b * kThreads, D.f_n1), n_fail, n_its);
+}
+
+template <typename T, int KIND>
+__global__ __launch_bounds__(kThreads) void k_local_i(KernelArgs a, IterParams ip) {
+  local_tile_i<T, KIND>(a, ip, xcd_remap(blockIdx.x, gridDim.x));
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(1)))
+void k_retry_i(KernelArgs a, IterParams ip, int nblk) {
+  retry_scan(a, nblk, [&](int blk) { local_tile_i<T, kRetryI>(a, ip, blk); });
+}
+
+// F and Lambda of the cells whose last iteration left them implicit. In the
+// float form A + Q as stored gives F to A's rounding only (Lambda / rho is
+// several times F - I in a stiff phase), so F is the closed form's point again.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_explicit(KernelArgs a, IterParams ip) {
+  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int r = find_rve(a.blk_v, a.n_rve, blk);
+  const RveDesc &D = a.desc[r];
+  const RveState *st = a.state + r;
+  if (!st->implicit) return;
+  const int V = (int)D.V, idx = (blk - a.blk_v[r]) * kThreads + threadIdx.x;
+  if (idx >= V) return;
+  const int n1 = D.n1, n2 = D.n2, n3 = D.n3;
+  const int row = fdiv(idx, D.f_n1), x1 = idx - row * n1;
+  const int x3 = fdiv(row, D.f_n2), x2 = row - x3 * n2;
+  const Stencil sn = stencil(n1, n2, n3, x1, x2, x3);
+  const auto Ap = global_view(static_cast<const T *>(D.Ai[1 - st->cur]));
+  const auto Qg = global_view(static_cast<const T *>(D.Qi));
+  const auto Eg = global_view(static_cast<T *>(D.E));
+  const auto Lg = global_view(static_cast<T *>(D.Lam));
+  double g[9];
+  T Q[9], A[9];
+#pragma unroll
+  for (int c = 0; c < 9; ++c) {
+    Q[c] = Qg[c * V + idx];
+    A[c] = Ap[c * V + idx];
+  }
+  grad_u(global_view(static_cast<const T *>(D.du)), V, sn, g);
+  const double rho = st->rho_used;
+#pragma unroll
+  for (int c = 0; c < 9; ++c)
+    Lg[c * V + idx] = (T)(rho * (g[c] + (st->Ebar[c] - st->Ebar_prev[c]) - (double)Q[c]));
+  T E[9];
+#pragma unroll
+  for (int c = 0; c < 9; ++c) E[c] = (T)((double)Q[c] + (double)A[c]);
+  const int ph = global_view(D.phase)[idx];
+  if (kDefect<T> && ph < a.n_mat) {
+    const Material m = a.mats[ph];
+    NeoHooke<T> M;
+    M.mu = (T)m.mu;
+    M.lam = (T)m.lam;
+    double q[9];
+    if (closed_point<T>(q, A, warm_code(warm_jm1(E)), m, M, rho, ip.newton_max) >= 0)
+#pragma unroll
+      for (int c = 0; c < 9; ++c) E[c] = (T)((double)A[c] + q[c]);
+  }
+#pragma unroll
+  for (int c = 0; c < 9; ++c) Eg[c * V + idx] = E[c];
 }
 
 // Frank term: the directors of the previous iteration, copied before Step 1
@@ -608,6 +846,8 @@ __global__ __launch_bounds__(kThreads) void k_orient_final(KernelArgs a) {
 // Mixed conditions: per local workgroup, the sums of F_{i+1} - I -
 // Lambda_i/rho over its voxels (cells with free components of <F> only),
 // for k_fbar. A pass of its own, so that the local kernel carries none of it.
+// Implicit iterations sum F - A instead: F - I - Lambda/rho = F - A + Ebar +
+// D_h u, and D_h u has no mean.
 template <typename T>
 __global__ __launch_bounds__(kThreads) void k_fsum(KernelArgs a) {
   __shared__ double red[9 * (kThreads / 64)];
@@ -630,8 +870,14 @@ __global__ __launch_bounds__(kThreads) void k_fsum(KernelArgs a) {
     const auto Lg = global_view(static_cast<const T *>(D.Lam));
     const int idx = grow * n1 + x1;
     const double irho = 1.0 / st->rho;
+    if (a.implicit) {
+      const auto Qg = global_view(static_cast<const T *>(D.Qi));
 #pragma unroll
-    for (int c = 0; c < 9; ++c) h[c] = (double)Eg[c * V + idx] - (double)Lg[c * V + idx] * irho;
+      for (int c = 0; c < 9; ++c) h[c] = (double)Qg[c * V + idx];
+    } else {
+#pragma unroll
+      for (int c = 0; c < 9; ++c) h[c] = (double)Eg[c * V + idx] - (double)Lg[c * V + idx] * irho;
+    }
   }
   block_sum<9>(h, red);
   if (t == 0)
@@ -665,7 +911,7 @@ __global__ __launch_bounds__(kThreads) void k_fbar(KernelArgs a) {
 #pragma unroll
     for (int c = 0; c < 9; ++c) {
       st->Ebar_prev[c] = st->Ebar[c];
-      if ((m >> c) & 1u) st->Ebar[c] = v[c] / V;
+      if ((m >> c) & 1u) st->Ebar[c] = (a.implicit ? st->Ebar[c] : 0.0) + v[c] / V;
     }
   }
 }
@@ -712,10 +958,12 @@ __global__ __launch_bounds__(kThreads) void k_local_check(KernelArgs a, IterPara
 // ----------------------------------------------------------------------------
 
 
-template <typename T>
+// IMP: an implicit iteration, whose right-hand side is D_h^T Qi alone
+template <typename T, bool IMP>
 // six waves per SIMD (what its LDS allows at 1024 x1-points): at that budget
-// the compiler issues a voxel's 73 loads in two batches rather than four
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 6))) void k_div_fwdx(KernelArgs a) {
+// the compiler issues a voxel's loads in two batches rather than four
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 6)))
+void k_div_fwdx(KernelArgs a) {
   using C = typename cplx<T>::type;
   extern __shared__ __align__(16) unsigned char smem[];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
@@ -759,8 +1007,8 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(6, 6))
     // A = I + D_h u_i + Ebar + Lambda/rho, H - D_h u_i = F - A + Ebar, and
     // D_h^T of the constant Ebar vanishes: where the local step of this
     // iteration left Q = F - A, the defect is D_h^T Q.
-    if (kDefect<T> && D.Q && st->q_cur) {
-      const T *Qg = static_cast<const T *>(D.Q);
+    if (IMP || (kDefect<T> && D.Q && st->q_cur)) {
+      const auto Qg = global_view(static_cast<const T *>(IMP ? D.Qi : D.Q));
 #pragma unroll
       for (int i = 0; i < 3; ++i) {
         double bi = 0.0;
@@ -896,7 +1144,11 @@ __global__ __launch_bounds__(kThreads) void k_fft_y(KernelArgs a) {
 // (blockIdx.y = component)
 // ----------------------------------------------------------------------------
 
-template <typename T, int B>
+// PLANE: every cell has n3 = 1. Along x3 there is nothing to transform, and the
+// pass runs along x2 instead: forward, solve, inverse in one launch where the
+// general sequence takes three (256 x 256 x 1 double: 46 us, of which 26 us for
+// workgroups of 8 points along x3).
+template <typename T, int B, bool PLANE>
 __global__ __launch_bounds__(kThreads) void k_poisson_z(KernelArgs a) {
   using C = typename cplx<T>::type;
   constexpr int PMAX = (kMaxN * B) / kThreads;
@@ -906,8 +1158,9 @@ __global__ __launch_bounds__(kThreads) void k_poisson_z(KernelArgs a) {
   const RveDesc &D = a.desc[r];
   if (!a.state[r].active) return;
   const int b = blk - a.blk_z[r];
-  const int n1 = D.n1, n2 = D.n2, n3 = D.n3, m1 = D.m1, m1s = D.m1s;
-  const int plane = n2 * m1s;  // stride between x3 planes (padding columns included)
+  const Plan1D &pl = PLANE ? D.p2 : D.p3;  // the transformed axis
+  const int n1 = D.n1, n2 = PLANE ? 1 : D.n2, n3 = PLANE ? D.n2 : D.n3, m1 = D.m1, m1s = D.m1s;
+  const int plane = n2 * m1s;  // stride along that axis (padding columns included)
   const int q0 = b * B;
   const int npts = n3 * B;
   C *base = static_cast<C *>(D.spec) + blockIdx.y * D.S + q0;
@@ -928,7 +1181,7 @@ __global__ __launch_bounds__(kThreads) void k_poisson_z(KernelArgs a) {
     if (w < npts) za[w] = v[k];
   }
   __syncthreads();
-  C *res = fft_lines<false>(za, zb, D.p3, tw, B, 1, B, true, t, nthr);
+  C *res = fft_lines<false>(za, zb, pl, tw, B, 1, B, true, t, nthr);
   // u_hat = b_hat / (|K|^2 V); zero where every K_j vanishes
   const double iV = 1.0 / (double)D.V;
 #pragma unroll
@@ -941,8 +1194,8 @@ __global__ __launch_bounds__(kThreads) void k_poisson_z(KernelArgs a) {
       const int m2 = q / m1s, mm1 = q - m2 * m1s;
       const bool pad = mm1 >= m1;  // padding column: stays zero
       const double K1 = (double)tw[D.p1.tw + (pad ? 0 : mm1)].y;
-      const double K2 = (double)tw[D.p2.tw + m2].y;
-      const double K3 = (double)tw[D.p3.tw + m3].y;
+      const double K2 = PLANE ? 0.0 : (double)tw[D.p2.tw + m2].y;
+      const double K3 = (double)tw[pl.tw + m3].y;
       const bool null = pad || ((mm1 == 0 || 2 * mm1 == n1) && (m2 == 0 || 2 * m2 == n2) &&
                                 (m3 == 0 || 2 * m3 == n3));
       const T s = null ? (T)0 : (T)(iV / (K1 * K1 + K2 * K2 + K3 * K3));
@@ -959,7 +1212,7 @@ __global__ __launch_bounds__(kThreads) void k_poisson_z(KernelArgs a) {
     if (w < npts) dst[w] = v[k];
   }
   __syncthreads();
-  res = fft_lines<true>(dst, res, D.p3, tw, B, 1, B, true, t, nthr);
+  res = fft_lines<true>(dst, res, pl, tw, B, 1, B, true, t, nthr);
 #pragma unroll
   for (int k = 0; k < PMAX; ++k) {
     const int w = t + k * nthr;
@@ -1121,8 +1374,9 @@ __global__ __launch_bounds__(kThreads) void k_inv_x(KernelArgs a) {
   __syncthreads();
   const C *tw = static_cast<const C *>(a.tw);
   C *res = fft_lines<true>(za, zb, D.p1, tw, ncl, n1, 1, false, t, nthr);
-  // double form: u_{i+1}; float form: the correction u_{i+1} - u_i
-  T *un = kDefect<T> ? static_cast<T *>(D.du) : static_cast<T *>(D.u[1 - st->cur]);
+  // double form: u_{i+1}; float form and implicit iterations: the correction
+  // u_{i+1} - u_i
+  T *un = kDefect<T> || a.implicit ? static_cast<T *>(D.du) : static_cast<T *>(D.u[1 - st->cur]);
   for (int w = t; w < 3 * R * n1; w += nthr) {
     const int ell = fdiv(w, D.f_n1), x1 = w - ell * n1;
     const int c = fdiv(ell, D.f_rows_f), rw = ell - c * R;
@@ -1310,32 +1564,35 @@ __global__ __launch_bounds__(kThreads) void k_inv_x256(KernelArgs a) {
 
 // The fluctuation's components that D_h does not see: the mean and the
 // Nyquist checkerboards chi_s(x) = (-1)^(s1 k1 + s2 k2 + s3 k3), s in {0,1}^3
-// (s3 = 0 only when n3 = 1). Step 2 in the double form returns u without
-// them; the float form adds corrections to u_i and would keep whatever u_i
-// holds, so each call of the float form first removes them from u:
-// k_null_sums (per update workgroup, the 24 sums of u_i chi_s), k_null_final
-// (per cell, fixed order, coefficients / V), k_null_sub.
+// (s3 = 0 only when n3 = 1). The double form's explicit Step 2 returns u
+// without them; the float form and implicit iterations add corrections to u_i
+// and would keep whatever u_i holds, so each of their calls first removes
+// them from u: k_null_sums (per workgroup, the 24 sums of u_i chi_s and the
+// sum of |u|^2), k_null_final (per cell, fixed order, coefficients / V, zero
+// where they are below the rounding of u itself, 1e-15 of its RMS), k_null_sub
+// (nothing where every coefficient is zero: a call after a call).
+constexpr int kNullSums = 25;
 __device__ __forceinline__ double chi(int s, int k1, int k2, int k3) {
   const int e = ((s & 1) ? k1 : 0) + ((s & 2) ? k2 : 0) + ((s & 4) ? k3 : 0);
   return (e & 1) ? -1.0 : 1.0;
 }
 
 __global__ __launch_bounds__(kThreads) void k_null_sums(KernelArgs a) {
-  __shared__ double red[24 * (kThreads / 64)];
+  __shared__ double red[kNullSums * (kThreads / 64)];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int r = find_rve(a.blk_u, a.n_rve, blk);
+  const int r = find_rve(a.blk_m, a.n_rve, blk);
   const RveDesc &D = a.desc[r];
   const RveState *st = a.state + r;
-  const int b = blk - a.blk_u[r];
+  const int b = blk - a.blk_m[r];
   const int V = (int)D.V, n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows;
   const double *u = static_cast<const double *>(D.u[st->cur]);
   const int t = threadIdx.x, row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, b, row, x2, z0);
-  double v[24];
+  column_tile(D, D.zmean, b, row, x2, z0);
+  double v[kNullSums];
 #pragma unroll
-  for (int k = 0; k < 24; ++k) v[k] = 0.0;
-  for (int k = 0; k < kZSeg; ++k) {
+  for (int k = 0; k < kNullSums; ++k) v[k] = 0.0;
+  for (int k = 0; k < D.zmean; ++k) {
     const int x3 = z0 + k;
     if (row >= R || x2 >= n2 || x3 >= n3) continue;
     const int idx = (x3 * n2 + x2) * n1 + x1;
@@ -1344,47 +1601,56 @@ __global__ __launch_bounds__(kThreads) void k_null_sums(KernelArgs a) {
       const double ui = u[i * V + idx];
 #pragma unroll
       for (int sgn = 0; sgn < 8; ++sgn) v[8 * i + sgn] += ui * chi(sgn, x1, x2, x3);
+      v[24] += ui * ui;
     }
   }
-  block_sum<24>(v, red);
+  block_sum<kNullSums>(v, red);
   if (t == 0)
 #pragma unroll
-    for (int k = 0; k < 24; ++k) a.nullpart[(size_t)blk * 24 + k] = v[k];
+    for (int k = 0; k < kNullSums; ++k) a.nullpart[(size_t)blk * kNullSums + k] = v[k];
 }
 
 __global__ __launch_bounds__(kThreads) void k_null_final(KernelArgs a) {
-  __shared__ double red[24 * (kThreads / 64)];
+  __shared__ double red[kNullSums * (kThreads / 64)];
   const int r = blockIdx.x;
-  const int p0 = a.blk_u[r], nb = a.blk_u[r + 1] - p0;
-  double v[24];
+  const int p0 = a.blk_m[r], nb = a.blk_m[r + 1] - p0;
+  double v[kNullSums];
 #pragma unroll
-  for (int k = 0; k < 24; ++k) v[k] = 0.0;
+  for (int k = 0; k < kNullSums; ++k) v[k] = 0.0;
   for (int q = threadIdx.x; q < nb; q += blockDim.x)
 #pragma unroll
-    for (int k = 0; k < 24; ++k) v[k] += a.nullpart[(size_t)(p0 + q) * 24 + k];
-  block_sum<24>(v, red);
+    for (int k = 0; k < kNullSums; ++k) v[k] += a.nullpart[(size_t)(p0 + q) * kNullSums + k];
+  block_sum<kNullSums>(v, red);
   if (threadIdx.x == 0) {
     const RveDesc &D = a.desc[r];
     const double iV = 1.0 / (double)D.V;
+    const double floor2 = 1e-30 * v[24] * iV;
+    int any = 0;
 #pragma unroll
-    for (int k = 0; k < 24; ++k)  // with n3 = 1 the patterns with s3 = 1 repeat s3 = 0
-      a.nullc[(size_t)r * 24 + k] = (D.n3 == 1 && (k & 4)) ? 0.0 : v[k] * iV;
+    for (int k = 0; k < 24; ++k) {  // with n3 = 1 the patterns with s3 = 1 repeat s3 = 0
+      double c = (D.n3 == 1 && (k & 4)) ? 0.0 : v[k] * iV;
+      if (c * c <= floor2) c = 0.0;
+      any |= c != 0.0;
+      a.nullc[(size_t)r * kNullSums + k] = c;
+    }
+    a.nullc[(size_t)r * kNullSums + 24] = (double)any;
   }
 }
 
 __global__ __launch_bounds__(kThreads) void k_null_sub(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int r = find_rve(a.blk_u, a.n_rve, blk);
+  const int r = find_rve(a.blk_m, a.n_rve, blk);
   const RveDesc &D = a.desc[r];
   const RveState *st = a.state + r;
-  const int b = blk - a.blk_u[r];
+  const int b = blk - a.blk_m[r];
   const int V = (int)D.V, n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows;
   double *u = static_cast<double *>(D.u[st->cur]);
-  const double *c = a.nullc + (size_t)r * 24;
+  const double *c = a.nullc + (size_t)r * kNullSums;
+  if (c[24] == 0.0) return;
   const int t = threadIdx.x, row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, b, row, x2, z0);
-  for (int k = 0; k < kZSeg; ++k) {
+  column_tile(D, D.zmean, b, row, x2, z0);
+  for (int k = 0; k < D.zmean; ++k) {
     const int x3 = z0 + k;
     if (row >= R || x2 >= n2 || x3 >= n3) continue;
     const int idx = (x3 * n2 + x2) * n1 + x1;
@@ -1422,7 +1688,7 @@ __global__ __launch_bounds__(kThreads) void k_compose_u(KernelArgs a) {
 
 // ----------------------------------------------------------------------------
 // Step 3 + partial sums of Step 4, walking x3. A workgroup owns R x1-lines
-// (one x2 group, every x1) on kZSeg consecutive planes and takes the planes
+// (one x2 group, every x1) on D.zseg consecutive planes and takes the planes
 // in x3 order. Step 3 needs the central-difference gradients of two 3-vector
 // fields: double form, u_{i+1} and u_i; float form, u_{i+1} = u_i + du
 // (formed in double as it is stored) and du. Each thread keeps both at its
@@ -1440,11 +1706,11 @@ template <typename T> struct UPair {
   T b[3];
 };
 
-template <typename T>
+template <typename T, bool DU>
 __device__ __forceinline__ void load_pair(const RveDesc &D, const RveState *st, int V, int idx,
                                           UPair<T> &p) {
   const auto uo = global_view(static_cast<const double *>(D.u[st->cur]));
-  if (kDefect<T>) {
+  if (DU) {
     const auto dug = global_view(static_cast<const T *>(D.du));
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
@@ -1461,22 +1727,22 @@ __device__ __forceinline__ void load_pair(const RveDesc &D, const RveState *st, 
   }
 }
 
-// the workgroup's residual partials and the Newton statistics the local
-// step's workgroups left in its slot (plus `f`, `sm`)
-__device__ __forceinline__ void store_partials(KernelArgs &a, int blk, double *v, int f, int sm) {
-  __shared__ double red[2 * (kThreads / 64)];
-  block_sum<2>(v, red);
-  if (threadIdx.x == 0) {
-    const int2 q = a.newton_part[blk];
-    a.newton_part[blk] = int2{0, 0};
-    a.partials[blk] = double4{v[0], v[1], (double)(q.x + f), (double)(q.y + sm)};
-  }
-}
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_update(KernelArgs a) {
+// IMP 0: F and Lambda in, Lambda out. IMP 1, an implicit iteration: with Q =
+// F_{i+1} - A and gb = D_h du + dEbar, Lambda_{i+1} = rho (gb - Q) is not
+// stored, only the next Step 1's data Ebar + D_h u_{i+1} + (gb - Q). IMP 2,
+// its last one in a call, whose local step also wrote F: Lambda out. KIND 0, 1, 2: IMP; 3: IMP 0
+// with the next local step's data (RveDesc::At: inexact local steps in float)
+// out as well, in a kernel of its own because those stores cost the others'
+// float form three spilled registers (its update of 256^3: 686 -> 760 us).
+template <typename T, int KIND>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kDefect<T> && KIND != 2 ? 3 : 1)))
+void k_update(KernelArgs a) {
+  constexpr int IMP = KIND == 3 ? 0 : KIND;
+  constexpr bool AT = KIND == 3;
+  constexpr bool DU = kDefect<T> || IMP;  // the fields are u, du (else u_{i+1}, u_i)
   __shared__ double lineA[2][3][kThreads];
   __shared__ T lineB[2][3][kThreads];
+  __shared__ double red[IMP ? kZSeg : 1][2][kThreads / 64];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_u, a.n_rve, blk);
   const RveDesc &D = a.desc[r];
@@ -1485,15 +1751,19 @@ __global__ __launch_bounds__(kThreads) void k_update(KernelArgs a) {
   const int b = blk - a.blk_u[r];
   const int V = (int)D.V;
   const int n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows;
-  const auto Eg = global_view(static_cast<const T *>(D.E));
-  const auto Lg = global_view(static_cast<T *>(D.Lam));
+  // in: F - I and Lambda, or F - A and A - I (KIND 2: F - I)
+  const auto Eg = global_view(static_cast<const T *>(IMP ? D.Qi : D.E));
+  const auto Lg = global_view(static_cast<T *>(IMP == 1 ? D.Ai[st->cur] : IMP ? D.E : D.Lam));
+  // out: Lambda or the next A - I
+  const auto Lo = IMP ? global_view(static_cast<T *>(IMP == 1 ? D.Ai[1 - st->cur] : D.Lam)) : Lg;
   const auto un = global_view(static_cast<double *>(D.u[1 - st->cur]));
-  const auto Ag = D.At ? global_view(static_cast<T *>(D.At)) : nullptr;
+  const auto Ag = global_view(static_cast<T *>(D.At));
   const int t = threadIdx.x;
   const int row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, b, row, x2, z0);
-  const int nz = min(kZSeg, n3 - z0);  // uniform over the workgroup
+  column_tile(D, D.zseg, b, row, x2, z0);
+  const int nz = min(D.zseg, n3 - z0);  // uniform over the workgroup
+  const int zpart = D.zpart;
   const bool act = row < R && x2 < n2;
   const int x2p = x2 + 1 >= n2 ? 0 : x2 + 1, x2m = x2 == 0 ? n2 - 1 : x2 - 1;
   const int l1p = row * n1 + (x1 + 1 == n1 ? 0 : x1 + 1);
@@ -1506,10 +1776,11 @@ __global__ __launch_bounds__(kThreads) void k_update(KernelArgs a) {
     pc.b[i] = (T)0;
   }
   if (act) {
-    load_pair<T>(D, st, V, ((z0 == 0 ? n3 - 1 : z0 - 1) * n2 + x2) * n1 + x1, pm);
-    load_pair<T>(D, st, V, (z0 * n2 + x2) * n1 + x1, pc);
+    load_pair<T, DU>(D, st, V, ((z0 == 0 ? n3 - 1 : z0 - 1) * n2 + x2) * n1 + x1, pm);
+    load_pair<T, DU>(D, st, V, (z0 * n2 + x2) * n1 + x1, pc);
   }
   double v[2] = {0.0, 0.0};
+  int kp = 0;  // planes summed into v
   for (int k = 0; k < nz; ++k) {
     const int x3 = z0 + k, buf = k & 1;
     // plane x3's lines for the +-x1 neighbours (two buffers: the one
@@ -1521,57 +1792,113 @@ __global__ __launch_bounds__(kThreads) void k_update(KernelArgs a) {
       lineB[buf][i][t] = pc.b[i];
     }
     __syncthreads();
-    if (!act) continue;
-    const int idx = (x3 * n2 + x2) * n1 + x1;
-    // every load of the plane before its first store (a store may alias a
-    // later load as far as the compiler knows)
-    load_pair<T>(D, st, V, ((x3 + 1 == n3 ? 0 : x3 + 1) * n2 + x2) * n1 + x1, pp);
-    UPair<T> q2p, q2m;
-    load_pair<T>(D, st, V, (x3 * n2 + x2p) * n1 + x1, q2p);
-    load_pair<T>(D, st, V, (x3 * n2 + x2m) * n1 + x1, q2m);
-    T E[9], L[9];
+    if (!IMP && !act) continue;
+    if (!IMP || act) {
+      const int idx = (x3 * n2 + x2) * n1 + x1;
+      // every load of the plane before its first store (a store may alias a
+      // later load as far as the compiler knows)
+      load_pair<T, DU>(D, st, V, ((x3 + 1 == n3 ? 0 : x3 + 1) * n2 + x2) * n1 + x1, pp);
+      UPair<T> q2p, q2m;
+      load_pair<T, DU>(D, st, V, (x3 * n2 + x2p) * n1 + x1, q2p);
+      load_pair<T, DU>(D, st, V, (x3 * n2 + x2m) * n1 + x1, q2m);
+      T E[9], L[9];
 #pragma unroll
-    for (int c = 0; c < 9; ++c) {
-      E[c] = Eg[c * V + idx];
-      L[c] = Lg[c * V + idx];
-    }
-    // component c = 3 i + j: Dn = grad u_{i+1}, Dd its change over the
-    // iteration (float form: grad du; double form: grad u_{i+1} - grad u_i)
-    T lam[9];
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      const double ap[3] = {lineA[buf][i][l1p], q2p.a[i], pp.a[i]};
-      const double am[3] = {lineA[buf][i][l1m], q2m.a[i], pm.a[i]};
-      const double bp[3] = {(double)lineB[buf][i][l1p], (double)q2p.b[i], (double)pp.b[i]};
-      const double bm[3] = {(double)lineB[buf][i][l1m], (double)q2m.b[i], (double)pm.b[i]};
-#pragma unroll
-      for (int j = 0; j < 3; ++j) {
-        const int c = 3 * i + j;
-        const double Dn = 0.5 * (ap[j] - am[j]);
-        const double gb = 0.5 * (bp[j] - bm[j]);
-        const double Dd = kDefect<T> ? gb : Dn - gb;
-        const double e = st->Ebar[c] + Dn - (double)E[c];
-        lam[c] = (T)((double)L[c] + rho * e);
-        // Step 1's data of the next iteration at this penalty, formed as the
-        // local step forms it (same operands, same order of operations)
-        if (kDefect<T> && Ag) Ag[c * V + idx] = (T)(Dn + st->Ebar[c] + (double)lam[c] * irho);
-        const double dd = Dd + (st->Ebar[c] - st->Ebar_prev[c]);
-        v[0] += e * e;
-        v[1] += dd * dd;
+      for (int c = 0; c < 9; ++c) {
+        E[c] = Eg[c * V + idx];
+        L[c] = Lg[c * V + idx];
       }
-    }
-    if (kDefect<T>) {
+      float jw = 0.0f;
+      if (IMP == 1) {
+        T F[9];
 #pragma unroll
-      for (int i = 0; i < 3; ++i) un[i * V + idx] = pc.a[i];
+        for (int c = 0; c < 9; ++c) F[c] = (T)((double)E[c] + (double)L[c]);
+        jw = warm_code(warm_jm1(F));
+      }
+      // component c = 3 i + j: Dn = grad u_{i+1}, Dd its change over the
+      // iteration (float form: grad du; double form: grad u_{i+1} - grad u_i)
+      T lam[9];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        const double ap[3] = {lineA[buf][i][l1p], q2p.a[i], pp.a[i]};
+        const double am[3] = {lineA[buf][i][l1m], q2m.a[i], pm.a[i]};
+        const double bp[3] = {(double)lineB[buf][i][l1p], (double)q2p.b[i], (double)pp.b[i]};
+        const double bm[3] = {(double)lineB[buf][i][l1m], (double)q2m.b[i], (double)pm.b[i]};
+#pragma unroll
+        for (int j = 0; j < 3; ++j) {
+          const int c = 3 * i + j;
+          const double Dn = 0.5 * (ap[j] - am[j]);
+          const double gb = 0.5 * (bp[j] - bm[j]);
+          const double Dd = DU ? gb : Dn - gb;
+          const double dd = Dd + (st->Ebar[c] - st->Ebar_prev[c]);
+          double e;
+          if (IMP) {
+            const double q = (double)E[c], s = dd - q;  // s: Lambda / rho
+            const double f = IMP == 1 ? q + (double)L[c] : (double)L[c];
+            e = st->Ebar[c] + Dn - f;
+            // (through Lambda as it is stored, so that a call that reads it back
+            // forms the same data at this penalty, bit for bit)
+            const T ls = (T)(rho * s);
+            Lo[c * V + idx] = IMP == 1 ? (T)(Dn + st->Ebar[c] + (double)ls * irho) : ls;
+          } else {
+            e = st->Ebar[c] + Dn - (double)E[c];
+            lam[c] = (T)((double)L[c] + rho * e);
+            // Step 1's data of the next iteration at this penalty, formed as the
+            // local step forms it (same operands, same order of operations)
+            if (AT) Ag[c * V + idx] = (T)(Dn + st->Ebar[c] + (double)lam[c] * irho);
+          }
+          v[0] += e * e;
+          v[1] += dd * dd;
+        }
+      }
+      if (DU) {
+#pragma unroll
+        for (int i = 0; i < 3; ++i) un[i * V + idx] = pc.a[i];
+      }
       // and the warm start's det F - 1 for the closed form of that step
-      if (Ag) Ag[9 * V + idx] = warm_code(warm_jm1(E));
-    }
+      if (IMP == 1) global_view(D.Wi)[idx] = jw;
+      else if (AT) Ag[9 * V + idx] = warm_code(warm_jm1(E));
+      if (!IMP)
 #pragma unroll
-    for (int c = 0; c < 9; ++c) Lg[c * V + idx] = lam[c];
-    pm = pc;
-    pc = pp;
+        for (int c = 0; c < 9; ++c) Lo[c * V + idx] = lam[c];
+      pm = pc;
+      pc = pp;
+    }
+    // one residual partial per zpart planes, whatever the walk: sums over the
+    // waves here, over the workgroup after the walk (an explicit walk is one
+    // part: the sums in the loop would cost its float form registers it spills)
+    if (IMP && (++kp == zpart || k + 1 == nz)) {
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[q] += __shfl_xor(v[q], off, 64);
+        if ((t & 63) == 0) red[k / zpart][q][t >> 6] = v[q];
+        v[q] = 0.0;
+      }
+      kp = 0;
+    }
   }
-  store_partials(a, blk, v, 0, 0);
+  // the sums of each part, and the Newton statistics the local step's
+  // workgroups left in its slot
+  if (!IMP) block_sum<2>(v, &red[0][0][0]);
+  __syncthreads();
+  const int np = (nz + zpart - 1) / zpart;
+  if (t < np) {
+    const int nw = (blockDim.x + 63) >> 6;
+    double s0 = 0.0, s1 = 0.0;
+    if (!IMP) {  // an explicit walk's sum stands in its first part
+      s0 = t == 0 ? v[0] : 0.0;
+      s1 = t == 0 ? v[1] : 0.0;
+    } else
+      for (int w = 0; w < nw; ++w) {
+        s0 += red[t][0][w];
+        s1 += red[t][1][w];
+      }
+    const int ny = (n2 + R - 1) / R;
+    const int slot = a.blk_p[r] + (z0 / zpart + t) * ny + b % ny;
+    const int2 q = a.newton_part[slot];
+    a.newton_part[slot] = int2{0, 0};
+    a.partials[slot] = double4{s0, s1, (double)q.x, (double)q.y};
+  }
 }
 
 // ----------------------------------------------------------------------------
@@ -1583,7 +1910,7 @@ __global__ __launch_bounds__(kThreads) void k_finalize(KernelArgs a, IterParams 
   const int r = blockIdx.x;
   RveState *st = a.state + r;
   if (!st->active) return;
-  const int p0 = a.blk_u[r], nb = a.blk_u[r + 1] - p0;
+  const int p0 = a.blk_p[r], nb = a.blk_p[r + 1] - p0;
   double v[4] = {0.0, 0.0, 0.0, 0.0};
   // eight loads in flight per thread, added in the order of k as one at a
   // time would (the sums keep their bits)
@@ -1627,7 +1954,8 @@ __global__ __launch_bounds__(kThreads) void k_finalize(KernelArgs a, IterParams 
   st->rp = rp;
   st->rd = rd;
   st->rho_used = rho;
-  st->at_rho = a.desc[r].At ? rho : 0.0;
+  st->at_rho = a.implicit == 1 || (!a.implicit && a.desc[r].At) ? rho : 0.0;
+  st->implicit = a.implicit == 1;
   st->n_retry = 0;  // the local step's retry pass has run
   st->q_cur = 0;   // the next local step decides
   st->iter = it + 1;
@@ -1674,9 +2002,9 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_mean_stress(KernelArgs a) {
   __shared__ double red[18 * (kThreads / 64)];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int r = find_rve(a.blk_u, a.n_rve, blk);
+  const int r = find_rve(a.blk_m, a.n_rve, blk);
   const RveDesc &D = a.desc[r];
-  const int b = blk - a.blk_u[r];
+  const int b = blk - a.blk_m[r];
   const int V = (int)D.V;
   const int n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows;
   const T *Eg = static_cast<const T *>(D.E);
@@ -1684,12 +2012,12 @@ __global__ __launch_bounds__(kThreads) void k_mean_stress(KernelArgs a) {
   const int t = threadIdx.x;
   const int row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, b, row, x2, z0);
+  column_tile(D, D.zmean, b, row, x2, z0);
   double v[18];
 #pragma unroll
   for (int k = 0; k < 18; ++k) v[k] = 0.0;
   int bad = 0;
-  for (int k = 0; k < kZSeg; ++k) {
+  for (int k = 0; k < D.zmean; ++k) {
     const int x3 = z0 + k;
     if (row >= R || x2 >= n2 || x3 >= n3) continue;
     const int idx = (x3 * n2 + x2) * n1 + x1;
@@ -1753,7 +2081,7 @@ __global__ __launch_bounds__(kThreads) void k_mean_stress(KernelArgs a) {
 __global__ __launch_bounds__(kThreads) void k_mean_final(KernelArgs a) {
   __shared__ double red[18 * (kThreads / 64)];
   const int r = blockIdx.x;
-  const int p0 = a.blk_u[r], nb = a.blk_u[r + 1] - p0;
+  const int p0 = a.blk_m[r], nb = a.blk_m[r + 1] - p0;
   double v[18];
 #pragma unroll
   for (int k = 0; k < 18; ++k) v[k] = 0.0;
@@ -1813,10 +2141,26 @@ static void launch_fft_y(const LaunchCfg &L, const KernelArgs &a) {
     hipLaunchKernelGGL((k_fft_y<T, B, INV>), grid, blk, lds, L.stream, a);
 }
 
+template <typename T, bool PLANE>
+static void launch_poisson_tiled(const LaunchCfg &L, const KernelArgs &a) {
+  using C = typename cplx<T>::type;
+  constexpr int B = tileB<T>();
+  const dim3 blk(kThreads), grid(L.nblk_z, 3);
+  const int tz = PLANE ? plane_tile(sizeof(T) == 8, L.n2max, L.tile_z) : L.tile_z;
+  const size_t lds = 2 * (size_t)(PLANE ? L.n2max : L.n3max) * tz * sizeof(C);
+  if (tz == B / 4)
+    hipLaunchKernelGGL((k_poisson_z<T, B / 4, PLANE>), grid, blk, lds, L.stream, a);
+  else if (tz == B / 2)
+    hipLaunchKernelGGL((k_poisson_z<T, B / 2, PLANE>), grid, blk, lds, L.stream, a);
+  else if (tz == 2 * B)
+    hipLaunchKernelGGL((k_poisson_z<T, 2 * B, PLANE>), grid, blk, lds, L.stream, a);
+  else
+    hipLaunchKernelGGL((k_poisson_z<T, B, PLANE>), grid, blk, lds, L.stream, a);
+}
+
 template <typename T>
 static void launch_poisson_z(const LaunchCfg &L, const KernelArgs &a) {
   using C = typename cplx<T>::type;
-  constexpr int B = tileB<T>();
   const dim3 blk(kThreads), grid(L.nblk_z, 3);
   if (L.tile_z == kTileCol16) {
     if (sizeof(T) == 4 && !L.col256_z) {
@@ -1829,15 +2173,10 @@ static void launch_poisson_z(const LaunchCfg &L, const KernelArgs &a) {
     }
     return;
   }
-  const size_t lds = 2 * (size_t)L.n3max * L.tile_z * sizeof(C);
-  if (L.tile_z == B / 4)
-    hipLaunchKernelGGL((k_poisson_z<T, B / 4>), grid, blk, lds, L.stream, a);
-  else if (L.tile_z == B / 2)
-    hipLaunchKernelGGL((k_poisson_z<T, B / 2>), grid, blk, lds, L.stream, a);
-  else if (L.tile_z == 2 * B)
-    hipLaunchKernelGGL((k_poisson_z<T, 2 * B>), grid, blk, lds, L.stream, a);
+  if (L.plane)
+    launch_poisson_tiled<T, true>(L, a);
   else
-    hipLaunchKernelGGL((k_poisson_z<T, B>), grid, blk, lds, L.stream, a);
+    launch_poisson_tiled<T, false>(L, a);
 }
 
 // one pass of Step 1 in the kernel variant of the context's materials
@@ -1860,6 +2199,18 @@ static void launch_local(const LaunchCfg &L, const KernelArgs &a, const IterPara
                        blk, 0, L.stream, a, ip, pass, L.nblk_x);
 }
 
+template <typename T> static void launch_update(const LaunchCfg &L, const KernelArgs &a) {
+  const dim3 grid(L.nblk_u), blk(L.thr_u);
+  if (a.implicit == 2)
+    hipLaunchKernelGGL((k_update<T, 2>), grid, blk, 0, L.stream, a);
+  else if (a.implicit == 1)
+    hipLaunchKernelGGL((k_update<T, 1>), grid, blk, 0, L.stream, a);
+  else if (sizeof(T) == 4 && L.any_at)
+    hipLaunchKernelGGL((k_update<float, 3>), grid, blk, 0, L.stream, a);
+  else
+    hipLaunchKernelGGL((k_update<T, 0>), grid, blk, 0, L.stream, a);
+}
+
 template <typename T>
 static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
                                         const IterParams &ip, Part part) {
@@ -1867,6 +2218,19 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
   switch (part) {
     case Part::Local: {
       Timed tm(L, K_LOCAL);
+      if (a.implicit) {
+        // up to one workgroup per CU the registers of the nine-component Newton
+        // cost nothing and the second pass's launch (4.5 us) is saved: 16^3
+        // double; beyond, they halve the waves in flight
+        if (L.nblk_v <= 256) {
+          hipLaunchKernelGGL((k_local_i<T, kInlineI>), dim3(L.nblk_v), blk, 0, L.stream, a, ip);
+          break;
+        }
+        hipLaunchKernelGGL((k_local_i<T, kFirstI>), dim3(L.nblk_v), blk, 0, L.stream, a, ip);
+        hipLaunchKernelGGL((k_retry_i<T>), dim3(std::min(L.nblk_v, kLocalPassGrid)), blk, 0,
+                           L.stream, a, ip, L.nblk_v);
+        break;
+      }
       const bool inexact = ip.local_ratio > 0.0 || ip.local_fraction > 0.0;
       const int passes = inexact ? ip.local_passes : 1;
       if (L.any_frank) hipLaunchKernelGGL((k_lag<T>), dim3(L.nblk_x), blk, 0, L.stream, a);
@@ -1888,11 +2252,14 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
           hipLaunchKernelGGL((k_fsum<T>), dim3(L.nblk_x), blk, 0, L.stream, a);
           hipLaunchKernelGGL(k_fbar, dim3(a.n_rve), blk, 0, L.stream, a);
         }
-        hipLaunchKernelGGL((k_div_fwdx<T>), dim3(L.nblk_f), blk, L.lds_x, L.stream, a);
+        if (a.implicit)
+          hipLaunchKernelGGL((k_div_fwdx<T, true>), dim3(L.nblk_f), blk, L.lds_x, L.stream, a);
+        else
+          hipLaunchKernelGGL((k_div_fwdx<T, false>), dim3(L.nblk_f), blk, L.lds_x, L.stream, a);
       }
       {
         Timed tm(L, K_FFT_Y_FWD);
-        launch_fft_y<T, false>(L, a);
+        if (!L.plane) launch_fft_y<T, false>(L, a);
       }
       {
         Timed tm(L, K_POISSON_Z);
@@ -1900,7 +2267,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
       }
       {
         Timed tm(L, K_FFT_Y_INV);
-        launch_fft_y<T, true>(L, a);
+        if (!L.plane) launch_fft_y<T, true>(L, a);
       }
       {
         Timed tm(L, K_INV_X);
@@ -1914,7 +2281,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
     case Part::Update: {
       {
         Timed tm(L, K_UPDATE);
-        hipLaunchKernelGGL((k_update<T>), dim3(L.nblk_u), blk, 0, L.stream, a);
+        launch_update<T>(L, a);
       }
       {
         Timed tm(L, K_FINALIZE);
@@ -1922,11 +2289,15 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
       }
       break;
     }
+    case Part::Explicit: {
+      hipLaunchKernelGGL((k_explicit<T>), dim3(L.nblk_v), blk, 0, L.stream, a, ip);
+      break;
+    }
     case Part::StripNull: {
-      if (kDefect<T>) {
-        hipLaunchKernelGGL(k_null_sums, dim3(L.nblk_u), blk, 0, L.stream, a);
+      if (kDefect<T> || a.implicit) {
+        hipLaunchKernelGGL(k_null_sums, dim3(L.nblk_m), blk, 0, L.stream, a);
         hipLaunchKernelGGL(k_null_final, dim3(a.n_rve), blk, 0, L.stream, a);
-        hipLaunchKernelGGL(k_null_sub, dim3(L.nblk_u), blk, 0, L.stream, a);
+        hipLaunchKernelGGL(k_null_sub, dim3(L.nblk_m), blk, 0, L.stream, a);
       }
       break;
     }
@@ -1936,7 +2307,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
     }
     case Part::MeanStress: {
       Timed tm(L, K_MEAN);
-      hipLaunchKernelGGL((k_mean_stress<T>), dim3(L.nblk_u), blk, 0, L.stream, a);
+      hipLaunchKernelGGL((k_mean_stress<T>), dim3(L.nblk_m), blk, 0, L.stream, a);
       hipLaunchKernelGGL(k_mean_final, dim3(a.n_rve), blk, 0, L.stream, a);
       break;
     }
@@ -1971,6 +2342,14 @@ int reg_columns(bool fp64, int n) {
 }
 size_t reg_lds(bool fp64, int pmax) {
   return fp64 ? col16_lds<double2>() : (size_t)pmax * kColSlab * sizeof(float2);
+}
+
+// columns per workgroup of the plane-strain pass along x2: the x3 tile width,
+// halved until its lines fit 64 KiB of LDS
+int plane_tile(bool fp64, int n2max, int tile_z) {
+  const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);
+  while (tile_z > tile_b(fp64) / 4 && 2 * (size_t)n2max * tile_z * csz > 65536) tile_z /= 2;
+  return tile_z;
 }
 
 bool tile_compiled(bool fp64, int B) {

@@ -14,11 +14,14 @@ struct KernelArgs {
   const int *blk_y;
   const int *blk_z;
   const int *blk_u;
+  const int *blk_p;  // residual partials (and Newton statistics) of each cell
+  const int *blk_m;  // the mean-stress and null-mode sums
+  const int *blk_v;  // the implicit local step: kThreads voxels each
   const int *blk_f;  // the x1-transform kernels (div_fwdx, inv_x)
   const int *blk_i;  // the register-resident inverse x1 pass (32 real lines each)
   const Material *mats;
   const void *tw;       // twiddle pool (float2 or double2)
-  double4 *partials;    // per update workgroup: sum e^2, sum dd^2, and the failed
+  double4 *partials;    // per part (zpart planes of an x2 group): sum e^2, sum dd^2, and the failed
                         // solves and Newton iterations of its rows' local step
   double *partials18;   // per workgroup: sums of P and Lambda
   double *mean_out;     // per cell: <P>, <Lambda>
@@ -27,15 +30,19 @@ struct KernelArgs {
                         // residual|^2, count of converged local solves)
   double *fpart;        // per local workgroup: sums of F - I - Lambda/rho (9), for
                         // the free components of <F>
-  int2 *newton_part;    // per update workgroup: failed solves and Newton iterations
+  int2 *newton_part;    // per part: failed solves and Newton iterations
                         // of the local-step workgroups in its tile
   unsigned *retry_mask; // per local workgroup, kThreads bits: voxels the exact
                         // pass's closed form left to the retry pass (zero between
                         // steps)
-  double *nullpart;     // per update workgroup: 24 sums of u_i chi_s (float form)
-  double *nullc;        // per cell: 24 null-mode coefficients of u
+  double *nullpart;     // per workgroup: 24 sums of u_i chi_s and of |u|^2
+  double *nullc;        // per cell: 24 null-mode coefficients of u, then whether
+                        // any is not zero
   int n_rve;
   int n_mat;
+  // 0: F and Lambda are read and written every iteration; 1: an implicit
+  // iteration (RveDesc::Ai, Qi); 2: the same, its update writing F and Lambda
+  int implicit;
 };
 
 // kernel ids of the profiling interface (same order as in include/admm.h)
@@ -55,7 +62,8 @@ struct KernelTimer {
 struct LaunchCfg {
   KernelTimer *timer;  // null unless profiling
   hipStream_t stream;
-  int nblk_x, nblk_y, nblk_z, nblk_u, nblk_f;
+  int nblk_x, nblk_y, nblk_z, nblk_u, nblk_f, nblk_m, nblk_v;
+  int thr_u;   // threads per workgroup of the update
   // float cells all of x1 length 256: the inverse x1 pass runs register
   // resident (k_inv_x256), nblk_i workgroups
   bool inv256;
@@ -65,17 +73,20 @@ struct LaunchCfg {
   size_t lds_coly, lds_colz;  // LDS bytes of the register-resident passes
   bool col256_y, col256_z;     // every length along x2 (x3) is 256: k_col16
   int n2max, n3max;
+  bool plane;    // every cell has n3 = 1: the solve runs in one pass along x2
   size_t lds_x;  // LDS bytes of the x1-pass kernels
   bool any_lce;   // some phase uses the LCE energy
   int lce_kind;   // 0 no LCE, 1 the ideal LCE, 2 some term of the full model or nu_F
+  bool any_at;    // RveDesc::At is there
   bool any_frank; // the Frank term needs the previous iteration's directors
   bool any_free;  // some cell leaves components of <F> free
 };
 
 // ComposeU: after a single Step 2 call of the float form, u_prev = u + du.
 // StripNull: the float form removes the mean and the Nyquist checkerboards
-// of u (which D_h does not see) before it iterates.
-enum class Part { Local, Project, Update, MeanStress, ComposeU, StripNull };
+// of u (which D_h does not see) before it iterates; so do implicit
+// iterations. Explicit: F and Lambda of the cells left implicit.
+enum class Part { Local, Project, Update, MeanStress, ComposeU, StripNull, Explicit };
 
 // Bloch-wave stability modulus of one cell (double precision; bloch.hip).
 // p: 3V complex (interleaved) start in, unit mode out. Returns 0, -1 (HIP
@@ -108,6 +119,7 @@ hipError_t launch_part(const LaunchCfg &L, const KernelArgs &a, const IterParams
 // quarter, half, default, double)
 int tile_b(bool fp64);
 bool tile_compiled(bool fp64, int B);
+int plane_tile(bool fp64, int n2max, int tile_z);
 int reg_points(bool fp64, int n);
 int reg_columns(bool fp64, int n);
 size_t reg_lds(bool fp64, int pmax);

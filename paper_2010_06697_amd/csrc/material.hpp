@@ -551,10 +551,10 @@ __device__ __forceinline__ float warm_code(double jm1) {
   return f > -1.0f ? f : -0x1.fffffep-1f;
 }
 
-// E: out (written only when the return value is >= 0); jw: warm_code of
-// det(I + E) - 1 of the warm start
+// Q: F - A out (written only when the return value is >= 0; At: A - I); jw:
+// warm_code of det F - 1 of the warm start
 template <typename TG>
-__device__ int neo_closed(TG *E, const TG *At, float jw, double mu, double lam, double rho,
+__device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double lam, double rho,
                           int maxit, double tol) {
   if (!(1.0 + (double)jw > 0.0)) return -2;
   double a[9];
@@ -706,13 +706,13 @@ __device__ int neo_closed(TG *E, const TG *At, float jw, double mu, double lam, 
                        sym(C1, i, 2) * sym(C2, 2, j);
       Pm[3 * i + j] = (i == j ? d[0] : 0.0) + h12 * sym(C1, i, j) + h123 * q;
     }
-  // E = F - I = (P - I) + (P - I) a + a
+  // F - A = (P - I) A = (P - I) + (P - I) a
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
     for (int j = 0; j < 3; ++j)
-      E[3 * i + j] = (TG)(Pm[3 * i + j] + a[3 * i + j] +
-                          (Pm[3 * i] * a[j] + Pm[3 * i + 1] * a[3 + j] + Pm[3 * i + 2] * a[6 + j]));
+      Q[3 * i + j] = Pm[3 * i + j] +
+                     (Pm[3 * i] * a[j] + Pm[3 * i + 1] * a[3 + j] + Pm[3 * i + 2] * a[6 + j]);
   return it;
 }
 
