@@ -203,8 +203,8 @@ __device__ __forceinline__ bool local_inexact(const IterParams &ip, const RveSta
 // the exact step's second pass over the problems its first pass left to the
 // nine-component Newton method (float form without LCE phases: the first
 // pass then compiles only the neo-Hookean closed form, at the registers
-// that need). The double form finishes the closed form's point with one
-// full Newton step and runs the Newton solve where the closed form fails.
+// that need). The double form runs the Newton solve where the closed form
+// fails.
 enum LocalMode { kLocalExact = 0, kLocalFirst = 1, kLocalLater = 2, kLocalRetry = 3 };
 static_assert(kThreads / 32 == 8, "the retry pass reads a workgroup's bits as two uint4");
 template <typename T, int LK, int MODE>
@@ -415,10 +415,7 @@ __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass
         M.lam = (T)m.lam;
         // exact mode: the minimiser up to one scalar; the nine-component
         // Newton where that form does not apply (in the retry pass when the
-        // closed form is compiled alone). In the double form the closed
-        // form's point (about 1e-12 relative, least accurate along
-        // rotations, where the objective is only rho-stiff and Newton's
-        // stopping test would accept it) is finished by one full Newton step.
+        // closed form is compiled alone).
         rc = -3;
         if (MODE == kLocalExact) {
           double Qd[9];
@@ -435,7 +432,6 @@ __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass
             rc = 0;
           }
         } else {
-          if (!kDefect<T> && rc >= 0) rc = newton_polish<T, T>(E, At, M, (T)rho) ? rc + 1 : -3;
           if (rc == -3)
             rc = newton<T, T>(E, At, M, (T)rho, cap, ip.gtol, ip.step_tol,
                                MODE == kLocalExact || MODE == kLocalRetry ? nullptr : &lsum[0]);
@@ -563,24 +559,6 @@ void k_local(KernelArgs a, IterParams ip, int pass, int nblk) {
 // du and Q.
 // ----------------------------------------------------------------------------
 
-// The closed form's point of a neo-Hookean voxel, as F - A; in the double form
-// (about 1e-12 along rotations) finished by one full Newton step. Returns as
-// neo_closed.
-template <typename T>
-__device__ __forceinline__ int closed_point(double *Q, const T *At, float jw, const Material &m,
-                                            const NeoHooke<T> &M, double rho, int cap) {
-  int rc = neo_closed<T>(Q, At, jw, m.mu, m.lam, rho, cap, 1e-5);
-  if (!kDefect<T> && rc >= 0) {
-    T E[9];
-#pragma unroll
-    for (int c = 0; c < 9; ++c) E[c] = (T)((double)At[c] + Q[c]);
-    rc = newton_polish<T, T>(E, At, M, (T)rho) ? rc + 1 : -3;
-#pragma unroll
-    for (int c = 0; c < 9; ++c) Q[c] = (double)E[c] - (double)At[c];
-  }
-  return rc;
-}
-
 // KIND: the first pass, which leaves the voxels without a closed form to the
 // second (kRetryI), or solves them itself (kInlineI)
 enum ImplicitLocal { kFirstI = 0, kRetryI = 1, kInlineI = 2 };
@@ -664,7 +642,7 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
       NeoHooke<T> M;
       M.mu = (T)m.mu;
       M.lam = (T)m.lam;
-      if (!RETRY) rc = closed_point<T>(Q, At, jw, m, M, rho, ip.newton_max);
+      if (!RETRY) rc = neo_closed<T>(Q, At, jw, m.mu, m.lam, rho, ip.newton_max, 1e-5);
       if (KIND == kFirstI && rc == -3) {
         atomicOr(&retry[t >> 5], 1u << (t & 31));
         atomicAdd(&st->n_retry, 1);
@@ -754,11 +732,8 @@ __global__ __launch_bounds__(kThreads) void k_explicit(KernelArgs a, IterParams 
   const int ph = global_view(D.phase)[idx];
   if (kDefect<T> && ph < a.n_mat) {
     const Material m = a.mats[ph];
-    NeoHooke<T> M;
-    M.mu = (T)m.mu;
-    M.lam = (T)m.lam;
     double q[9];
-    if (closed_point<T>(q, A, warm_code(warm_jm1(E)), m, M, rho, ip.newton_max) >= 0)
+    if (neo_closed<T>(q, A, warm_code(warm_jm1(E)), m.mu, m.lam, rho, ip.newton_max, 1e-5) >= 0)
 #pragma unroll
       for (int c = 0; c < 9; ++c) E[c] = (T)((double)A[c] + q[c]);
   }

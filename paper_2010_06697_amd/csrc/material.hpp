@@ -288,10 +288,8 @@ template <typename TG> __device__ __forceinline__ bool admissible(const TG *E) {
 }
 
 // The iterations of newton() from the point s at E; on exit s is the point
-// of the returned iterate when KEEP is set (otherwise it may be stale). ONE:
-// a single full Newton step, no stopping test and no line search (returns 1,
-// or -1 with E unchanged where the tangent is not positive definite).
-template <typename TG, typename TH, bool KEEP, typename M, bool ONE = false>
+// of the returned iterate when KEEP is set (otherwise it may be stale).
+template <typename TG, typename TH, bool KEEP, typename M>
 __device__ int newton_loop(TG *E, const TG *A, const M &m, TG rho, int maxit, double gtol,
                            double step_tol, Point<TG> &s) {
   const double smod = m.smod() + (double)rho;
@@ -304,7 +302,7 @@ __device__ int newton_loop(TG *E, const TG *A, const M &m, TG rho, int maxit, do
   for (int it = 0; it < maxit; ++it) {
     const double nF2 = (double)norm2_ipx(E);
     const double thr = gtol * smod * (1.0 + sqrt(nF2) + nA);
-    if (!ONE && (double)s.gn2 <= thr * thr) return it;
+    if ((double)s.gn2 <= thr * thr) return it;
 
     // prox tangent, lower triangle packed, assembled in TH
     TH L[45], Gh[9], id[9];
@@ -360,12 +358,6 @@ __device__ int newton_loop(TG *E, const TG *A, const M &m, TG rho, int maxit, do
     } else {
 #pragma unroll
       for (int i = 0; i < 9; ++i) d[i] = -s.g[i];
-    }
-    if (ONE) {
-      if (!pd) return -1;
-#pragma unroll
-      for (int k = 0; k < 9; ++k) E[k] += d[k];
-      return 1;
     }
 
     TG slope_t = (TG)0, nd2_t = (TG)0;
@@ -442,16 +434,6 @@ __device__ int newton_loop(TG *E, const TG *A, const M &m, TG rho, int maxit, do
 // up (E keeps the last accepted iterate; a second call with the remaining
 // budget continues the same iterates), -2 when det F <= 0 at the start.
 // g2 (optional) receives |grad phi|^2 at the returned iterate.
-// One full Newton step from E, for a point inside the region of quadratic
-// convergence (the closed form's): no line search. False (E unchanged) when
-// det F <= 0 at E or the tangent is not positive definite there.
-template <typename TG, typename TH, typename M>
-__device__ bool newton_polish(TG *E, const TG *A, const M &m, TG rho) {
-  Point<TG> s;
-  if (!m.point(E, A, rho, s)) return false;
-  return newton_loop<TG, TH, false, M, true>(E, A, m, rho, 1, 0.0, 0.0, s) == 1;
-}
-
 template <typename TG, typename TH, typename M>
 __device__ int newton(TG *E, const TG *A, const M &m, TG rho, int maxit, double gtol,
                       double step_tol, double *g2 = nullptr) {
@@ -580,12 +562,13 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
              a[3 * i + 2] * a[3 * j + 2];
     }
   }
-  // eigenvalues e_1 >= e_2 >= e_3 of B - I: the roots t = 2 p cos(angle) of
-  // the deviator's characteristic cubic t^3 - 3 p2 t - det = 0 from the
-  // angle in float, then one Newton step each in double (the error goes
-  // from float's to double's; at a double root the step is skipped, and
-  // there an error in the nodes moves g and P only at second order); their
-  // sum is exact by construction
+  // eigenvalues e_1 >= e_2 >= e_3 of B - I: the deviator's are p u with the
+  // roots u of u^3 - 3 u = 2 r, |r| <= 1. The root of r's sign lies in
+  // [sqrt 3, 2] away from the other two (slope 3 (u^2 - 1) >= 6): a cubic in
+  // |r| within 4e-4 and Newton's steps, squaring the error each, give it to
+  // 6e-15 (two, float form) or to rounding (three, double form). The other two
+  // follow from the quadratic that is left; their difference is inexact near a
+  // double root, their sum and product are not, and P depends on those alone.
   const double qm = (b[0] + b[1] + b[2]) * (1.0 / 3.0);
   const double c00 = b[0] - qm, c11 = b[1] - qm, c22 = b[2] - qm;
   const double p2 = (c00 * c00 + c11 * c11 + c22 * c22 +
@@ -594,21 +577,22 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
   if (p2 > 1e-60) {
     const double dC = c00 * (c11 * c22 - b[5] * b[5]) - b[3] * (b[3] * c22 - b[5] * b[4]) +
                       b[4] * (b[3] * b[5] - c11 * b[4]);
-    const float p2f = (float)p2, pf = __builtin_amdgcn_sqrtf(p2f);
-    const float r = fminf(1.0f, fmaxf(-1.0f, (float)dC * __builtin_amdgcn_rcpf(2.0f * p2f * pf)));
-    const float cpf = __cosf(acosf(r) * (1.0f / 3.0f));  // angle in [0, pi/3]
-    const float spf = __builtin_amdgcn_sqrtf(fmaxf(0.0f, 1.0f - cpf * cpf));
-    double t1 = (double)(2.0f * pf * cpf);
-    double t3 = (double)(2.0f * pf * (-0.5f * cpf - 0.8660254f * spf));  // angle + 2 pi/3
-    auto refine = [&](double &t) {
-      const double dp = 3.0 * (t * t - p2);
-      if (fabs(dp) > 1e-3 * p2) t -= (t * (t * t - 3.0 * p2) - dC) * rcp_nr(dp);
-    };
-    refine(t1);
-    refine(t3);
-    e1 = qm + t1;
-    e3 = qm + t3;
-    e2 = 3.0 * qm - e1 - e3;
+    const double ip = rsqrt_nr(p2), pp = p2 * ip;
+    const double r = fmin(1.0, fabs(0.5 * dC * (ip * ip * ip)));
+    double u = fma(fma(fma(0.02387, r, -0.08925), r, 1.0 / 3.0), r, 1.7320508075688773);
+    constexpr int kSteps = sizeof(TG) == 4 ? 2 : 3;
+#pragma unroll
+    for (int s = 0; s < kSteps; ++s) {
+      const double uu = u * u;
+      u -= (u * (uu - 3.0) - 2.0 * r) * rcp_nr(3.0 * uu - 3.0);
+    }
+    const double q4 = fmax(fma(-0.75 * u, u, 3.0), 0.0);
+    const double w = q4 > 0.0 ? pp * sqrt_nr(q4) : 0.0, t = pp * u;
+    const double up = 0.5 * t + w, um = 0.5 * t - w;
+    const bool pos = dC >= 0.0;
+    e1 = qm + (pos ? t : up);
+    e2 = qm + (pos ? -um : um);
+    e3 = qm + (pos ? -up : -t);
   }
   const double x1 = 1.0 + e1, x2 = 1.0 + e2, x3 = 1.0 + e3;
   if (!(x3 > 0.0)) return -3;
@@ -660,29 +644,34 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
   }
   if (!done) return -3;
   // one Newton step in double from there (the error goes from float's to
-  // its square), with S_i and h_i - 1 carried to the new gamma to first
-  // order (dS/dgamma = -2m / (x S), dh/dgamma = -1 / (x S))
+  // its square; the double form takes a second), with S_i and h_i - 1 carried
+  // to the new gamma to first order (dS/dgamma = -2m / (x S), dh/dgamma =
+  // -1 / (x S))
   double G = (double)gam;
   double S[3], d[3], w[3];
 #pragma unroll
-  for (int i = 0; i < 3; ++i) {
-    S[i] = sqrt_nr(r2 - 4.0 * m * (G - mu) * ixd[i]);
-    d[i] = -2.0 * (G + mu * es[i]) * ixd[i] * rcp_nr(S[i] + rho + 2.0 * mu);
-    w[i] = ixd[i] * rcp_nr(S[i]);  // -dh_i/dgamma
-  }
-  {
-    const double dp = d[0] + d[1] + d[2] + (d[0] * d[1] + d[0] * d[2] + d[1] * d[2]) +
-                      d[0] * d[1] * d[2];
-    const double g = G - lam * (lnA + log1p_near1_nr(dp));
-    const double sw = w[0] * rcp_nr(1.0 + d[0]) + w[1] * rcp_nr(1.0 + d[1]) +
-                      w[2] * rcp_nr(1.0 + d[2]);
-    const double delta = -g * rcp_nr(1.0 + lam * sw);
-    G += delta;
+  for (int s = sizeof(TG) == 4 ? 1 : 0; s < 2; ++s) {
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      S[i] -= 2.0 * m * w[i] * delta;
-      d[i] -= w[i] * delta;
+      S[i] = sqrt_nr(r2 - 4.0 * m * (G - mu) * ixd[i]);
+      d[i] = -2.0 * (G + mu * es[i]) * ixd[i] * rcp_nr(S[i] + rho + 2.0 * mu);
+      w[i] = ixd[i] * rcp_nr(S[i]);  // -dh_i/dgamma
     }
+    {
+      const double dp = d[0] + d[1] + d[2] + (d[0] * d[1] + d[0] * d[2] + d[1] * d[2]) +
+                        d[0] * d[1] * d[2];
+      const double g = G - lam * (lnA + log1p_near1_nr(dp));
+      const double sw = w[0] * rcp_nr(1.0 + d[0]) + w[1] * rcp_nr(1.0 + d[1]) +
+                        w[2] * rcp_nr(1.0 + d[2]);
+      const double delta = -g * rcp_nr(1.0 + lam * sw);
+      G += delta;
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+        S[i] -= 2.0 * m * w[i] * delta;
+        d[i] -= w[i] * delta;
+      }
+    }
+    if (sizeof(TG) == 8 && !(G < ghi)) return -3;
   }
   if (!(G < ghi)) return -3;
   // P - I = (h_1 - 1) I + h[x1,x2] (B - x1 I) + h[x1,x2,x3] (B - x1 I)(B - x2 I)
@@ -713,7 +702,7 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
     for (int j = 0; j < 3; ++j)
       Q[3 * i + j] = Pm[3 * i + j] +
                      (Pm[3 * i] * a[j] + Pm[3 * i + 1] * a[3 + j] + Pm[3 * i + 2] * a[6 + j]);
-  return it;
+  return sizeof(TG) == 4 ? it : it + 1;  // (with the double form's second step)
 }
 
 // ---------------------------------------------------------------------------
