@@ -550,7 +550,6 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
                                             (a[0] * a[4] - a[1] * a[3])) +
                     (a[0] * m0 + a[1] * m1 + a[2] * m2);
   if (!(jA > -1.0)) return -3;
-  const double lnA = log1p_near1_nr(jA);
   // B - I = a + a^T + a a^T
   double b[6];  // 00 11 22 01 02 12
   {
@@ -584,7 +583,7 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
 #pragma unroll
     for (int s = 0; s < kSteps; ++s) {
       const double uu = u * u;
-      u -= (u * (uu - 3.0) - 2.0 * r) * rcp_nr(3.0 * uu - 3.0);
+      u -= (u * (uu - 3.0) - 2.0 * r) * __builtin_amdgcn_rcp(3.0 * uu - 3.0);
     }
     const double q4 = fmax(fma(-0.75 * u, u, 3.0), 0.0);
     const double w = q4 > 0.0 ? pp * sqrt_nr(q4) : 0.0, t = pp * u;
@@ -598,14 +597,18 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
   if (!(x3 > 0.0)) return -3;
   const double m = mu + rho, r2 = rho * rho;
   const double es[3] = {e1, e2, e3};
-  const double ixd[3] = {rcp_nr(x1), rcp_nr(x2), rcp_nr(x3)};
+  const double x12 = x1 * x2, ix123 = rcp_nr(x12 * x3), ix12 = ix123 * x3;
+  const double ixd[3] = {ix12 * x2, ix12 * x1, ix123 * x12};
   const double ghi = mu + r2 * x3 / (4.0 * m);  // S(x_3) real up to here
-  // gamma to float accuracy by Newton's method in float (hardware
-  // reciprocal, square root and logarithm: the step in double below removes
-  // their error too), kept inside the bracket [lo, hi] of g's sign change
+  // gamma by Newton's method in float (hardware reciprocals, square roots and
+  // logarithm), kept inside the bracket [lo, hi] of g's sign change, until a
+  // step is small against gamma and against the distance to ghi, where S_3's
+  // root makes g steep: the error left is that ratio's square (4e-6), and the
+  // steps in double below square it again. With H = h_1 h_2 h_3 the step
+  // g / g' is g H / (H + lambda sum_i H / (x_i S_i h_i)), one reciprocal.
   const float lamf = (float)lam, muf = (float)mu;
-  const float r2f = (float)r2, m4f = (float)(4.0 * m), lnAf = (float)lnA;
-  const float c2f = (float)(rho + 2.0 * mu);
+  const float r2f = (float)r2, m4f = (float)(4.0 * m), jAf = (float)jA;
+  const float c2f = (float)(rho + 2.0 * mu), ghif = (float)ghi;
   float ix[3], ef[3];
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
@@ -613,26 +616,28 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
     ef[i] = (float)es[i];
   }
   constexpr float kLn2 = 0.69314718f;
-  float lo = -INFINITY, hi = (float)ghi;
+  float lo = -INFINITY, hi = ghif;
   float gam = fminf(lamf * kLn2 * __builtin_amdgcn_logf(1.0f + jw), 0.5f * hi);
   int it = 0;
   bool done = false;
   for (; it < maxit; ++it) {
-    float Sf[3], df[3];
+    float hf[3], wf[3], df[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      Sf[i] = __builtin_amdgcn_sqrtf(fmaxf(0.0f, r2f - m4f * (gam - muf) * ix[i]));
-      df[i] = -2.0f * (gam + muf * ef[i]) * ix[i] * __builtin_amdgcn_rcpf(Sf[i] + c2f);
+      const float s2 = fmaxf(1e-12f * r2f, r2f - m4f * (gam - muf) * ix[i]);
+      const float rs = __builtin_amdgcn_rsqf(s2);
+      df[i] = -2.0f * (gam + muf * ef[i]) * ix[i] * __builtin_amdgcn_rcpf(s2 * rs + c2f);
+      hf[i] = 1.0f + df[i];
+      wf[i] = ix[i] * rs;
     }
     const float dp = df[0] + df[1] + df[2] + (df[0] * df[1] + df[0] * df[2] + df[1] * df[2]) +
                      df[0] * df[1] * df[2];
-    const float g = gam - lamf * (lnAf + kLn2 * __builtin_amdgcn_logf(1.0f + dp));
+    const float H = 1.0f + dp;
+    const float g = gam - lamf * (kLn2 * __builtin_amdgcn_logf(1.0f + (jAf + dp + jAf * dp)));
     if (g > 0.0f) hi = gam; else lo = gam;
-    const float gp = 1.0f + lamf * (ix[0] * __builtin_amdgcn_rcpf(Sf[0] * (1.0f + df[0])) +
-                                    ix[1] * __builtin_amdgcn_rcpf(Sf[1] * (1.0f + df[1])) +
-                                    ix[2] * __builtin_amdgcn_rcpf(Sf[2] * (1.0f + df[2])));
-    const float step = g * __builtin_amdgcn_rcpf(gp);
-    if (fabsf(step) <= (float)tol * (1.0f + fabsf(gam))) {
+    const float n = (wf[0] * hf[1] + wf[1] * hf[0]) * hf[2] + wf[2] * (hf[0] * hf[1]);
+    const float step = g * H * __builtin_amdgcn_rcpf(H + lamf * n);
+    if (fabsf(step) <= (float)tol * fminf(1.0f + fabsf(gam), ghif - gam)) {
       gam -= step;
       done = true;
       ++it;
@@ -643,57 +648,65 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
     gam = nx;
   }
   if (!done) return -3;
-  // one Newton step in double from there (the error goes from float's to
-  // its square; the double form takes a second), with S_i and h_i - 1 carried
-  // to the new gamma to first order (dS/dgamma = -2m / (x S), dh/dgamma =
-  // -1 / (x S))
+  // one Newton step in double from there (the double form takes a second),
+  // with S_i and h_i - 1 carried to the new gamma to first order (dS/dgamma =
+  // -2m / (x S), dh/dgamma = -1 / (x S)). 1 / S_i is the square root's own
+  // reciprocal after one refinement, and the step's denominator is not refined:
+  // both only scale the step. The three h_i share one reciprocal.
   double G = (double)gam;
   double S[3], d[3], w[3];
 #pragma unroll
   for (int s = sizeof(TG) == 4 ? 1 : 0; s < 2; ++s) {
+    double q[3];
 #pragma unroll
     for (int i = 0; i < 3; ++i) {
-      S[i] = sqrt_nr(r2 - 4.0 * m * (G - mu) * ixd[i]);
-      d[i] = -2.0 * (G + mu * es[i]) * ixd[i] * rcp_nr(S[i] + rho + 2.0 * mu);
-      w[i] = ixd[i] * rcp_nr(S[i]);  // -dh_i/dgamma
+      const double s2 = r2 - 4.0 * m * (G - mu) * ixd[i];
+      double rs = __builtin_amdgcn_rsq(s2);
+      rs = rs * fma(-0.5 * s2 * rs, rs, 1.5);
+      const double s1 = s2 * rs;
+      S[i] = fma(0.5 * rs, fma(-s1, s1, s2), s1);
+      w[i] = ixd[i] * rs;  // -dh_i/dgamma
+      q[i] = S[i] + rho + 2.0 * mu;
     }
-    {
-      const double dp = d[0] + d[1] + d[2] + (d[0] * d[1] + d[0] * d[2] + d[1] * d[2]) +
-                        d[0] * d[1] * d[2];
-      const double g = G - lam * (lnA + log1p_near1_nr(dp));
-      const double sw = w[0] * rcp_nr(1.0 + d[0]) + w[1] * rcp_nr(1.0 + d[1]) +
-                        w[2] * rcp_nr(1.0 + d[2]);
-      const double delta = -g * rcp_nr(1.0 + lam * sw);
-      G += delta;
+    const double q01 = q[0] * q[1], iq = rcp_nr(q01 * q[2]), iq01 = iq * q[2];
+    const double ic[3] = {iq01 * q[1], iq01 * q[0], iq * q01};
 #pragma unroll
-      for (int i = 0; i < 3; ++i) {
-        S[i] -= 2.0 * m * w[i] * delta;
-        d[i] -= w[i] * delta;
-      }
+    for (int i = 0; i < 3; ++i) d[i] = -2.0 * (G + mu * es[i]) * ixd[i] * ic[i];
+    const double dp = d[0] + d[1] + d[2] + (d[0] * d[1] + d[0] * d[2] + d[1] * d[2]) +
+                      d[0] * d[1] * d[2];
+    const double g = G - lam * log1p_near1_nr(jA + dp + jA * dp);
+    const double h0 = 1.0 + d[0], h1 = 1.0 + d[1], h2 = 1.0 + d[2];
+    const double n = (w[0] * h1 + w[1] * h0) * h2 + w[2] * (h0 * h1);
+    const double delta = -g * (1.0 + dp) * __builtin_amdgcn_rcp(fma(lam, n, 1.0 + dp));
+    G += delta;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+      S[i] -= 2.0 * m * w[i] * delta;
+      d[i] -= w[i] * delta;
     }
     if (sizeof(TG) == 8 && !(G < ghi)) return -3;
   }
   if (!(G < ghi)) return -3;
   // P - I = (h_1 - 1) I + h[x1,x2] (B - x1 I) + h[x1,x2,x3] (B - x1 I)(B - x2 I)
   const double km = 2.0 * (G - mu);  // 4 m c / (2 m)
-  const double i12 = ixd[0] * ixd[1] * rcp_nr(S[0] + S[1]);
-  const double h12 = km * i12;
-  const double h123 = -km * i12 * ixd[2] * rcp_nr(S[1] + S[2]) *
-                      (S[1] + (r2 * (x1 + x3) - 2.0 * m * km) * rcp_nr(x3 * S[2] + x1 * S[0]));
+  const double sa = S[0] + S[1], sb = S[1] + S[2], sc = x3 * S[2] + x1 * S[0];
+  const double sab = sa * sb, is = rcp_nr(sab * sc), isc = is * sc;
+  const double h12 = km * (ixd[0] * ixd[1]) * (isc * sb);
+  const double h123 = -h12 * ixd[2] * (isc * sa) * (S[1] + (r2 * (x1 + x3) - 2.0 * m * km) * (is * sab));
   // C1 = B - x1 I, C2 = B - x2 I (symmetric, in the order of b)
   const double C1[6] = {b[0] - e1, b[1] - e1, b[2] - e1, b[3], b[4], b[5]};
   const double C2[6] = {b[0] - e2, b[1] - e2, b[2] - e2, b[3], b[4], b[5]};
   auto sym = [](const double *M, int i, int j) {
     return i == j ? M[i] : M[i + j + 2];  // (0,1) -> 3, (0,2) -> 4, (1,2) -> 5
   };
-  double Pm[9];
+  double Pm[9];  // symmetric (C1 and C2 commute)
 #pragma unroll
   for (int i = 0; i < 3; ++i)
 #pragma unroll
-    for (int j = 0; j < 3; ++j) {
+    for (int j = i; j < 3; ++j) {
       const double q = sym(C1, i, 0) * sym(C2, 0, j) + sym(C1, i, 1) * sym(C2, 1, j) +
                        sym(C1, i, 2) * sym(C2, 2, j);
-      Pm[3 * i + j] = (i == j ? d[0] : 0.0) + h12 * sym(C1, i, j) + h123 * q;
+      Pm[3 * i + j] = Pm[3 * j + i] = (i == j ? d[0] : 0.0) + h12 * sym(C1, i, j) + h123 * q;
     }
   // F - A = (P - I) A = (P - I) + (P - I) a
 #pragma unroll
