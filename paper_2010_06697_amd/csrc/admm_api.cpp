@@ -436,36 +436,43 @@ int set_tiles(admm_ctx *c, int ty, int tz) {
   const int n = c->n_rve;
   int *by = c->blk_h.data() + (n + 1), *bz = c->blk_h.data() + 2 * (n + 1);
   by[0] = bz[0] = 0;
-  int py = 0, pz = 0;
+  LaunchCfg &L = c->L;
+  L.lds_coly = L.lds_colz = 0;
+  L.big_y = L.big_z = false;
+  L.col256_y = L.col256_z = true;
   for (int r = 0; r < n; ++r) {
-    const RveDesc &D = c->desc_h[r];
+    RveDesc &D = c->desc_h[r];
+    const int nz = L.plane ? D.n2 : D.n3;  // lines of the solving pass
+    L.col256_y = L.col256_y && D.n2 == 256;
+    L.col256_z = L.col256_z && D.n3 == 256;
     if (ty == kTileCol16) {
       const int cw = reg_columns(c->fp64, D.n2);
       by[r + 1] = by[r] + (D.n3 * D.m1 + cw - 1) / cw;
-      py = std::max(py, reg_points(c->fp64, D.n2));
+      L.lds_coly = std::max(L.lds_coly, reg_lds(c->fp64, reg_points(c->fp64, D.n2)));
     } else {
-      by[r + 1] = by[r] + D.n3 * ((D.m1 + ty - 1) / ty);
+      D.lcb2 = cols_log2(c->fp64, D.n2, ty);
+      by[r + 1] = by[r] + ((D.n3 * D.m1 - 1) >> D.lcb2) + 1;
+      L.lds_coly = std::max(L.lds_coly, cols_lds(c->fp64, D.n2, D.lcb2));
+      L.big_y = L.big_y || cols_big(D.n2);
     }
     if (tz == kTileCol16) {
       const int cw = reg_columns(c->fp64, D.n3);
       bz[r + 1] = bz[r] + (D.n2 * D.m1 + cw - 1) / cw;
-      pz = std::max(pz, reg_points(c->fp64, D.n3));
+      L.lds_colz = std::max(L.lds_colz, reg_lds(c->fp64, reg_points(c->fp64, D.n3)));
     } else {
-      const int w = c->L.plane ? plane_tile(c->fp64, c->L.n2max, tz) : tz;
-      bz[r + 1] = bz[r] + ((c->L.plane ? 1 : D.n2) * D.m1s + w - 1) / w;
+      const int lcb = cols_log2(c->fp64, nz, tz);
+      (L.plane ? D.lcb2 : D.lcb3) = lcb;
+      bz[r + 1] = bz[r] + (((L.plane ? 1 : D.n2) * D.m1 - 1) >> lcb) + 1;
+      L.lds_colz = std::max(L.lds_colz, cols_lds(c->fp64, nz, lcb));
+      L.big_z = L.big_z || cols_big(nz);
     }
   }
-  c->L.col256_y = c->L.col256_z = true;
-  for (const RveDesc &D : c->desc_h) {
-    c->L.col256_y = c->L.col256_y && D.n2 == 256;
-    c->L.col256_z = c->L.col256_z && D.n3 == 256;
-  }
-  c->L.lds_coly = reg_lds(c->fp64, py);
-  c->L.lds_colz = reg_lds(c->fp64, pz);
-  c->L.tile_y = ty;
-  c->L.tile_z = tz;
-  c->L.nblk_y = by[n];
-  c->L.nblk_z = bz[n];
+  L.tile_y = ty;
+  L.tile_z = tz;
+  L.nblk_y = by[n];
+  L.nblk_z = bz[n];
+  HIP_TRY(hipMemcpyAsync(c->desc_d, c->desc_h.data(), sizeof(RveDesc) * n, hipMemcpyHostToDevice,
+                         c->stream));
   HIP_TRY(hipMemcpyAsync(c->blk_d, c->blk_h.data(), sizeof(int) * c->blk_h.size(),
                          hipMemcpyHostToDevice, c->stream));
   HIP_TRY(hipStreamSynchronize(c->stream));
@@ -1033,8 +1040,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     bx[r + 1] = bx[r] + (nrows + D.rows - 1) / D.rows;
     bf[r + 1] = bf[r] + (nrows + D.rows_f - 1) / D.rows_f;
     bi[r + 1] = bi[r] + (3 * nrows + 31) / 32;
-    by[r + 1] = by[r] + D.n3 * ((D.m1 + B - 1) / B);
-    bz[r + 1] = bz[r] + ((plane ? 1 : D.n2) * D.m1s + Bz - 1) / Bz;
+    by[r + 1] = bz[r + 1] = 0;  // (set_tiles below)
     n2max = std::max(n2max, D.n2);
     n3max = std::max(n3max, D.n3);
     lds_x = std::max(lds_x, 2 * ((3 * D.rows_f + 1) / 2) * D.n1);
@@ -1100,8 +1106,6 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   c->L.any_free = false;
   c->L.stream = c->stream;
   c->L.nblk_x = bx[n_rve];
-  c->L.nblk_y = by[n_rve];
-  c->L.nblk_z = bz[n_rve];
   c->L.tile_y = B;
   c->L.tile_z = Bz;
   c->L.plane = plane;
@@ -1236,7 +1240,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   A.fpart = c->fpart_d;
   A.n_rve = n_rve;
   A.n_mat = n_mat;
-  if (snapshot_step(c) != ADMM_OK || hipStreamSynchronize(c->stream) != hipSuccess) {
+  if (set_tiles(c, c->L.tile_y, c->L.tile_z) != ADMM_OK || snapshot_step(c) != ADMM_OK || hipStreamSynchronize(c->stream) != hipSuccess) {
     free_ctx(c);
     return ADMM_EHIP;
   }

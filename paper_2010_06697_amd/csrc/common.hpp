@@ -57,6 +57,8 @@ struct RveDesc {
   long long S;              // complex entries of one spectral component
   int rows;                 // x1-lines per workgroup of the per-voxel kernels
   int rows_f;               // x1-lines per workgroup of the x1 transforms
+  int lcb2, lcb3;           // log2 of the columns per workgroup of the x2 and x3
+                            // column passes (k_cols)
   int zseg;                 // planes a workgroup of the update walks
   int zpart;                // planes per residual partial (divides zseg)
   int zmean;                // planes per workgroup of the mean-stress and

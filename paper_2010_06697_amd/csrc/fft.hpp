@@ -140,12 +140,39 @@ template <bool INV, typename C> __device__ __forceinline__ void dft24(C *v) {
   dft_split<8, 3, INV>(v, wc, ws);
 }
 
+// lengths 6 = 2 x 3, 9 = 3 x 3 and 18 = 2 x 9 (the column passes)
+template <bool INV, typename C> __device__ __forceinline__ void dft6(C *v) {
+  const double h3 = 0.866025403784438646764;
+  const double wc[3] = {1.0, 0.5, -0.5}, ws[3] = {0.0, h3, h3};
+  dft_split<2, 3, INV>(v, wc, ws);
+}
+template <bool INV, typename C> __device__ __forceinline__ void dft9(C *v) {
+  // cos and sin of 2 pi m / 9, m = 0, 1, 2, 4 (m = 3 does not occur)
+  const double wc[5] = {1.0, 0.766044443118978035202, 0.173648177666930348852, 0.0,
+                        -0.939692620785908384054};
+  const double ws[5] = {0.0, 0.642787609686539326323, 0.984807753012208059367, 0.0,
+                        0.342020143325668733044};
+  dft_split<3, 3, INV>(v, wc, ws);
+}
+template <bool INV, typename C> __device__ __forceinline__ void dft18(C *v) {
+  const double c1 = 0.939692620785908384054, c2 = 0.766044443118978035202;
+  const double s1 = 0.342020143325668733044, s2 = 0.642787609686539326323;
+  const double c4 = 0.173648177666930348852, s4 = 0.984807753012208059367;
+  const double h3 = 0.866025403784438646764;
+  const double wc[9] = {1.0, c1, c2, 0.5, c4, -c4, -0.5, -c2, -c1};
+  const double ws[9] = {0.0, s1, s2, h3, s4, s4, h3, s2, s1};
+  dft_split<2, 9, INV>(v, wc, ws);
+}
+
 template <int R, bool INV, typename C> __device__ __forceinline__ void dftR(C *v) {
   if constexpr (R == 1) (void)v;
   else if constexpr (R == 2) dft2<INV>(v);
   else if constexpr (R == 3) dft3<INV>(v);
   else if constexpr (R == 4) dft4<INV>(v);
+  else if constexpr (R == 6) dft6<INV>(v);
   else if constexpr (R == 8) dft8<INV>(v);
+  else if constexpr (R == 9) dft9<INV>(v);
+  else if constexpr (R == 18) dft18<INV>(v);
   else if constexpr (R == 12) dft12<INV>(v);
   else if constexpr (R == 16) dft16<INV>(v);
   else dft24<INV>(v);

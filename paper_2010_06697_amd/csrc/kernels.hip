@@ -1078,141 +1078,177 @@ void k_div_fwdx(KernelArgs a) {
 }
 
 // ----------------------------------------------------------------------------
-// FFT along x2 of the three spectral components (blockIdx.y = component)
+// Column passes along x2 and x3 of every length (blockIdx.y = component). A
+// length N = P T is transformed in two steps through one exchange in LDS: with
+// n = j + T r and k = k2 + P k1,
+//     X[k2 + P k1] = sum_j w_T^(j k1) [ w_N^(j k2) sum_r x[j + T r] w_P^(r k2) ],
+// item (column, j) loads its P points straight into registers, takes the inner
+// transform and the twiddles and stores to LDS; item (column, k2) reads its T
+// values, takes the outer transform and stores to memory. The x3 pass solves
+// there, in registers, and mirrors the steps: the inverse length-T transform,
+// the conjugate twiddles, the same places of LDS, and the inverse length-P
+// transform on the points the item loaded. Lengths up to 18 are one step
+// without LDS (T = 1). Two passes over LDS and two (x3: three) barriers take
+// the place of four to ten of the stage-by-stage transform, at half its LDS:
+// x2 / x3 / x2 inverse of 144 x 108 x 162 float 29 / 67 / 29 us before.
+//
+// A workgroup takes a power of two of columns of the flattened (x3, m1) or
+// (m2, m1) set, padding columns excluded: the tile width, from the default one
+// up doubled while the items leave half the workgroup idle. Each k2's slab of LDS is padded to an odd
+// number of half bank rows, so that the rows a wave reads fall in different
+// banks.
 // ----------------------------------------------------------------------------
 
-template <typename T, int B, bool INV>
-__global__ __launch_bounds__(kThreads) void k_fft_y(KernelArgs a) {
+// the inner length P of N (0: not a supported length); T = N / P
+__host__ __device__ constexpr int cols_points(int n) {
+  return n <= 18                         ? n
+         : n == 24 || n == 36            ? 6
+         : n == 32 || n == 48 || n == 64 ? 8
+         : n == 54 || n == 72            ? 9
+         : n == 96 || n == 108 || n == 144 ? 12
+         : n == 128 || n == 192 || n == 256 ? 16
+         : n == 162 || n == 216          ? 18
+                                         : 0;
+}
+// LDS slab of one k2 in complex values of csz bytes
+__host__ __device__ inline int cols_slab(int csz, int tcb) {
+  const int u = 256 / csz;
+  return tcb + ((u / 2 - tcb) % u + u) % u;
+}
+
+// COLS 0: x2 forward, 1: x2 inverse, 2: x3 forward, u_hat = b_hat / (|K|^2 V),
+// x3 inverse; 3: the same along x2, for plane strain (every n3 = 1), where x3
+// has nothing to transform: one launch instead of three
+template <typename T, int COLS, int P, int TT>
+__device__ __forceinline__ void cols_tile(const KernelArgs &a, const RveDesc &D, int b,
+                                          typename cplx<T>::type *X) {
   using C = typename cplx<T>::type;
-  constexpr int PMAX = (kMaxN * B) / kThreads;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int r = find_rve(a.blk_y, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  if (!a.state[r].active) return;
-  const int b = blk - a.blk_y[r];
-  const int n2 = D.n2, m1 = D.m1, m1s = D.m1s;
-  const int nty = (m1 + B - 1) / B;
-  const int x3 = b / nty, m0 = (b - x3 * nty) * B;
-  C *base = static_cast<C *>(D.spec) + blockIdx.y * D.S + (long long)x3 * n2 * m1s;
-  C *za = reinterpret_cast<C *>(smem);
-  C *zb = za + n2 * B;
-  const int t = threadIdx.x, nthr = blockDim.x;
-  const int npts = n2 * B;
-  // every load of the tile in flight before the first LDS store
-  C v[PMAX];
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    const int x2 = w / B, bb = w - x2 * B;
-    v[k] = (w < npts && m0 + bb < m1) ? base[x2 * m1s + m0 + bb] : C{(T)0, (T)0};
-  }
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    if (w < npts) za[w] = v[k];
-  }
-  __syncthreads();
+  constexpr bool SOLVE = COLS >= 2, INV = COLS == 1;
+  constexpr int N = P * TT;
+  const int n2 = COLS == 3 ? 1 : D.n2, m1 = D.m1, m1s = D.m1s;
+  const int lcb = COLS == 2 ? D.lcb3 : D.lcb2, CB = 1 << lcb;
+  const int ncol = (COLS == 2 ? n2 : COLS == 3 ? 1 : D.n3) * m1;
+  // rows of a column are es apart; column g of the set starts at outer * os + q
+  const int es = COLS == 2 ? n2 * m1s : m1s;
+  const long long os = COLS == 2 ? m1s : (long long)D.n2 * m1s;
+  C *base = static_cast<C *>(D.spec) + blockIdx.y * D.S;
   const C *tw = static_cast<const C *>(a.tw);
-  C *res = fft_lines<INV>(za, zb, D.p2, tw, B, 1, B, true, t, nthr);
+  const C *twN = tw + (COLS == 2 ? D.p3.tw : D.p2.tw);
+  const int SL = cols_slab(sizeof(C), TT << lcb);
+  const int g0 = b << lcb, t = threadIdx.x;
+  const double iV = SOLVE ? 1.0 / (double)D.V : 0.0;
+  // scale of mode k along the axis for column (outer, q): zero on null modes
+  const auto solve = [&](int outer, int q, int k) {
+    const double K1 = (double)tw[D.p1.tw + q].y;
+    const double K2 = COLS == 3 ? 0.0 : (double)tw[D.p2.tw + outer].y;
+    const double K3 = (double)twN[k].y;
+    const bool null = (q == 0 || 2 * q == D.n1) && (outer == 0 || 2 * outer == n2) &&
+                      (k == 0 || 2 * k == N);
+    return null ? (T)0 : (T)(iV / (K1 * K1 + K2 * K2 + K3 * K3));
+  };
+  for (int it = t; it < TT << lcb; it += kThreads) {
+    const int c = it & (CB - 1), j = it >> lcb, g = g0 + c;
+    const bool ok = g < ncol;
+    const int outer = ok ? g / m1 : 0, q = ok ? g - outer * m1 : 0;
+    C *col = base + outer * os + q;
+    C v[P];
 #pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    if (w < npts) v[k] = res[w];
+    for (int r = 0; r < P; ++r) v[r] = ok ? col[(long long)(j + TT * r) * es] : C{(T)0, (T)0};
+    dftR<P, INV>(v);
+    if (TT == 1) {
+      if (SOLVE) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) {
+          const T s = solve(outer, q, k);
+          v[k] = C{v[k].x * s, v[k].y * s};
+        }
+        dftR<P, true>(v);
+      }
+      if (ok) {
+#pragma unroll
+        for (int k = 0; k < P; ++k) col[(long long)k * es] = v[k];
+      }
+    } else {
+#pragma unroll
+      for (int k2 = 0; k2 < P; ++k2) {
+        if (k2) {
+          const C w = twN[j * k2];  // j k2 < N
+          v[k2] = INV ? cmulc(v[k2], w) : cmul(v[k2], w);
+        }
+        X[k2 * SL + (j << lcb) + c] = v[k2];
+      }
+    }
   }
+  if (TT == 1) return;
+  __syncthreads();
+  for (int it = t; it < P << lcb; it += kThreads) {
+    const int c = it & (CB - 1), k2 = it >> lcb, g = g0 + c;
+    const bool ok = g < ncol;
+    const int outer = ok ? g / m1 : 0, q = ok ? g - outer * m1 : 0;
+    C *x = X + k2 * SL + c;
+    C z[TT];
 #pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    const int x2 = w / B, bb = w - x2 * B;
-    if (w < npts && m0 + bb < m1) base[x2 * m1s + m0 + bb] = v[k];
+    for (int j = 0; j < TT; ++j) z[j] = x[j << lcb];
+    dftR<TT, INV>(z);
+    if (SOLVE) {
+#pragma unroll
+      for (int k1 = 0; k1 < TT; ++k1) {
+        const T s = solve(outer, q, k2 + P * k1);
+        z[k1] = C{z[k1].x * s, z[k1].y * s};
+      }
+      dftR<TT, true>(z);
+#pragma unroll
+      for (int j = 0; j < TT; ++j) x[j << lcb] = j ? cmulc(z[j], twN[j * k2]) : z[0];
+    } else if (ok) {
+      C *col = base + outer * os + q;
+#pragma unroll
+      for (int k1 = 0; k1 < TT; ++k1) col[(long long)(k2 + P * k1) * es] = z[k1];
+    }
+  }
+  if (!SOLVE) return;
+  __syncthreads();
+  for (int it = t; it < TT << lcb; it += kThreads) {
+    const int c = it & (CB - 1), j = it >> lcb, g = g0 + c;
+    if (g >= ncol) continue;
+    const int outer = g / m1, q = g - outer * m1;
+    C *col = base + outer * os + q;
+    C v[P];
+#pragma unroll
+    for (int k2 = 0; k2 < P; ++k2) v[k2] = X[k2 * SL + (j << lcb) + c];
+    dftR<P, true>(v);
+#pragma unroll
+    for (int r = 0; r < P; ++r) col[(long long)(j + TT * r) * es] = v[r];
   }
 }
 
-// ----------------------------------------------------------------------------
-// FFT along x3, Poisson solve in Fourier space, inverse FFT along x3
-// (blockIdx.y = component)
-// ----------------------------------------------------------------------------
-
-// PLANE: every cell has n3 = 1. Along x3 there is nothing to transform, and the
-// pass runs along x2 instead: forward, solve, inverse in one launch where the
-// general sequence takes three (256 x 256 x 1 double: 46 us, of which 26 us for
-// workgroups of 8 points along x3).
-template <typename T, int B, bool PLANE>
-__global__ __launch_bounds__(kThreads) void k_poisson_z(KernelArgs a) {
+// BIG: some line of the launch takes 18 points per thread (18, 162, 216),
+// compiled apart so that the others keep the registers of 16
+template <typename T, int COLS, bool BIG>
+__global__ __launch_bounds__(kThreads) void k_cols(KernelArgs a) {
   using C = typename cplx<T>::type;
-  constexpr int PMAX = (kMaxN * B) / kThreads;
   extern __shared__ __align__(16) unsigned char smem[];
+  C *X = reinterpret_cast<C *>(smem);
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int r = find_rve(a.blk_z, a.n_rve, blk);
+  const int *tab = COLS >= 2 ? a.blk_z : a.blk_y;
+  const int r = find_rve(tab, a.n_rve, blk);
   const RveDesc &D = a.desc[r];
   if (!a.state[r].active) return;
-  const int b = blk - a.blk_z[r];
-  const Plan1D &pl = PLANE ? D.p2 : D.p3;  // the transformed axis
-  const int n1 = D.n1, n2 = PLANE ? 1 : D.n2, n3 = PLANE ? D.n2 : D.n3, m1 = D.m1, m1s = D.m1s;
-  const int plane = n2 * m1s;  // stride along that axis (padding columns included)
-  const int q0 = b * B;
-  const int npts = n3 * B;
-  C *base = static_cast<C *>(D.spec) + blockIdx.y * D.S + q0;
-  const C *tw = static_cast<const C *>(a.tw);
-  C *za = reinterpret_cast<C *>(smem);
-  C *zb = za + n3 * B;
-  const int t = threadIdx.x, nthr = blockDim.x;
-  C v[PMAX];
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    const int x3 = w / B, bb = w - x3 * B;
-    v[k] = (w < npts && q0 + bb < plane) ? base[x3 * plane + bb] : C{(T)0, (T)0};
+  const int b = blk - tab[r];
+#define COLS_CASE(n) \
+  case n: cols_tile<T, COLS, cols_points(n), n / cols_points(n)>(a, D, b, X); break;
+#define COLS_CASE_BIG(n) \
+  case n: \
+    if constexpr (BIG) cols_tile<T, COLS, cols_points(n), n / cols_points(n)>(a, D, b, X); \
+    break;
+  switch (COLS == 2 ? D.n3 : D.n2) {  // uniform over the workgroup
+    COLS_CASE(1) COLS_CASE(4) COLS_CASE(6) COLS_CASE(8) COLS_CASE(12) COLS_CASE(16)
+    COLS_CASE(24) COLS_CASE(32) COLS_CASE(36) COLS_CASE(48) COLS_CASE(54) COLS_CASE(64)
+    COLS_CASE(72) COLS_CASE(96) COLS_CASE(108) COLS_CASE(128) COLS_CASE(144) COLS_CASE(192)
+    COLS_CASE(256)
+    COLS_CASE_BIG(18) COLS_CASE_BIG(162) COLS_CASE_BIG(216)
   }
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    if (w < npts) za[w] = v[k];
-  }
-  __syncthreads();
-  C *res = fft_lines<false>(za, zb, pl, tw, B, 1, B, true, t, nthr);
-  // u_hat = b_hat / (|K|^2 V); zero where every K_j vanishes
-  const double iV = 1.0 / (double)D.V;
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    if (w < npts) {
-      const int m3 = w / B, bb = w - m3 * B;
-      int q = q0 + bb;
-      if (q >= plane) q = 0;
-      const int m2 = q / m1s, mm1 = q - m2 * m1s;
-      const bool pad = mm1 >= m1;  // padding column: stays zero
-      const double K1 = (double)tw[D.p1.tw + (pad ? 0 : mm1)].y;
-      const double K2 = PLANE ? 0.0 : (double)tw[D.p2.tw + m2].y;
-      const double K3 = (double)tw[pl.tw + m3].y;
-      const bool null = pad || ((mm1 == 0 || 2 * mm1 == n1) && (m2 == 0 || 2 * m2 == n2) &&
-                                (m3 == 0 || 2 * m3 == n3));
-      const T s = null ? (T)0 : (T)(iV / (K1 * K1 + K2 * K2 + K3 * K3));
-      const C h = res[w];
-      v[k] = C{h.x * s, h.y * s};
-    }
-  }
-  // res is one of the two buffers and every thread has read what it needs
-  // from it; the scaled values go to the other one
-  C *dst = (res == za) ? zb : za;
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    if (w < npts) dst[w] = v[k];
-  }
-  __syncthreads();
-  res = fft_lines<true>(dst, res, pl, tw, B, 1, B, true, t, nthr);
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    if (w < npts) v[k] = res[w];
-  }
-#pragma unroll
-  for (int k = 0; k < PMAX; ++k) {
-    const int w = t + k * nthr;
-    const int x3 = w / B, bb = w - x3 * B;
-    if (w < npts && q0 + bb < plane) base[x3 * plane + bb] = v[k];
-  }
+#undef COLS_CASE
+#undef COLS_CASE_BIG
 }
 
 // ----------------------------------------------------------------------------
@@ -2102,70 +2138,48 @@ struct Timed {
   }
 };
 
-// the x2 / x3 passes at a runtime tile width (one of four compiled widths)
+template <typename T, int COLS>
+static void launch_cols(const LaunchCfg &L, const KernelArgs &a) {
+  const dim3 blk(kThreads), grid(COLS >= 2 ? L.nblk_z : L.nblk_y, 3);
+  const size_t lds = COLS >= 2 ? L.lds_colz : L.lds_coly;
+  if (COLS >= 2 ? L.big_z : L.big_y)
+    hipLaunchKernelGGL((k_cols<T, COLS, true>), grid, blk, lds, L.stream, a);
+  else
+    hipLaunchKernelGGL((k_cols<T, COLS, false>), grid, blk, lds, L.stream, a);
+}
+
 template <typename T, bool INV>
 static void launch_fft_y(const LaunchCfg &L, const KernelArgs &a) {
   using C = typename cplx<T>::type;
-  constexpr int B = tileB<T>();
   const dim3 blk(kThreads), grid(L.nblk_y, 3);
-  if (L.tile_y == kTileCol16) {
-    if (sizeof(T) == 4 && !L.col256_y) {
-      if (L.lds_coly > reg_lds(false, 16))
-        hipLaunchKernelGGL((k_colreg<INV ? 1 : 0, 24>), grid, blk, L.lds_coly, L.stream, a);
-      else
-        hipLaunchKernelGGL((k_colreg<INV ? 1 : 0, 16>), grid, blk, L.lds_coly, L.stream, a);
-    } else {
-      hipLaunchKernelGGL((k_col16<T, INV ? 1 : 0>), grid, blk, col16_lds<C>(), L.stream, a);
-    }
-    return;
+  if (L.tile_y != kTileCol16) {
+    launch_cols<T, INV ? 1 : 0>(L, a);
+  } else if (sizeof(T) == 4 && !L.col256_y) {
+    if (L.lds_coly > reg_lds(false, 16))
+      hipLaunchKernelGGL((k_colreg<INV ? 1 : 0, 24>), grid, blk, L.lds_coly, L.stream, a);
+    else
+      hipLaunchKernelGGL((k_colreg<INV ? 1 : 0, 16>), grid, blk, L.lds_coly, L.stream, a);
+  } else {
+    hipLaunchKernelGGL((k_col16<T, INV ? 1 : 0>), grid, blk, col16_lds<C>(), L.stream, a);
   }
-  const size_t lds = 2 * (size_t)L.n2max * L.tile_y * sizeof(C);
-  if (L.tile_y == B / 4)
-    hipLaunchKernelGGL((k_fft_y<T, B / 4, INV>), grid, blk, lds, L.stream, a);
-  else if (L.tile_y == B / 2)
-    hipLaunchKernelGGL((k_fft_y<T, B / 2, INV>), grid, blk, lds, L.stream, a);
-  else if (L.tile_y == 2 * B)
-    hipLaunchKernelGGL((k_fft_y<T, 2 * B, INV>), grid, blk, lds, L.stream, a);
-  else
-    hipLaunchKernelGGL((k_fft_y<T, B, INV>), grid, blk, lds, L.stream, a);
-}
-
-template <typename T, bool PLANE>
-static void launch_poisson_tiled(const LaunchCfg &L, const KernelArgs &a) {
-  using C = typename cplx<T>::type;
-  constexpr int B = tileB<T>();
-  const dim3 blk(kThreads), grid(L.nblk_z, 3);
-  const int tz = PLANE ? plane_tile(sizeof(T) == 8, L.n2max, L.tile_z) : L.tile_z;
-  const size_t lds = 2 * (size_t)(PLANE ? L.n2max : L.n3max) * tz * sizeof(C);
-  if (tz == B / 4)
-    hipLaunchKernelGGL((k_poisson_z<T, B / 4, PLANE>), grid, blk, lds, L.stream, a);
-  else if (tz == B / 2)
-    hipLaunchKernelGGL((k_poisson_z<T, B / 2, PLANE>), grid, blk, lds, L.stream, a);
-  else if (tz == 2 * B)
-    hipLaunchKernelGGL((k_poisson_z<T, 2 * B, PLANE>), grid, blk, lds, L.stream, a);
-  else
-    hipLaunchKernelGGL((k_poisson_z<T, B, PLANE>), grid, blk, lds, L.stream, a);
 }
 
 template <typename T>
 static void launch_poisson_z(const LaunchCfg &L, const KernelArgs &a) {
   using C = typename cplx<T>::type;
   const dim3 blk(kThreads), grid(L.nblk_z, 3);
-  if (L.tile_z == kTileCol16) {
-    if (sizeof(T) == 4 && !L.col256_z) {
-      if (L.lds_colz > reg_lds(false, 16))
-        hipLaunchKernelGGL((k_colreg<2, 24>), grid, blk, L.lds_colz, L.stream, a);
-      else
-        hipLaunchKernelGGL((k_colreg<2, 16>), grid, blk, L.lds_colz, L.stream, a);
-    } else {
-      hipLaunchKernelGGL((k_col16<T, 2>), grid, blk, col16_lds<C>(), L.stream, a);
-    }
-    return;
+  if (L.plane) {
+    launch_cols<T, 3>(L, a);
+  } else if (L.tile_z != kTileCol16) {
+    launch_cols<T, 2>(L, a);
+  } else if (sizeof(T) == 4 && !L.col256_z) {
+    if (L.lds_colz > reg_lds(false, 16))
+      hipLaunchKernelGGL((k_colreg<2, 24>), grid, blk, L.lds_colz, L.stream, a);
+    else
+      hipLaunchKernelGGL((k_colreg<2, 16>), grid, blk, L.lds_colz, L.stream, a);
+  } else {
+    hipLaunchKernelGGL((k_col16<T, 2>), grid, blk, col16_lds<C>(), L.stream, a);
   }
-  if (L.plane)
-    launch_poisson_tiled<T, true>(L, a);
-  else
-    launch_poisson_tiled<T, false>(L, a);
 }
 
 // one pass of Step 1 in the kernel variant of the context's materials
@@ -2333,13 +2347,21 @@ size_t reg_lds(bool fp64, int pmax) {
   return fp64 ? col16_lds<double2>() : (size_t)pmax * kColSlab * sizeof(float2);
 }
 
-// columns per workgroup of the plane-strain pass along x2: the x3 tile width,
-// halved until its lines fit 64 KiB of LDS
-int plane_tile(bool fp64, int n2max, int tile_z) {
-  const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);
-  while (tile_z > tile_b(fp64) / 4 && 2 * (size_t)n2max * tile_z * csz > 65536) tile_z /= 2;
-  return tile_z;
+int cols_log2(bool fp64, int n, int B) {
+  const int P = cols_points(n), items = n > P ? std::max(P, n / P) : 1;
+  int lcb = 0;
+  while ((2 << lcb) <= B) ++lcb;
+  // from the default width up, doubled while twice the columns' items still fit
+  // the workgroup, up to the LDS of four workgroups per CU (narrower tiles are
+  // for launches of few columns)
+  while (B >= tile_b(fp64) && (items << (lcb + 1)) <= kThreads && cols_lds(fp64, n, lcb + 1) <= 40960) ++lcb;
+  return lcb;
 }
+size_t cols_lds(bool fp64, int n, int lcb) {
+  const int csz = fp64 ? 16 : 8, P = cols_points(n), TT = n / P;
+  return TT == 1 ? 0 : (size_t)P * cols_slab(csz, TT << lcb) * csz;
+}
+bool cols_big(int n) { return cols_points(n) == 18; }
 
 bool tile_compiled(bool fp64, int B) {
   const int d = tile_b(fp64);

@@ -70,7 +70,8 @@ struct LaunchCfg {
   int nblk_i;
   int tile_y, tile_z;  // columns per workgroup of the x2 and x3 passes,
                        // or kTileCol16 (the register-resident pass)
-  size_t lds_coly, lds_colz;  // LDS bytes of the register-resident passes
+  size_t lds_coly, lds_colz;  // LDS bytes of the column passes
+  bool big_y, big_z;          // some line of a column pass needs 18 points per thread
   bool col256_y, col256_z;     // every length along x2 (x3) is 256: k_col16
   int n2max, n3max;
   bool plane;    // every cell has n3 = 1: the solve runs in one pass along x2
@@ -119,7 +120,12 @@ hipError_t launch_part(const LaunchCfg &L, const KernelArgs &a, const IterParams
 // quarter, half, default, double)
 int tile_b(bool fp64);
 bool tile_compiled(bool fp64, int B);
-int plane_tile(bool fp64, int n2max, int tile_z);
+// the column passes (k_cols): log2 of the columns per workgroup for lines of n
+// points at tile width B, their LDS bytes, and whether n needs the kernel
+// compiled for 18 points per thread
+int cols_log2(bool fp64, int n, int B);
+size_t cols_lds(bool fp64, int n, int lcb);
+bool cols_big(int n);
 int reg_points(bool fp64, int n);
 int reg_columns(bool fp64, int n);
 size_t reg_lds(bool fp64, int pmax);
