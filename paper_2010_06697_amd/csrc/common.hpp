@@ -24,7 +24,8 @@ inline FastDiv make_fastdiv(unsigned d) {
   f.m = d <= 1 ? 0u : (unsigned)(((1ull << 32) + d - 1) / d);
   return f;
 }
-__device__ __forceinline__ int fdiv(int n, FastDiv f) {
+// (F: FastDiv, in any address space)
+template <typename F> __device__ __forceinline__ int fdiv(int n, const F &f) {
   return f.m ? (int)__umulhi((unsigned)n, f.m) : n;
 }
 

@@ -205,9 +205,9 @@ __device__ __forceinline__ void dft_split(C *v, const double *wc, const double *
 // One radix-R stage over `nlines` lines. Element k of line l lives at
 // buf[l*ls + k*es]. lfast: consecutive threads take consecutive lines (for the
 // [k][line] layouts) instead of consecutive butterflies of one line.
-template <int R, bool INV, typename C>
+template <int R, bool INV, typename C, typename FD>
 __device__ __forceinline__ void fft_stage(const C *__restrict__ src, C *__restrict__ dst, int N,
-                                          int Ns, FastDiv fnb, FastDiv fns, int nlines, int ls,
+                                          int Ns, const FD &fnb, const FD &fns, int nlines, int ls,
                                           int es, bool lfast, const C *__restrict__ tw, int tid,
                                           int nthr) {
   const int nb = N / R;
@@ -247,8 +247,9 @@ __device__ __forceinline__ void fft_stage(const C *__restrict__ src, C *__restri
 
 // Transforms every line; a and b are two LDS buffers of the same shape, a
 // holds the input. Returns the buffer holding the result. Ends with a barrier.
-template <bool INV, typename C>
-__device__ C *fft_lines(C *a, C *b, const Plan1D &p, const C *__restrict__ twpool, int nlines,
+// (PL: Plan1D, in any address space)
+template <bool INV, typename C, typename PL>
+__device__ C *fft_lines(C *a, C *b, const PL &p, const C *__restrict__ twpool, int nlines,
                         int ls, int es, bool lfast, int tid, int nthr) {
   const C *tw = twpool + p.tw;
   int Ns = 1;

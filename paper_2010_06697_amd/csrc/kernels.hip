@@ -71,6 +71,14 @@ template <typename T> __device__ __forceinline__ gptr<T> global_view(T *p) {
   return (gptr<T>)p;
 }
 
+// Descriptors and state words a kernel reads and no kernel running with it
+// writes: read through the constant address space they stay scalar loads also
+// after the kernel's own stores, which the compiler must take to alias them.
+template <typename T> using cptr = const __attribute__((address_space(4))) T *;
+template <typename T> __device__ __forceinline__ cptr<T> const_view(const T *p) {
+  return (cptr<T>)p;
+}
+
 // Component c of a field at voxel idx: the component's address is uniform over
 // the wave and stays in scalar registers, the voxel's byte offset is one 32-bit
 // register for all components of an element size (a field's component has less
@@ -141,11 +149,11 @@ __device__ __forceinline__ void chunk_order(int b, int ny, int nz, int &yg, int 
 // D.zseg) and of the mean-stress and null-mode sums (seg = D.zmean): R
 // x1-lines (one x2 group) on seg consecutive planes, x2 group fastest (the
 // workgroups of neighbouring x2 groups run side by side)
-__device__ __forceinline__ void column_tile(const RveDesc &D, int seg, int b, int row, int &x2,
+__device__ __forceinline__ void column_tile(int n2, int rows, int seg, int b, int row, int &x2,
                                             int &z0) {
-  const int ny = (D.n2 + D.rows - 1) / D.rows;
+  const int ny = (n2 + rows - 1) / rows;
   const int zb = b / ny;
-  x2 = (b - zb * ny) * D.rows + row;
+  x2 = (b - zb * ny) * rows + row;
   z0 = zb * seg;
 }
 
@@ -232,7 +240,8 @@ constexpr bool kFullPass = kDefect<T> && LK <= 1 && (MODE == kLocalExact || MODE
 // Newton statistics of a local-step workgroup whose first line is `line`:
 // summed per workgroup and added to one slot of the update's parts (atomics
 // from every wave on one address per cell serialised the kernel's tail)
-__device__ __forceinline__ void newton_stats(const KernelArgs &a, const RveDesc &D, int r, int line,
+template <typename DT>
+__device__ __forceinline__ void newton_stats(const KernelArgs &a, const DT &D, int r, int line,
                                              int n_fail, int n_its) {
   __shared__ int wsum[2 * (kThreads / 64)];
 #pragma unroll
@@ -267,7 +276,7 @@ __device__ __forceinline__ void newton_stats(const KernelArgs &a, const RveDesc 
 template <typename T, int LK, int MODE>
 __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass, int blk) {
   const int r = find_rve(a.blk_x, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
+  const auto &D = *const_view(a.desc + r);
   RveState *st = a.state + r;
   if (!st->active) return;
   const bool inexact =
@@ -580,7 +589,7 @@ template <typename T, int KIND>
 __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterParams &ip, int blk) {
   constexpr bool RETRY = KIND == kRetryI;
   const int r = find_rve(a.blk_v, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
+  const auto &D = *const_view(a.desc + r);
   RveState *st = a.state + r;
   if (!st->active) return;
   const int b = blk - a.blk_v[r], t = threadIdx.x;
@@ -715,8 +724,8 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_explicit(KernelArgs a, IterParams ip) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_v, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   if (!st->implicit) return;
   const int V = (int)D.V, idx = (blk - a.blk_v[r]) * kThreads + threadIdx.x;
   if (idx >= V) return;
@@ -761,8 +770,8 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_lag(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_x, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  if (!a.state[r].active || !D.dir_lag) return;
+  const auto &D = *const_view(a.desc + r);
+  if (!const_view(a.state + r)->active || !D.dir_lag) return;
   const int b = blk - a.blk_x[r];
   const int n1 = D.n1, R = D.rows, nrows = D.n2 * D.n3, V = (int)D.V;
   const int row = threadIdx.x / n1, x1 = threadIdx.x - row * n1;
@@ -783,7 +792,7 @@ __global__ __launch_bounds__(kThreads) void k_orient(KernelArgs a) {
   __shared__ double red[7 * (kThreads / 64)];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_x, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
+  const auto &D = *const_view(a.desc + r);
   const int b = blk - a.blk_x[r];
   const int n1 = D.n1, R = D.rows, nrows = D.n2 * D.n3, V = (int)D.V;
   const int row = threadIdx.x / n1, x1 = threadIdx.x - row * n1;
@@ -842,8 +851,8 @@ __global__ __launch_bounds__(kThreads) void k_fsum(KernelArgs a) {
   __shared__ double red[9 * (kThreads / 64)];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_x, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   if (!st->active || !st->free_mask) return;
   const int b = blk - a.blk_x[r];
   const int n1 = D.n1, R = D.rows, nrows = D.n2 * D.n3;
@@ -957,8 +966,8 @@ void k_div_fwdx(KernelArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_f, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   if (!st->active) return;
   const int b = blk - a.blk_f[r];
   const int n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows_f, m1 = D.m1, m1s = D.m1s;
@@ -1119,8 +1128,8 @@ __host__ __device__ inline int cols_slab(int csz, int tcb) {
 // COLS 0: x2 forward, 1: x2 inverse, 2: x3 forward, u_hat = b_hat / (|K|^2 V),
 // x3 inverse; 3: the same along x2, for plane strain (every n3 = 1), where x3
 // has nothing to transform: one launch instead of three
-template <typename T, int COLS, int P, int TT>
-__device__ __forceinline__ void cols_tile(const KernelArgs &a, const RveDesc &D, int b,
+template <typename T, int COLS, int P, int TT, typename DT>
+__device__ __forceinline__ void cols_tile(const KernelArgs &a, const DT &D, int b,
                                           typename cplx<T>::type *X) {
   using C = typename cplx<T>::type;
   constexpr bool SOLVE = COLS >= 2, INV = COLS == 1;
@@ -1231,8 +1240,8 @@ __global__ __launch_bounds__(kThreads) void k_cols(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int *tab = COLS >= 2 ? a.blk_z : a.blk_y;
   const int r = find_rve(tab, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  if (!a.state[r].active) return;
+  const auto &D = *const_view(a.desc + r);
+  if (!const_view(a.state + r)->active) return;
   const int b = blk - tab[r];
 #define COLS_CASE(n) \
   case n: cols_tile<T, COLS, cols_points(n), n / cols_points(n)>(a, D, b, X); break;
@@ -1301,8 +1310,8 @@ __global__ __launch_bounds__(kThreads) void k_col16(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int *tab = MODE == 2 ? a.blk_z : a.blk_y;
   const int r = find_rve(tab, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  if (!a.state[r].active) return;
+  const auto &D = *const_view(a.desc + r);
+  if (!const_view(a.state + r)->active) return;
   const int b = blk - tab[r];
   const int n2 = D.n2, m1 = D.m1, m1s = D.m1s;
   const int t = threadIdx.x, c = t & 15, j = t >> 4;
@@ -1355,8 +1364,8 @@ __global__ __launch_bounds__(kThreads) void k_inv_x(KernelArgs a) {
   extern __shared__ __align__(16) unsigned char smem[];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_f, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   if (!st->active) return;
   const int b = blk - a.blk_f[r];
   const int n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows_f;
@@ -1456,8 +1465,8 @@ __device__ __forceinline__ void colreg(float2 *v, float2 *X, const float2 *__res
 }
 
 // one workgroup's columns of one cell; MODE as k_col16
-template <int MODE, int TT, int P>
-__device__ __forceinline__ void colreg_tile(const KernelArgs &a, const RveDesc &D, int b,
+template <int MODE, int TT, int P, typename DT>
+__device__ __forceinline__ void colreg_tile(const KernelArgs &a, const DT &D, int b,
                                             float2 *X) {
   constexpr int CW = kThreads / TT, N = TT * P;
   const int t = threadIdx.x, c = t % CW, j = t / CW;
@@ -1510,8 +1519,8 @@ __global__ __launch_bounds__(kThreads) void k_colreg(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int *tab = MODE == 2 ? a.blk_z : a.blk_y;
   const int r = find_rve(tab, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  if (!a.state[r].active) return;
+  const auto &D = *const_view(a.desc + r);
+  if (!const_view(a.state + r)->active) return;
   const int b = blk - tab[r];
   switch (MODE == 2 ? D.n3 : D.n2) {  // uniform over the workgroup
     case 32: colreg_tile<MODE, 2, 16>(a, D, b, X); break;
@@ -1545,8 +1554,8 @@ __global__ __launch_bounds__(kThreads) void k_inv_x256(KernelArgs a) {
   C *X = reinterpret_cast<C *>(smem);
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_i, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   if (!st->active) return;
   const int b = blk - a.blk_i[r];
   const int nrows = D.n2 * D.n3, nl = 3 * nrows, m1s = D.m1s;
@@ -1606,14 +1615,14 @@ __global__ __launch_bounds__(kThreads) void k_null_sums(KernelArgs a) {
   __shared__ double red[kNullSums * (kThreads / 64)];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_m, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   const int b = blk - a.blk_m[r];
   const int V = (int)D.V, n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows;
   const double *u = static_cast<const double *>(D.u[st->cur]);
   const int t = threadIdx.x, row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, D.zmean, b, row, x2, z0);
+  column_tile(D.n2, D.rows, D.zmean, b, row, x2, z0);
   double v[kNullSums];
 #pragma unroll
   for (int k = 0; k < kNullSums; ++k) v[k] = 0.0;
@@ -1647,7 +1656,7 @@ __global__ __launch_bounds__(kThreads) void k_null_final(KernelArgs a) {
     for (int k = 0; k < kNullSums; ++k) v[k] += a.nullpart[(size_t)(p0 + q) * kNullSums + k];
   block_sum<kNullSums>(v, red);
   if (threadIdx.x == 0) {
-    const RveDesc &D = a.desc[r];
+    const auto &D = *const_view(a.desc + r);
     const double iV = 1.0 / (double)D.V;
     const double floor2 = 1e-30 * v[24] * iV;
     int any = 0;
@@ -1665,8 +1674,8 @@ __global__ __launch_bounds__(kThreads) void k_null_final(KernelArgs a) {
 __global__ __launch_bounds__(kThreads) void k_null_sub(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_m, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   const int b = blk - a.blk_m[r];
   const int V = (int)D.V, n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows;
   double *u = static_cast<double *>(D.u[st->cur]);
@@ -1674,7 +1683,7 @@ __global__ __launch_bounds__(kThreads) void k_null_sub(KernelArgs a) {
   if (c[24] == 0.0) return;
   const int t = threadIdx.x, row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, D.zmean, b, row, x2, z0);
+  column_tile(D.n2, D.rows, D.zmean, b, row, x2, z0);
   for (int k = 0; k < D.zmean; ++k) {
     const int x3 = z0 + k;
     if (row >= R || x2 >= n2 || x3 >= n3) continue;
@@ -1695,8 +1704,8 @@ template <typename T>
 __global__ __launch_bounds__(kThreads) void k_compose_u(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_x, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  const RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   if (!st->active || !D.du) return;
   const int b = blk - a.blk_x[r];
   const int n1 = D.n1, R = D.rows, nrows = D.n2 * D.n3, V = (int)D.V;
@@ -1732,22 +1741,16 @@ template <typename T> struct UPair {
 };
 
 template <typename T, bool DU>
-__device__ __forceinline__ void load_pair(const RveDesc &D, const RveState *st, int V, int idx,
-                                          UPair<T> &p) {
-  const auto uo = global_view(static_cast<const double *>(D.u[st->cur]));
-  if (DU) {
-    const auto dug = global_view(static_cast<const T *>(D.du));
+__device__ __forceinline__ void load_pair(gptr<const double> uo, gptr<const double> un,
+                                          gptr<const T> dug, int V, unsigned idx, UPair<T> &p) {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      p.b[i] = dug[i * V + idx];
-      p.a[i] = uo[i * V + idx] + (double)p.b[i];
-    }
-  } else {
-    const auto un = global_view(static_cast<const double *>(D.u[1 - st->cur]));
-#pragma unroll
-    for (int i = 0; i < 3; ++i) {
-      p.a[i] = un[i * V + idx];
-      p.b[i] = (T)uo[i * V + idx];
+  for (int i = 0; i < 3; ++i) {
+    if (DU) {
+      p.b[i] = *at(dug, V, i, idx * (unsigned)sizeof(T));
+      p.a[i] = *at(uo, V, i, idx * 8u) + (double)p.b[i];
+    } else {
+      p.a[i] = *at(un, V, i, idx * 8u);
+      p.b[i] = (T)*at(uo, V, i, idx * 8u);
     }
   }
 }
@@ -1760,8 +1763,7 @@ __device__ __forceinline__ void load_pair(const RveDesc &D, const RveState *st, 
 // out as well, in a kernel of its own because those stores cost the others'
 // float form three spilled registers (its update of 256^3: 686 -> 760 us).
 template <typename T, int KIND>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(kDefect<T> && KIND != 2 ? 3 : 1)))
-void k_update(KernelArgs a) {
+__global__ __launch_bounds__(kThreads) void k_update(KernelArgs a) {
   constexpr int IMP = KIND == 3 ? 0 : KIND;
   constexpr bool AT = KIND == 3;
   constexpr bool DU = kDefect<T> || IMP;  // the fields are u, du (else u_{i+1}, u_i)
@@ -1770,8 +1772,8 @@ void k_update(KernelArgs a) {
   __shared__ double red[IMP ? kZSeg : 1][2][kThreads / 64];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_u, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
-  RveState *st = a.state + r;
+  const auto &D = *const_view(a.desc + r);
+  const auto *st = const_view(a.state + r);
   if (!st->active) return;
   const int b = blk - a.blk_u[r];
   const int V = (int)D.V;
@@ -1782,11 +1784,13 @@ void k_update(KernelArgs a) {
   // out: Lambda or the next A - I
   const auto Lo = IMP ? global_view(static_cast<T *>(IMP == 1 ? D.Ai[1 - st->cur] : D.Lam)) : Lg;
   const auto un = global_view(static_cast<double *>(D.u[1 - st->cur]));
+  const gptr<const double> uo = global_view(static_cast<const double *>(D.u[st->cur]));
+  const gptr<const T> dug = global_view(static_cast<const T *>(D.du));
   const auto Ag = global_view(static_cast<T *>(D.At));
   const int t = threadIdx.x;
   const int row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, D.zseg, b, row, x2, z0);
+  column_tile(n2, R, D.zseg, b, row, x2, z0);
   const int nz = min(D.zseg, n3 - z0);  // uniform over the workgroup
   const int zpart = D.zpart;
   const bool act = row < R && x2 < n2;
@@ -1801,8 +1805,8 @@ void k_update(KernelArgs a) {
     pc.b[i] = (T)0;
   }
   if (act) {
-    load_pair<T, DU>(D, st, V, ((z0 == 0 ? n3 - 1 : z0 - 1) * n2 + x2) * n1 + x1, pm);
-    load_pair<T, DU>(D, st, V, (z0 * n2 + x2) * n1 + x1, pc);
+    load_pair<T, DU>(uo, un, dug, V, ((z0 == 0 ? n3 - 1 : z0 - 1) * n2 + x2) * n1 + x1, pm);
+    load_pair<T, DU>(uo, un, dug, V, (z0 * n2 + x2) * n1 + x1, pc);
   }
   double v[2] = {0.0, 0.0};
   int kp = 0;  // planes summed into v
@@ -1819,18 +1823,18 @@ void k_update(KernelArgs a) {
     __syncthreads();
     if (!IMP && !act) continue;
     if (!IMP || act) {
-      const int idx = (x3 * n2 + x2) * n1 + x1;
+      const unsigned idx = (x3 * n2 + x2) * n1 + x1, off = idx * (unsigned)sizeof(T);
       // every load of the plane before its first store (a store may alias a
       // later load as far as the compiler knows)
-      load_pair<T, DU>(D, st, V, ((x3 + 1 == n3 ? 0 : x3 + 1) * n2 + x2) * n1 + x1, pp);
+      load_pair<T, DU>(uo, un, dug, V, ((x3 + 1 == n3 ? 0 : x3 + 1) * n2 + x2) * n1 + x1, pp);
       UPair<T> q2p, q2m;
-      load_pair<T, DU>(D, st, V, (x3 * n2 + x2p) * n1 + x1, q2p);
-      load_pair<T, DU>(D, st, V, (x3 * n2 + x2m) * n1 + x1, q2m);
+      load_pair<T, DU>(uo, un, dug, V, (x3 * n2 + x2p) * n1 + x1, q2p);
+      load_pair<T, DU>(uo, un, dug, V, (x3 * n2 + x2m) * n1 + x1, q2m);
       T E[9], L[9];
 #pragma unroll
       for (int c = 0; c < 9; ++c) {
-        E[c] = Eg[c * V + idx];
-        L[c] = Lg[c * V + idx];
+        E[c] = *at(Eg, V, c, off);
+        L[c] = *at(Lg, V, c, off);
       }
       float jw = 0.0f;
       if (IMP == 1) {
@@ -1863,13 +1867,13 @@ void k_update(KernelArgs a) {
             // (through Lambda as it is stored, so that a call that reads it back
             // forms the same data at this penalty, bit for bit)
             const T ls = (T)(rho * s);
-            Lo[c * V + idx] = IMP == 1 ? (T)(Dn + st->Ebar[c] + (double)ls * irho) : ls;
+            *at(Lo, V, c, off) = IMP == 1 ? (T)(Dn + st->Ebar[c] + (double)ls * irho) : ls;
           } else {
             e = st->Ebar[c] + Dn - (double)E[c];
             lam[c] = (T)((double)L[c] + rho * e);
             // Step 1's data of the next iteration at this penalty, formed as the
             // local step forms it (same operands, same order of operations)
-            if (AT) Ag[c * V + idx] = (T)(Dn + st->Ebar[c] + (double)lam[c] * irho);
+            if (AT) *at(Ag, V, c, off) = (T)(Dn + st->Ebar[c] + (double)lam[c] * irho);
           }
           v[0] += e * e;
           v[1] += dd * dd;
@@ -1877,14 +1881,14 @@ void k_update(KernelArgs a) {
       }
       if (DU) {
 #pragma unroll
-        for (int i = 0; i < 3; ++i) un[i * V + idx] = pc.a[i];
+        for (int i = 0; i < 3; ++i) *at(un, V, i, idx * 8u) = pc.a[i];
       }
       // and the warm start's det F - 1 for the closed form of that step
-      if (IMP == 1) global_view(D.Wi)[idx] = jw;
-      else if (AT) Ag[9 * V + idx] = warm_code(warm_jm1(E));
+      if (IMP == 1) *at(global_view(D.Wi), V, 0, idx * 4u) = jw;
+      else if (AT) *at(Ag, V, 9, off) = warm_code(warm_jm1(E));
       if (!IMP)
 #pragma unroll
-        for (int c = 0; c < 9; ++c) Lo[c * V + idx] = lam[c];
+        for (int c = 0; c < 9; ++c) *at(Lo, V, c, off) = lam[c];
       pm = pc;
       pc = pp;
     }
@@ -2028,7 +2032,7 @@ __global__ __launch_bounds__(kThreads) void k_mean_stress(KernelArgs a) {
   __shared__ double red[18 * (kThreads / 64)];
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_m, a.n_rve, blk);
-  const RveDesc &D = a.desc[r];
+  const auto &D = *const_view(a.desc + r);
   const int b = blk - a.blk_m[r];
   const int V = (int)D.V;
   const int n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows;
@@ -2037,7 +2041,7 @@ __global__ __launch_bounds__(kThreads) void k_mean_stress(KernelArgs a) {
   const int t = threadIdx.x;
   const int row = t / n1, x1 = t - row * n1;
   int x2, z0;
-  column_tile(D, D.zmean, b, row, x2, z0);
+  column_tile(D.n2, D.rows, D.zmean, b, row, x2, z0);
   double v[18];
 #pragma unroll
   for (int k = 0; k < 18; ++k) v[k] = 0.0;
