@@ -1054,7 +1054,10 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     thr_u = std::max(thr_u, wave_threads(D.rows * D.n1));
     bx[r + 1] = bx[r] + (nrows + D.rows - 1) / D.rows;
     bf[r + 1] = bf[r] + (nrows + D.rows_f - 1) / D.rows_f;
-    bi[r + 1] = bi[r] + (3 * nrows + 31) / 32;
+    const int ncl = (3 * nrows + 1) / 2;  // complex lines of the inverse x1 pass
+    D.lpi = inv_lines(fp64, D.n1, ncl);
+    bi[r + 1] = bi[r] + (ncl + D.lpi - 1) / D.lpi;
+    c->L.lds_i = std::max(c->L.lds_i, inv_lds(fp64, D.n1, D.lpi));
     by[r + 1] = bz[r + 1] = 0;  // (set_tiles below)
     n2max = std::max(n2max, D.n2);
     n3max = std::max(n3max, D.n3);
@@ -1130,12 +1133,6 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   c->L.thr_u = thr_u;
   c->L.nblk_f = bf[n_rve];
   c->L.nblk_i = bi[n_rve];
-  {
-    // the register-resident inverse x1 pass: float cells, every x1 length 256
-    bool all256 = !fp64;
-    for (const RveDesc &D : c->desc_h) all256 = all256 && D.n1 == 256 && D.m1s >= 129;
-    c->L.inv256 = all256;
-  }
   c->xpoints = 0;
   c->L.n2max = n2max;
   c->L.n3max = n3max;

@@ -60,6 +60,7 @@ struct RveDesc {
   int rows_f;               // x1-lines per workgroup of the x1 transforms
   int lcb2, lcb3;           // log2 of the columns per workgroup of the x2 and x3
                             // column passes (k_cols)
+  int lpi;                  // complex lines per workgroup of the inverse x1 pass
   int zseg;                 // planes a workgroup of the update walks
   int zpart;                // planes per residual partial (divides zseg)
   int zmean;                // planes per workgroup of the mean-stress and

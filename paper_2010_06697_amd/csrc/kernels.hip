@@ -1281,10 +1281,8 @@ template <typename C> constexpr int col16_slab() { return sizeof(C) == 8 ? 264 :
 template <typename C> constexpr size_t col16_lds() { return 16 * col16_slab<C>() * sizeof(C); }
 
 // The exchange buffer holds a slab of SL values per k2; within it the value of
-// (line c, point j) sits at c * 16 + j when JFAST (consecutive lanes take
-// consecutive points), else at j * 16 + c (consecutive lanes take
-// consecutive lines).
-template <bool INV, int SL, bool JFAST, typename C>
+// (column c, point j) sits at j * 16 + c.
+template <bool INV, int SL, typename C>
 __device__ __forceinline__ void col256(C *v, C *X, const C *__restrict__ tw, int c, int j) {
   dft16<INV>(v);
 #pragma unroll
@@ -1293,10 +1291,10 @@ __device__ __forceinline__ void col256(C *v, C *X, const C *__restrict__ tw, int
     v[k2] = INV ? cmulc(v[k2], w) : cmul(v[k2], w);
   }
 #pragma unroll
-  for (int k2 = 0; k2 < 16; ++k2) X[k2 * SL + (JFAST ? c * 16 + j : j * 16 + c)] = v[k2];
+  for (int k2 = 0; k2 < 16; ++k2) X[k2 * SL + j * 16 + c] = v[k2];
   __syncthreads();
 #pragma unroll
-  for (int jj = 0; jj < 16; ++jj) v[jj] = X[j * SL + (JFAST ? c * 16 + jj : jj * 16 + c)];
+  for (int jj = 0; jj < 16; ++jj) v[jj] = X[j * SL + jj * 16 + c];
   dft16<INV>(v);
 }
 
@@ -1329,7 +1327,7 @@ __global__ __launch_bounds__(kThreads) void k_col16(KernelArgs a) {
   C v[16];
 #pragma unroll
   for (int k = 0; k < 16; ++k) v[k] = ok ? col[(j + 16 * k) * es] : C{(T)0, (T)0};
-  col256<MODE == 1, col16_slab<C>(), false>(v, X, tw256, c, j);
+  col256<MODE == 1, col16_slab<C>()>(v, X, tw256, c, j);
   if (MODE == 2) {
     // thread (c, j) holds m3 = j + 16 k1
     const double iV = 1.0 / (double)D.V;
@@ -1346,79 +1344,11 @@ __global__ __launch_bounds__(kThreads) void k_col16(KernelArgs a) {
       v[k] = C{v[k].x * s, v[k].y * s};
     }
     __syncthreads();  // every thread has read the exchange buffer
-    col256<true, col16_slab<C>(), false>(v, X, tw256, c, j);
+    col256<true, col16_slab<C>()>(v, X, tw256, c, j);
   }
   if (ok) {
 #pragma unroll
     for (int k = 0; k < 16; ++k) col[(j + 16 * k) * es] = v[k];
-  }
-}
-
-// ----------------------------------------------------------------------------
-// inverse complex-to-real FFT along x1 into u_{i+1}
-// ----------------------------------------------------------------------------
-
-template <typename T>
-__global__ __launch_bounds__(kThreads) void k_inv_x(KernelArgs a) {
-  using C = typename cplx<T>::type;
-  extern __shared__ __align__(16) unsigned char smem[];
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
-  const int r = find_rve(a.blk_f, a.n_rve, blk);
-  const auto &D = *const_view(a.desc + r);
-  const auto *st = const_view(a.state + r);
-  if (!st->active) return;
-  const int b = blk - a.blk_f[r];
-  const int n1 = D.n1, n2 = D.n2, n3 = D.n3, R = D.rows_f;
-  const int nrows = n2 * n3;
-  const int row0 = b * R;
-  const int ncl = (3 * R + 1) / 2;
-  const int V = (int)D.V;
-  const long long S = D.S;
-  const C *spec = static_cast<const C *>(D.spec);
-  C *za = reinterpret_cast<C *>(smem);
-  C *zb = za + ncl * n1;
-  const int t = threadIdx.x, nthr = blockDim.x;
-  const int h = n1 / 2;
-
-  // Z[k] = A[k] + i B[k] over the full length from the half spectra of the
-  // two real lines (A, B Hermitian; DC and Nyquist taken as real)
-  for (int w = t; w < ncl * n1; w += nthr) {
-    const int p = fdiv(w, D.f_n1), k = w - p * n1;
-    const int kk = k <= h ? k : n1 - k;
-    C Av = C{(T)0, (T)0}, Bv = C{(T)0, (T)0};
-    const int la = 2 * p, lb = 2 * p + 1;
-    {
-      const int c = fdiv(la, D.f_rows_f), rw = la - c * R;
-      if (row0 + rw < nrows) Av = spec[c * S + (long long)(row0 + rw) * D.m1s + kk];
-    }
-    if (lb < 3 * R) {
-      const int c = fdiv(lb, D.f_rows_f), rw = lb - c * R;
-      if (row0 + rw < nrows) Bv = spec[c * S + (long long)(row0 + rw) * D.m1s + kk];
-    }
-    if (kk == 0 || kk == h) {
-      Av.y = (T)0;
-      Bv.y = (T)0;
-    }
-    if (k > h) {
-      Av.y = -Av.y;
-      Bv.y = -Bv.y;
-    }
-    za[w] = C{Av.x - Bv.y, Av.y + Bv.x};
-  }
-  __syncthreads();
-  const C *tw = static_cast<const C *>(a.tw);
-  C *res = fft_lines<true>(za, zb, D.p1, tw, ncl, n1, 1, false, t, nthr);
-  // double form: u_{i+1}; float form and implicit iterations: the correction
-  // u_{i+1} - u_i
-  T *un = kDefect<T> || a.implicit ? static_cast<T *>(D.du) : static_cast<T *>(D.u[1 - st->cur]);
-  for (int w = t; w < 3 * R * n1; w += nthr) {
-    const int ell = fdiv(w, D.f_n1), x1 = w - ell * n1;
-    const int c = fdiv(ell, D.f_rows_f), rw = ell - c * R;
-    const int grow = row0 + rw;
-    if (grow < nrows) {
-      const C v = res[(ell >> 1) * n1 + x1];
-      un[c * V + grow * n1 + x1] = (ell & 1) ? v.y : v.x;
-    }
   }
 }
 
@@ -1534,22 +1464,104 @@ __global__ __launch_bounds__(kThreads) void k_colreg(KernelArgs a) {
   }
 }
 
-// Inverse complex-to-real transforms along x1 of length 256 in float,
-// register resident. The cell's 3 n2 n3 real output lines, ordered
-// (component, row), go 32 to a workgroup as 16 complex lines (lines 2p and
-// 2p + 1 as the real and imaginary parts, the same pairing as k_inv_x).
-// Thread (p, j) = (t / 16, t % 16) loads points j + 16 r of complex line p
-// from the two half spectra (completed by Hermitian symmetry; the 16 threads
-// of a line read consecutive entries), runs the length-256 transform of the
-// x2 / x3 passes (col256, one exchange through LDS) and stores x1 = j + 16 k1
-// of both real lines (64 consecutive bytes per line and store).
-// exchange slab stride 257: the lanes of a wave, 16 points of 4 lines, fall
-// in different banks both when they write and when they read the exchange
-constexpr int kInvSlab = 257;
-constexpr size_t kInvLds = 16 * kInvSlab * sizeof(float2);
+// ----------------------------------------------------------------------------
+// Inverse complex-to-real transforms along x1, in the two register steps of
+// the column passes (N = P T, one exchange in LDS). The cell's 3 n2 n3 real
+// output lines, ordered (component, row), are paired as the real and imaginary
+// parts of complex lines; item (line, j) loads its points j + T r from the two
+// half spectra, completed by Hermitian symmetry (consecutive items read
+// consecutive entries), item (line, k2) stores x1 = k2 + P k1 of both real
+// lines. The traffic (the half spectra in, the field out) bounds it at 256^3:
+// 95 us float, 182 us double (4.2 and 4.4 TB/s). Lines staged through LDS and
+// transformed stage by stage there took 140 and 243 us, 144 x 108 x 162 float
+// 30 us (now 19), 64^3 float 8.2 us (now 6.6).
+// ----------------------------------------------------------------------------
 
-__global__ __launch_bounds__(kThreads) void k_inv_x256(KernelArgs a) {
-  using C = float2;
+// the inner length P of N along x1 (contiguous lines: short ones are split too,
+// so that several items share a line's consecutive entries)
+__host__ __device__ constexpr int rows_points(int n) {
+  return n == 12 || n == 16 ? 4 : n == 18 ? 6 : cols_points(n);
+}
+// LDS values of one line: P groups of T padded by one, so that both the items
+// that write (consecutive j) and those that read (consecutive k2) spread over
+// the banks
+__host__ __device__ constexpr int rows_slab(int n) {
+  return n == rows_points(n) ? 0 : rows_points(n) * (n / rows_points(n) + 1);
+}
+
+template <typename T, int P, int TT, typename DT, typename ST>
+__device__ __forceinline__ void inv_rows_tile(const KernelArgs &a, const DT &D, const ST *st, int b,
+                                              typename cplx<T>::type *X) {
+  using C = typename cplx<T>::type;
+  constexpr int N = P * TT, h = N / 2, SL = rows_slab(N);
+  const int nrows = D.n2 * D.n3, nl = 3 * nrows, m1s = D.m1s, lpi = D.lpi;
+  const unsigned S = (unsigned)D.S;
+  const int l0 = b * lpi, t = threadIdx.x;
+  typedef T pair __attribute__((ext_vector_type(2)));
+  const auto spec = (gptr<const char>)global_view(static_cast<const C *>(D.spec));
+  const C *tw = static_cast<const C *>(a.tw) + D.p1.tw;
+  // double form: u_{i+1}; float form and implicit iterations: the correction
+  // u_{i+1} - u_i
+  const auto un = global_view(
+      kDefect<T> || a.implicit ? static_cast<T *>(D.du) : static_cast<T *>(D.u[1 - st->cur]));
+  // (lines ordered (component, row) are the field's own order, as V = nrows N)
+  const auto store = [&](int line, int x, C v) {
+    const unsigned o = (unsigned)(2 * line) * N + x;
+    if (2 * line < nl) un[o] = v.x;
+    if (2 * line + 1 < nl) un[o + N] = v.y;
+  };
+  // byte offset of line l's half spectrum
+  const auto at_line = [&](int l) {
+    const int c = l >= 2 * nrows ? 2 : (l >= nrows ? 1 : 0);
+    return (c * S + (unsigned)(l - c * nrows) * (unsigned)m1s) * (unsigned)sizeof(C);
+  };
+  for (int it = t; it < lpi * TT; it += kThreads) {
+    const int p = it / TT, j = it - p * TT;
+    const int LA = 2 * (l0 + p), LB = LA + 1;
+    const bool okA = LA < nl, okB = LB < nl;
+    const unsigned oA = at_line(LA), oB = at_line(LB);
+    C v[P];
+#pragma unroll
+    for (int r = 0; r < P; ++r) {
+      const int k = j + TT * r, kk = k <= h ? k : N - k;
+      pair Av = 0, Bv = 0;
+      if (okA) Av = *(gptr<const pair>)(spec + (oA + (unsigned)kk * (unsigned)sizeof(C)));
+      if (okB) Bv = *(gptr<const pair>)(spec + (oB + (unsigned)kk * (unsigned)sizeof(C)));
+      if (kk == 0 || kk == h) {  // DC and Nyquist taken as real
+        Av.y = (T)0;
+        Bv.y = (T)0;
+      }
+      if (k > h) {
+        Av.y = -Av.y;
+        Bv.y = -Bv.y;
+      }
+      v[r] = C{Av.x - Bv.y, Av.y + Bv.x};
+    }
+    dftR<P, true>(v);
+#pragma unroll
+    for (int k2 = 0; k2 < P; ++k2) {
+      if (TT == 1)
+        store(l0 + p, k2, v[k2]);
+      else
+        X[p * SL + k2 * (TT + 1) + j] = k2 ? cmulc(v[k2], tw[j * k2]) : v[0];
+    }
+  }
+  if (TT == 1) return;
+  __syncthreads();
+  for (int it = t; it < lpi * P; it += kThreads) {
+    const int p = it / P, k2 = it - p * P;
+    C z[TT];
+#pragma unroll
+    for (int j = 0; j < TT; ++j) z[j] = X[p * SL + k2 * (TT + 1) + j];
+    dftR<TT, true>(z);
+#pragma unroll
+    for (int k1 = 0; k1 < TT; ++k1) store(l0 + p, k2 + P * k1, z[k1]);
+  }
+}
+
+template <typename T>
+__global__ __launch_bounds__(kThreads) void k_inv_x(KernelArgs a) {
+  using C = typename cplx<T>::type;
   extern __shared__ __align__(16) unsigned char smem[];
   C *X = reinterpret_cast<C *>(smem);
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
@@ -1558,42 +1570,15 @@ __global__ __launch_bounds__(kThreads) void k_inv_x256(KernelArgs a) {
   const auto *st = const_view(a.state + r);
   if (!st->active) return;
   const int b = blk - a.blk_i[r];
-  const int nrows = D.n2 * D.n3, nl = 3 * nrows, m1s = D.m1s;
-  const int V = (int)D.V;
-  const long long S = D.S;
-  const int t = threadIdx.x, p = t >> 4, j = t & 15;
-  const int LA = b * 32 + 2 * p, LB = LA + 1;
-  const bool okA = LA < nl, okB = LB < nl;
-  const int cA = LA >= 2 * nrows ? 2 : (LA >= nrows ? 1 : 0), rA = LA - cA * nrows;
-  const int cB = LB >= 2 * nrows ? 2 : (LB >= nrows ? 1 : 0), rB = LB - cB * nrows;
-  const C *spec = static_cast<const C *>(D.spec);
-  const C *sA = spec + cA * S + (long long)rA * m1s;
-  const C *sB = spec + cB * S + (long long)rB * m1s;
-  C v[16];
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int k = j + 16 * q;
-    const int kk = k <= 128 ? k : 256 - k;
-    C Av = okA ? sA[kk] : C{0.0f, 0.0f}, Bv = okB ? sB[kk] : C{0.0f, 0.0f};
-    if (kk == 0 || kk == 128) {
-      Av.y = 0.0f;
-      Bv.y = 0.0f;
-    }
-    if (k > 128) {
-      Av.y = -Av.y;
-      Bv.y = -Bv.y;
-    }
-    v[q] = C{Av.x - Bv.y, Av.y + Bv.x};
+#define ROWS_CASE(n) \
+  case n: inv_rows_tile<T, rows_points(n), n / rows_points(n)>(a, D, st, b, X); break;
+  switch (D.n1) {  // uniform over the workgroup
+    ROWS_CASE(4) ROWS_CASE(6) ROWS_CASE(8) ROWS_CASE(12) ROWS_CASE(16) ROWS_CASE(18)
+    ROWS_CASE(24) ROWS_CASE(32) ROWS_CASE(36) ROWS_CASE(48) ROWS_CASE(54) ROWS_CASE(64)
+    ROWS_CASE(72) ROWS_CASE(96) ROWS_CASE(108) ROWS_CASE(128) ROWS_CASE(144) ROWS_CASE(162)
+    ROWS_CASE(192) ROWS_CASE(216) ROWS_CASE(256)
   }
-  const C *tw = static_cast<const C *>(a.tw) + D.p1.tw;
-  col256<true, kInvSlab, true>(v, X, tw, p, j);
-  float *du = static_cast<float *>(D.du);
-  float *oA = du + cA * V + rA * 256, *oB = du + cB * V + rB * 256;
-#pragma unroll
-  for (int k1 = 0; k1 < 16; ++k1) {
-    if (okA) oA[j + 16 * k1] = v[k1].x;
-    if (okB) oB[j + 16 * k1] = v[k1].y;
-  }
+#undef ROWS_CASE
 }
 
 // The fluctuation's components that D_h does not see: the mean and the
@@ -2278,10 +2263,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
       }
       {
         Timed tm(L, K_INV_X);
-        if (sizeof(T) == 4 && L.inv256)
-          hipLaunchKernelGGL(k_inv_x256, dim3(L.nblk_i), blk, kInvLds, L.stream, a);
-        else
-          hipLaunchKernelGGL((k_inv_x<T>), dim3(L.nblk_f), blk, L.lds_x, L.stream, a);
+        hipLaunchKernelGGL(k_inv_x<T>, dim3(L.nblk_i), blk, L.lds_i, L.stream, a);
       }
       break;
     }
@@ -2365,6 +2347,18 @@ size_t cols_lds(bool fp64, int n, int lcb) {
   const int csz = fp64 ? 16 : 8, P = cols_points(n), TT = n / P;
   return TT == 1 ? 0 : (size_t)P * cols_slab(csz, TT << lcb) * csz;
 }
+// complex lines per workgroup of the inverse x1 pass for `lines` of them: as many
+// as fill its threads within the LDS of four workgroups per CU, halved down to
+// two wavefronts of items while the cell gives fewer than 1024 workgroups
+int inv_lines(bool fp64, int n, int lines) {
+  const int P = rows_points(n), TT = n / P;
+  int l = kThreads / std::max(P, TT);
+  if (TT > 1) l = std::min(l, 40960 / (rows_slab(n) * (fp64 ? 16 : 8)));
+  while (l * TT >= 128 && (lines + l - 1) / l < 1024) l /= 2;
+  return std::max(l, 1);
+}
+size_t inv_lds(bool fp64, int n, int l) { return (size_t)l * rows_slab(n) * (fp64 ? 16 : 8); }
+
 bool cols_big(int n) { return cols_points(n) == 18; }
 
 bool tile_compiled(bool fp64, int B) {

@@ -17,8 +17,8 @@ struct KernelArgs {
   const int *blk_p;  // residual partials (and Newton statistics) of each cell
   const int *blk_m;  // the mean-stress and null-mode sums
   const int *blk_v;  // the implicit local step: kThreads voxels each
-  const int *blk_f;  // the x1-transform kernels (div_fwdx, inv_x)
-  const int *blk_i;  // the register-resident inverse x1 pass (32 real lines each)
+  const int *blk_f;  // the x1-transform kernels (div_fwdx)
+  const int *blk_i;  // the inverse x1 pass
   const Material *mats;
   const void *tw;       // twiddle pool (float2 or double2)
   double4 *partials;    // per part (zpart planes of an x2 group): sum e^2, sum dd^2, and the failed
@@ -64,10 +64,8 @@ struct LaunchCfg {
   hipStream_t stream;
   int nblk_x, nblk_y, nblk_z, nblk_u, nblk_f, nblk_m, nblk_v;
   int thr_u;   // threads per workgroup of the update
-  // float cells all of x1 length 256: the inverse x1 pass runs register
-  // resident (k_inv_x256), nblk_i workgroups
-  bool inv256;
-  int nblk_i;
+  int nblk_i;    // the inverse x1 pass: workgroups and LDS bytes
+  size_t lds_i;
   int tile_y, tile_z;  // columns per workgroup of the x2 and x3 passes,
                        // or kTileCol16 (the register-resident pass)
   size_t lds_coly, lds_colz;  // LDS bytes of the column passes
@@ -126,6 +124,8 @@ bool tile_compiled(bool fp64, int B);
 int cols_log2(bool fp64, int n, int B);
 size_t cols_lds(bool fp64, int n, int lcb);
 bool cols_big(int n);
+int inv_lines(bool fp64, int n, int lines);
+size_t inv_lds(bool fp64, int n, int l);
 int reg_points(bool fp64, int n);
 int reg_columns(bool fp64, int n);
 size_t reg_lds(bool fp64, int pmax);
