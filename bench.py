@@ -43,28 +43,21 @@ def kernel_bytes_per_voxel(s, c):
     """Algorithmic HBM bytes per voxel of each kernel (every operand read or
     written once; s = scalar bytes of F, Lambda and the spectra, c =
     (n1/2+1)/n1 half-spectrum fraction, a complex half-spectrum component
-    costs 2 c s per voxel). u is double in both forms; the float form solves
-    Step 2 for the correction du (float), formed into u by the update. The
-    float form without LCE phases (the fibre cell) also has the update store
-    the next local step's data A - I (9 float) and the det F - 1 of its warm
-    start (1 float), which that step reads at an unchanged penalty (every
-    iteration of a call but its first) in place of u, Lambda and F; and the
-    local step store F - A (9 float), from which Step 2 forms its defect in
-    place of F, Lambda and u."""
-    f32 = s == 4
+    costs 2 c s per voxel). The cell's iterations (neo-Hookean, exact local
+    step) keep F and Lambda implicit but in a call's first and last one: the
+    local step reads its data A - I and the code of its warm start's
+    det F - 1 (one float) and writes Q = F - A; Step 2 solves for the
+    correction du from D_h^T Q; the update forms u_{i+1} and the next A - I
+    from u, du, Q and A. u is double in both forms."""
     return {
-        # float: A - I 9, det F - 1 of the warm start 1, phase in; F 9, F - A 9 out.
-        # double: u 3, F 9, Lambda 9, phase in; F 9 out
-        "local": 28 * s + 1 if f32 else 3 * 8 + 27 * s + 1,
-        # float: F - A 9 in; double: F 9, Lambda 9 in; 3 half spectra out
-        "div_fwdx": (9 * s if f32 else 18 * s) + 6 * c * s,
+        "local": 18 * s + 4 + 1,         # A 9, warm start, phase in; Q 9 out
+        "div_fwdx": 9 * s + 6 * c * s,   # Q 9 in; 3 half spectra out
         "fft_y_fwd": 12 * c * s,         # 3 components in and out
         "poisson_z": 12 * c * s,
         "fft_y_inv": 12 * c * s,
-        "inv_x": 6 * c * s + 3 * s if f32 else 6 * c * s + 3 * 8,  # spectra in; du or u out
-        # u_i 3 (double) and du 3 in, u_{i+1} 3 out (float form) or u_{i+1}, u_i in;
-        # F 9, Lambda 9 in; Lambda 9 out (float form: and A - I 9, det F - 1 1 out)
-        "update": (3 * 8 + 3 * s + 3 * 8 + 10 * s if f32 else 6 * 8) + 27 * s,
+        "inv_x": 6 * c * s + 3 * s,      # spectra in; du out
+        # u_i 3 (double), du 3, Q 9, A 9 in; u_{i+1} 3, A 9, warm start out
+        "update": 6 * 8 + 30 * s + 4,
         "finalize": 0.0,
         "mean_stress": 18 * s + 1,
     }

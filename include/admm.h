@@ -215,12 +215,16 @@ size_t admm_workspace_bytes(const admm_rve *rves, int32_t n_rve, int32_t precisi
  *   hip_stream: hipStream_t to enqueue on (NULL = default stream).
  * The penalty of every cell starts at params->rho0, the iteration count at 0.
  * The fields are used as given (the caller zeroes u, F - I and Lambda for a
- * fresh start). In ADMM_FP32_FP64RED without nu_F or the full LCE model's
- * terms the context also allocates 36 bytes per voxel for F - A as the
- * local step leaves it for Step 2, and without LCE materials 40 more for
- * the local step's data as the multiplier update forms it (reused within
- * one call; every call reads the fields afresh, so the caller may write
- * them between calls). Errors: EINVAL, EUNSUPPORTED, ENOMEM, EHIP, ENOGPU. */
+ * fresh start). Without LCE materials and with exact local steps the context
+ * also allocates 112 bytes per voxel (ADMM_FP32_FP64RED; 244 in ADMM_FP64):
+ * the iterations of a call then pass the local step's data and result and
+ * the correction of u between the steps in place of F and Lambda, which the
+ * call's end writes (every call reads the fields afresh, so the caller may
+ * write them between calls); where the card has no room for it, F and Lambda
+ * pass between the steps as well. Otherwise, in ADMM_FP32_FP64RED without
+ * nu_F or the full LCE model's terms, it allocates 36 bytes per voxel for
+ * F - A as the local step leaves it for Step 2, and without LCE materials 40
+ * more for the local step's data as the multiplier update forms it. Errors: EINVAL, EUNSUPPORTED, ENOMEM, EHIP, ENOGPU. */
 int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve,
               const admm_material *mats, int32_t n_mat, const admm_params *params,
               int32_t precision, void *workspace, size_t workspace_bytes,
@@ -371,11 +375,14 @@ typedef struct {
   int32_t tile_y, tile_z;   /* columns per workgroup of the x2 / x3 passes,
                                or ADMM_TILE_REG16 (below) */
   int32_t n_len;            /* distinct edge lengths of the context's cells */
-  int32_t x_points;         /* points per workgroup of the x1 transforms
-                               (256, 512 or 1024; lines = points / n1) */
+  int32_t x_points;         /* points per workgroup of the forward x1
+                               transforms (256, 512 or 1024; lines =
+                               points / n1) */
   int32_t len[24];          /* those lengths, ascending */
   int32_t radix[24][8];     /* radix sequence of each length (2, 3, 4, 8),
-                               0-terminated */
+                               0-terminated: the stages of the forward x1
+                               transforms (the other passes take fixed
+                               registers-and-LDS splits of each length) */
   double ms_default;        /* Step 2 over all cells, ms per call, before */
   double ms_tuned;          /* and after tuning */
 } admm_tuning;
@@ -392,7 +399,7 @@ typedef struct {
 /* Autotuner (a performance control with no counterpart in the method): times
  * Step 2 over all cells on the context's stream, `reps` calls per candidate
  * (best of three), and keeps the fastest number of points per workgroup of
- * the x1 transforms, then the fastest tile width of the x2 pass, then of
+ * the forward x1 transforms, then the fastest tile width of the x2 pass, then of
  * the x3 pass (a quarter, half, default or double width, LDS <= 64 KiB, or
  * ADMM_TILE_REG16 where every cell's length along that axis is supported), then the
  * fastest radix sequence of each transform length in turn (every order of

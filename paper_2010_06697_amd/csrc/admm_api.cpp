@@ -1064,6 +1064,23 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     lds_x = std::max(lds_x, 2 * ((3 * D.rows_f + 1) / 2) * D.n1);
   }
   c->implicit = !any_lce && !any_ext && !(p.local_ratio > 0.0) && !(p.local_fraction > 0.0);
+  // Implicit iterations (exact local step, no LCE phase): A - I twice, F - A
+  // and one float; the double form also its correction du (the float form's
+  // lies in the workspace). Where the card has no room for them, iterations
+  // are explicit.
+  const size_t si = fp64 ? 8 : 4, per = 27 * si + 4 + (fp64 ? 3 * si : 0);
+  if (c->implicit) {
+    size_t tot = 0;
+    for (const RveDesc &D : c->desc_h) tot += align_up(per * (size_t)D.V, 256);
+    const hipError_t e = hipMalloc(&c->at_d, tot);
+    if (e == hipErrorOutOfMemory) {
+      (void)hipGetLastError();
+      c->at_d = nullptr;
+      c->implicit = false;
+    } else {
+      INIT_TRY(e);
+    }
+  }
   // planes a workgroup of the update walks, over the context's cells (one part
   // each in explicit iterations)
   for (int walk = kZSeg;; walk /= 2) {
@@ -1083,18 +1100,11 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   // update forms it (9 floats) and det F - 1 of the local step's warm start
   // (one float), read by the next local step at the same penalty instead of
   // the stencil gradient of u, Lambda and F
-  // Implicit iterations instead (exact local step, no LCE phase, both forms):
-  // A - I twice, F - A and one float; the double form also its correction du
-  // (the float form's lies in the workspace).
   if (c->implicit) {
-    const size_t s = fp64 ? 8 : 4, per = 27 * s + 4 + (fp64 ? 3 * s : 0);
-    size_t tot = 0;
-    for (const RveDesc &D : c->desc_h) tot += align_up(per * (size_t)D.V, 256);
-    INIT_TRY(hipMalloc(&c->at_d, tot));
     size_t off = 0;
     for (RveDesc &D : c->desc_h) {
       char *base = static_cast<char *>(c->at_d) + off;
-      const size_t f = 9 * (size_t)D.V * s;
+      const size_t f = 9 * (size_t)D.V * si;
       D.Ai[0] = base;
       D.Ai[1] = base + f;
       D.Qi = base + 2 * f;
@@ -1103,16 +1113,16 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
       off += align_up(per * (size_t)D.V, 256);
     }
   } else if (!fp64 && !any_ext) {
-    const size_t per = any_lce ? 9 : 19;
+    const size_t nq = any_lce ? 9 : 19;
     size_t tot = 0;
-    for (const RveDesc &D : c->desc_h) tot += per * (size_t)D.V;
+    for (const RveDesc &D : c->desc_h) tot += nq * (size_t)D.V;
     INIT_TRY(hipMalloc(&c->at_d, tot * sizeof(float)));
     size_t off = 0;
     for (RveDesc &D : c->desc_h) {
       float *base = static_cast<float *>(c->at_d) + off;
       if (!any_lce) D.At = base;
       D.Q = base + (any_lce ? 0 : 10 * (size_t)D.V);
-      off += per * (size_t)D.V;
+      off += nq * (size_t)D.V;
     }
   }
   const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);

@@ -9,19 +9,24 @@
 // leaves three components to transform instead of nine.
 //
 // Per iteration, over every active cell of the batch, in this order:
-//   k_local        Step 1: the local solve per voxel (F; in the float form
-//                  without the full LCE model's terms also F - A for Step 2)
-//   k_div_fwdx     b = D_h^T (F - Lambda/rho) (float form: the defect
-//                  D_h^T (F - A), whose solve is u_{i+1} - u_i) and its
-//                  forward real-to-complex FFT along x1 (two real rows per
-//                  complex transform)
-//   k_fft_y        forward FFT along x2 of the three components
-//   k_poisson_z    forward FFT along x3, u_hat = b_hat / (|K|^2 V) (zero on
-//                  the eight modes where every K_j vanishes), inverse along x3
-//   k_fft_y        inverse FFT along x2
-//   k_inv_x        inverse complex-to-real FFT along x1 into u_{i+1}
-//   k_update       Step 3 (Lambda += rho (grad u_{i+1} - F)) and the
-//                  per-workgroup partial sums of Step 4
+//   k_local_i      Step 1, neo-Hookean cells with exact local steps: Q = F - A
+//                  from the data A the last update left (F and Lambda stay
+//                  implicit until the call's last iteration)
+//   k_local        Step 1 otherwise (F; in the float form without the full
+//                  LCE model's terms also F - A for Step 2)
+//   k_div_fwdx     b = D_h^T (F - Lambda/rho) (implicit iterations and the
+//                  float form: the defect D_h^T (F - A), whose solve is
+//                  u_{i+1} - u_i) and its forward real-to-complex FFT along x1
+//                  (two real rows per complex transform)
+//   k_cols         forward FFT along x2 of the three components; forward along
+//                  x3, u_hat = b_hat / (|K|^2 V) (zero on the eight modes where
+//                  every K_j vanishes), inverse along x3; inverse along x2
+//                  (k_col16 / k_colreg at the register-resident tile width;
+//                  n3 = 1: one pass along x2 with the solve)
+//   k_inv_x        inverse complex-to-real FFT along x1 into u_{i+1}, or the
+//                  correction u_{i+1} - u_i
+//   k_update       Step 3 (Lambda += rho (grad u_{i+1} - F), or the next
+//                  Step 1's data) and the partial sums of Step 4
 //   k_finalize     fixed-order reduction of the partials, r_p, r_d, the
 //                  convergence test and the adaptive penalty (Sec. 2.1)
 // All scalar iteration state (rho, residuals, which u buffer is current,
@@ -575,8 +580,10 @@ void k_local(KernelArgs a, IterParams ip, int pass, int nblk) {
 // needs Q, du and u alone. Every kernel is bound by memory traffic: this drops
 // F from the local step's stores and the update's loads, and Lambda from both
 // of the update's, for one more load of A (bytes per voxel, float / double:
-// local 77 / 153 against 113 / 241, divergence 48 / 96 against 48 / 168,
-// update 172 / 316 against 208 / 264).
+// local 77 / 149 against 113 / 241, divergence 48 / 96 against 48 / 168,
+// update 172 / 292 against 208 / 264; us at 256^3: local 420 / 520 against
+// 520 / 2125 (with the closed form's own gains), divergence 216 / 380 against
+// 250 / 653, update 605 / 1040 against 797 / 1105).
 // Where the penalty changed since A was formed, Step 1 forms it again from u,
 // du and Q.
 // ----------------------------------------------------------------------------
@@ -1103,9 +1110,9 @@ void k_div_fwdx(KernelArgs a) {
 //
 // A workgroup takes a power of two of columns of the flattened (x3, m1) or
 // (m2, m1) set, padding columns excluded: the tile width, from the default one
-// up doubled while the items leave half the workgroup idle. Each k2's slab of LDS is padded to an odd
-// number of half bank rows, so that the rows a wave reads fall in different
-// banks.
+// up doubled while the items leave half the workgroup idle. Each k2's slab of
+// LDS is padded to an odd number of half bank rows, so that the rows a wave
+// reads fall in different banks.
 // ----------------------------------------------------------------------------
 
 // the inner length P of N (0: not a supported length); T = N / P
@@ -1743,8 +1750,8 @@ __device__ __forceinline__ void load_pair(gptr<const double> uo, gptr<const doub
 // IMP 0: F and Lambda in, Lambda out. IMP 1, an implicit iteration: with Q =
 // F_{i+1} - A and gb = D_h du + dEbar, Lambda_{i+1} = rho (gb - Q) is not
 // stored, only the next Step 1's data Ebar + D_h u_{i+1} + (gb - Q). IMP 2,
-// its last one in a call, whose local step also wrote F: Lambda out. KIND 0, 1, 2: IMP; 3: IMP 0
-// with the next local step's data (RveDesc::At: inexact local steps in float)
+// its last one in a call, whose local step also wrote F: Lambda out. KIND 0,
+// 1, 2: IMP; 3: IMP 0 with the next local step's data (RveDesc::At: inexact local steps in float)
 // out as well, in a kernel of its own because those stores cost the others'
 // float form three spilled registers (its update of 256^3: 686 -> 760 us).
 template <typename T, int KIND>
@@ -2138,7 +2145,7 @@ static void launch_cols(const LaunchCfg &L, const KernelArgs &a) {
 }
 
 template <typename T, bool INV>
-static void launch_fft_y(const LaunchCfg &L, const KernelArgs &a) {
+static void launch_cols_y(const LaunchCfg &L, const KernelArgs &a) {
   using C = typename cplx<T>::type;
   const dim3 blk(kThreads), grid(L.nblk_y, 3);
   if (L.tile_y != kTileCol16) {
@@ -2251,7 +2258,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
       }
       {
         Timed tm(L, K_FFT_Y_FWD);
-        if (!L.plane) launch_fft_y<T, false>(L, a);
+        if (!L.plane) launch_cols_y<T, false>(L, a);
       }
       {
         Timed tm(L, K_POISSON_Z);
@@ -2259,7 +2266,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
       }
       {
         Timed tm(L, K_FFT_Y_INV);
-        if (!L.plane) launch_fft_y<T, true>(L, a);
+        if (!L.plane) launch_cols_y<T, true>(L, a);
       }
       {
         Timed tm(L, K_INV_X);

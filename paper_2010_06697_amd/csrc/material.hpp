@@ -464,7 +464,7 @@ __device__ int newton(TG *E, const TG *A, const M &m, TG rho, int maxit, double 
 // P - I are formed without subtracting numbers near one. Returns the Newton
 // count; -2 when the warm start has det F <= 0 (as newton()); -3 where the
 // form does not apply (det A <= 0, no root below the bracket's upper end, no
-// convergence), for the caller to run the nine-component Newton instead.
+// convergence, in double det A too small), for the caller to run the nine-component Newton instead.
 // ---------------------------------------------------------------------------
 // reciprocal and square root in double from the hardware approximations
 // (v_rcp_f64, v_rsq_f64), each refined by Newton's method: two steps for
@@ -595,6 +595,10 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
   }
   const double x1 = 1.0 + e1, x2 = 1.0 + e2, x3 = 1.0 + e3;
   if (!(x3 > 0.0)) return -3;
+  // x_3 carries e_3's rounding, a few 1e-16 of x_1: where its share exceeds a
+  // few 1e-14 of x_3 the double form leaves the voxel to Newton's method (data
+  // with det A near zero; F was off by 1e-10 there)
+  if (sizeof(TG) == 8 && !(x3 * 256.0 > x1)) return -3;
   const double m = mu + rho, r2 = rho * rho;
   const double es[3] = {e1, e2, e3};
   const double x12 = x1 * x2, ix123 = rcp_nr(x12 * x3), ix12 = ix123 * x3;
