@@ -140,15 +140,14 @@ int planes_per_segment(int ny, int n3, int target) {
   return z;
 }
 
-// x1-lines per workgroup of the x1 transforms, for about `points` points per
+// x1-lines per workgroup of the forward x1 transforms, for about `points` points per
 // workgroup (more lines keep more of the workgroup busy in every radix stage;
 // fewer need less LDS); the autotuner picks `points`
 int rows_per_fft_block(int n1, int points) { return std::max(1, points / n1); }
 int default_fft_points(bool fp64) { return fp64 ? 512 : 1024; }
 // The default for one cell: halved while the cell gives fewer than 1024
-// workgroups (64^3 float: divergence 13.9 -> 9.8 us and inverse x1 11.0 -> 7.9
-// us at 256 points; 256^3 double 466 -> 399 and 304 -> 243 us at 512 against
-// 256). By the cell alone: which lines share a complex transform, and so their
+// workgroups (64^3 float: divergence 13.9 -> 9.8 us at 256 points; 256^3 double
+// 466 -> 399 us at 512 against 256). By the cell alone: which lines share a complex transform, and so their
 // rounding, depends on it, and a cell has the same bits in any batch.
 int cell_fft_points(bool fp64, int n1, int n2, int n3) {
   int p = default_fft_points(fp64);
@@ -510,7 +509,7 @@ int set_plan(admm_ctx *c, const Plan1D &p) {
   return ADMM_OK;
 }
 
-// points per workgroup of the x1 transforms (0: each cell's default): lines per
+// points per workgroup of the forward x1 transforms (0: each cell's default): lines per
 // workgroup of every cell, prefix table, grid size and LDS
 int set_xpoints(admm_ctx *c, int points) {
   const int n = c->n_rve;
