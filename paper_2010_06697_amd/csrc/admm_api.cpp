@@ -358,29 +358,6 @@ int download_states(admm_ctx *c) {
   return ADMM_OK;
 }
 
-// after a launch sequence: read the state back and make `u` the current
-// fluctuation buffer of every cell again
-int settle(admm_ctx *c) {
-  int rc = download_states(c);
-  if (rc != ADMM_OK) return rc;
-  bool moved = false;
-  for (int r = 0; r < c->n_rve; ++r) {
-    const RveDesc &D = c->desc_h[r];
-    if (c->state_h[r].cur == 1) {
-      HIP_TRY(hipMemcpyAsync(D.u[0], D.u[1], 3 * (size_t)D.V * sizeof(double), hipMemcpyDeviceToDevice,
-                             c->stream));
-      c->state_h[r].cur = 0;
-      moved = true;
-    }
-  }
-  if (moved) {
-    rc = upload_states(c);
-    if (rc != ADMM_OK) return rc;
-    HIP_TRY(hipStreamSynchronize(c->stream));
-  }
-  return ADMM_OK;
-}
-
 IterParams iter_params(const admm_ctx *c, int test_conv) {
   const admm_params &p = c->params;
   IterParams ip{};
@@ -539,6 +516,36 @@ int set_xpoints(admm_ctx *c, int points) {
 int launch(admm_ctx *c, Part part, const IterParams &ip) {
   hipError_t e = launch_part(c->L, c->A, ip, part, c->fp64);
   return e == hipSuccess ? ADMM_OK : ADMM_EHIP;
+}
+
+// after a launch sequence: read the state back, write F and Lambda of the
+// cells whose last iteration left them implicit (admm_solve's; a cell that
+// failed before the last iteration of an admm_step) and make `u` the current
+// fluctuation buffer of every cell again
+int settle(admm_ctx *c) {
+  int rc = download_states(c);
+  if (rc != ADMM_OK) return rc;
+  bool moved = false;
+  for (const RveState &s : c->state_h) moved = moved || s.implicit;
+  if (moved) {
+    rc = launch(c, Part::Explicit, iter_params(c, 0));
+    if (rc != ADMM_OK) return rc;
+  }
+  for (int r = 0; r < c->n_rve; ++r) {
+    const RveDesc &D = c->desc_h[r];
+    if (c->state_h[r].cur == 1) {
+      HIP_TRY(hipMemcpyAsync(D.u[0], D.u[1], 3 * (size_t)D.V * sizeof(double), hipMemcpyDeviceToDevice,
+                             c->stream));
+      c->state_h[r].cur = 0;
+      moved = true;
+    }
+  }
+  if (moved) {
+    rc = upload_states(c);
+    if (rc != ADMM_OK) return rc;
+    HIP_TRY(hipStreamSynchronize(c->stream));
+  }
+  return ADMM_OK;
 }
 
 // last: the call's final iteration (known for admm_step only): where
@@ -1449,10 +1456,6 @@ int admm_solve(admm_ctx *ctx, int32_t *iters_out, int32_t *status_out) {
     rc = run_iterations(ctx, ip, every, false);
     if (rc != ADMM_OK) return rc;
     rc = download_states(ctx);
-    if (rc != ADMM_OK) return rc;
-  }
-  if (ctx->implicit) {
-    rc = launch(ctx, Part::Explicit, ip);
     if (rc != ADMM_OK) return rc;
   }
   rc = settle(ctx);

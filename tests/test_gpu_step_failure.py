@@ -1,0 +1,64 @@
+"""A cell that fails inside admm_step leaves its last iterate (u, F and Lambda
+of the failing iteration) whatever iteration of the call that is, and the
+other cells of the batch are not affected.
+
+One voxel holds a phase index without a material: the first iteration marks
+the cell, keeps that voxel's F and runs to its end, so five iterations have to
+leave what one iteration leaves. The two take different kernels for the end of
+a call: the bound is rounding, a few units of the type.
+"""
+import numpy as np
+import pytest
+
+from paper_2010_06697_amd import admm, microstructure as M
+from parity_util import gpu_solver, random_state, rel
+
+pytestmark = pytest.mark.gpu
+
+MATS = [M.neohooke(10.0, 40.0), M.neohooke(1.0, 4.0)]
+
+
+def say(*a):
+    print(*a, flush=True)
+
+
+@pytest.fixture(scope="module", autouse=True)
+def need_gpu():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+
+
+def run(precision, shape, n, graph, bad, cells):
+    phases = [M.random_two_phase(shape, 0.4, seed=3 + k) for k in range(cells)]
+    if bad:
+        phases[0][1, 2, 3] = len(MATS)
+    s = gpu_solver(phases, MATS, [M.random_fbar(0.03, seed=5)] * cells, precision, rho0=8.0,
+                   mu_ref=4.0, use_graph=graph, check_every=2)
+    u, F, L = random_state(shape, seed=6)
+    for k in range(cells):
+        s.set_state(k, u=u, F=F, Lambda=L)
+    rc = s.step(n)[0]
+    st = [s.state(k) for k in range(cells)]
+    info = [s.info(k) for k in range(cells)]
+    s.close()
+    return rc, st, info
+
+
+# one workgroup per CU at most (8 x 12 x 16) and beyond (36 x 48 x 48)
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("graph", [0, 1])
+@pytest.mark.parametrize("shape", [(8, 12, 16), (36, 48, 48)])
+def test_failed_cell_keeps_its_last_iterate(precision, graph, shape):
+    say("cell failing in the first of five iterations", precision, graph, shape)
+    rc1, one, _ = run(precision, shape, 1, graph, True, 2)
+    rc5, five, info = run(precision, shape, 5, graph, True, 2)
+    rc, good, _ = run(precision, shape, 5, graph, False, 2)
+    assert (rc1, rc5, rc) == (admm.EDOMAIN, admm.EDOMAIN, admm.OK)
+    assert info[0][0] == 1 and info[0][1] == admm.EDOMAIN and info[1][0] == 5
+    tol = 1e-13 if precision == "fp64" else 1e-6
+    for f in ("u", "F", "Lambda"):
+        err, same = rel(five[0][f], one[0][f]), np.array_equal(five[1][f], good[1][f])
+        say("  ", f, err, same)
+        assert err <= tol, f
+        assert same, f
