@@ -216,7 +216,7 @@ size_t admm_workspace_bytes(const admm_rve *rves, int32_t n_rve, int32_t precisi
  * The penalty of every cell starts at params->rho0, the iteration count at 0.
  * The fields are used as given (the caller zeroes u, F - I and Lambda for a
  * fresh start). Without LCE materials and with exact local steps the context
- * also allocates 112 bytes per voxel (ADMM_FP32_FP64RED; 244 in ADMM_FP64):
+ * also allocates 120 bytes per voxel (ADMM_FP32_FP64RED; 244 in ADMM_FP64):
  * the iterations of a call then pass the local step's data and result and
  * the correction of u between the steps in place of F and Lambda, which the
  * call's end writes (every call reads the fields afresh, so the caller may

@@ -1071,10 +1071,10 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   }
   c->implicit = !any_lce && !any_ext && !(p.local_ratio > 0.0) && !(p.local_fraction > 0.0);
   // Implicit iterations (exact local step, no LCE phase): A - I twice, F - A
-  // and one float; the double form also its correction du (the float form's
-  // lies in the workspace). Where the card has no room for them, iterations
-  // are explicit.
-  const size_t si = fp64 ? 8 : 4, per = 27 * si + 4 + (fp64 ? 3 * si : 0);
+  // and one float; the float form also the bits of F - A beyond its floats,
+  // the double form its correction du (the float form's lies in the
+  // workspace). Where the card has no room for them, iterations are explicit.
+  const size_t si = fp64 ? 8 : 4, per = 27 * si + 4 + (fp64 ? 3 * si : 8);
   if (c->implicit) {
     size_t tot = 0;
     for (const RveDesc &D : c->desc_h) tot += align_up(per * (size_t)D.V, 256);
@@ -1115,6 +1115,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
       D.Ai[1] = base + f;
       D.Qi = base + 2 * f;
       if (fp64) D.du = base + 3 * f;
+      else D.Ri = reinterpret_cast<unsigned long long *>(base + 3 * f);  // (V is a multiple of 4)
       D.Wi = reinterpret_cast<float *>(base + (per - 4) * (size_t)D.V);
       off += align_up(per * (size_t)D.V, 256);
     }

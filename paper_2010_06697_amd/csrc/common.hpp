@@ -97,6 +97,7 @@ struct RveDesc {
   // none.
   void *Ai[2];
   void *Qi;
+  unsigned long long *Ri;   // float form: the bits of F - A beyond Qi's floats (V)
   float *Wi;
 };
 

@@ -580,13 +580,50 @@ void k_local(KernelArgs a, IterParams ip, int pass, int nblk) {
 // needs Q, du and u alone. Every kernel is bound by memory traffic: this drops
 // F from the local step's stores and the update's loads, and Lambda from both
 // of the update's, for one more load of A (bytes per voxel, float / double:
-// local 77 / 149 against 113 / 241, divergence 48 / 96 against 48 / 168,
-// update 172 / 292 against 208 / 264; us at 256^3: local 420 / 520 against
+// local 85 / 149 against 113 / 241, divergence 48 / 96 against 48 / 168,
+// update 180 / 292 against 208 / 264; us at 256^3: local 430 / 520 against
 // 520 / 2125 (with the closed form's own gains), divergence 216 / 380 against
-// 250 / 653, update 605 / 1040 against 797 / 1105).
+// 250 / 653, update 631 / 1040 against 797 / 1105).
 // Where the penalty changed since A was formed, Step 1 forms it again from u,
 // du and Q.
 // ----------------------------------------------------------------------------
+
+// The float form rounds Q to a float for Step 2, as explicit iterations do. In a
+// stiff phase Q is many times F - I, and F = A + Q or Lambda from the rounded Q
+// would have its error (u and Lambda 1.3 times explicit iterations' error on the
+// 64^3 wavy laminate, with it 1.15 and 1.1, F the same; less than theirs at
+// penalties above the moduli). So each component's next 7 bits are kept as well,
+// 8 bytes per voxel (RveDesc::Ri), and Step 3, the warm start and the end of a
+// call take Q to 31 bits: F rounds as it does where it is stored. Local step 400
+// -> 430 us at 256^3, update 605 -> 631.
+// code: (Q - q) / 2^-7 of the last place of q = (float)Q, -64 .. 63, as the
+// difference of the doubles' bit patterns (2^22 a unit, also across a power of
+// two). Both ways are integer instructions on the low words.
+__device__ __forceinline__ unsigned q_code(double Q, float q) {
+  const int d = (int)((unsigned)__double_as_longlong(Q) - (unsigned)__double_as_longlong((double)q));
+  return (unsigned)min((d + (1 << 21)) >> 22, 63) & 127u;
+}
+__device__ __forceinline__ double q_value(float q, unsigned code) {
+  const long long k = (int)(code << 25) >> 25;
+  return __longlong_as_double(__double_as_longlong((double)q) + (k << 22));
+}
+__device__ __forceinline__ unsigned q_bits(unsigned long long w, int c) {
+  return (unsigned)(w >> (7 * c)) & 127u;
+}
+
+// Q as an implicit iteration's local step left it
+template <typename T, typename DT>
+__device__ __forceinline__ void load_q(const DT &D, int V, unsigned idx, double *Q) {
+  const auto Qg = global_view(static_cast<const T *>(D.Qi));
+  if constexpr (kDefect<T>) {
+    const unsigned long long w = *at(global_view(D.Ri), V, 0, idx * 8u);
+#pragma unroll
+    for (int c = 0; c < 9; ++c) Q[c] = q_value(*at(Qg, V, c, idx * 4u), q_bits(w, c));
+  } else {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) Q[c] = (double)*at(Qg, V, c, idx * 8u);
+  }
+}
 
 // KIND: the first pass, which leaves the voxels without a closed form to the
 // second (kRetryI), or solves them itself (kInlineI)
@@ -627,11 +664,12 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
         // formed at another penalty: Lambda from du and Q, which the last
         // iteration left, as its update would have stored it
         const double irho = 1.0 / rho;
-        double gb[9];
+        double gb[9], q[9];
         grad_u(global_view(static_cast<const T *>(D.du)), V, sn, gb);
+        load_q<T>(D, V, idx, q);
 #pragma unroll
         for (int c = 0; c < 9; ++c) {
-          const double s = gb[c] + (st->Ebar[c] - st->Ebar_prev[c]) - (double)*at(Qg, V, c, off);
+          const double s = gb[c] + (st->Ebar[c] - st->Ebar_prev[c]) - q[c];
           At[c] = (T)(g[c] + st->Ebar[c] + (double)(T)(ar * s) * irho);
         }
         jw = *at(global_view(D.Wi), V, 0, (unsigned)idx * 4u);
@@ -655,8 +693,10 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
     const auto warm = [&](T *E) {
       if (st->implicit) {
         const auto Ap = global_view(static_cast<const T *>(D.Ai[1 - cur]));
+        double q[9];
+        load_q<T>(D, V, idx, q);
 #pragma unroll
-        for (int c = 0; c < 9; ++c) E[c] = (T)((double)*at(Qg, V, c, off) + (double)*at(Ap, V, c, off));
+        for (int c = 0; c < 9; ++c) E[c] = (T)(q[c] + (double)*at(Ap, V, c, off));
       } else {
         const auto Eg = global_view(static_cast<const T *>(D.E));
 #pragma unroll
@@ -698,14 +738,22 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
 #pragma unroll
         for (int c = 0; c < 9; ++c) Q[c] = (double)E[c] - (double)At[c];
       }
+      unsigned long long w = 0;
 #pragma unroll
-      for (int c = 0; c < 9; ++c) *at(Qg, V, c, off) = (T)Q[c];
-      if (a.implicit == 2) {
-        // the call's last iteration: F itself, which A + Q as stored would
-        // give to A's rounding only
+      for (int c = 0; c < 9; ++c) {
+        const T q = (T)Q[c];
+        *at(Qg, V, c, off) = q;
+        if constexpr (kDefect<T>) w |= (unsigned long long)q_code(Q[c], q) << (7 * c);
+      }
+      if (kDefect<T>) *at(global_view(D.Ri), V, 0, (unsigned)idx * 8u) = w;
+      if (a.implicit == 2) {  // the call's last iteration: F itself
         const auto Eo = global_view(static_cast<T *>(D.E));
 #pragma unroll
-        for (int c = 0; c < 9; ++c) *at(Eo, V, c, off) = (T)((double)At[c] + Q[c]);
+        for (int c = 0; c < 9; ++c) {
+          double q = Q[c];
+          if constexpr (kDefect<T>) q = q_value((T)q, q_bits(w, c));  // as load_q gives it
+          *at(Eo, V, c, off) = (T)((double)At[c] + q);
+        }
       }
     }
   }
@@ -724,11 +772,9 @@ void k_retry_i(KernelArgs a, IterParams ip, int nblk) {
   retry_scan(a, nblk, [&](int blk) { local_tile_i<T, kRetryI>(a, ip, blk); });
 }
 
-// F and Lambda of the cells whose last iteration left them implicit. In the
-// float form A + Q as stored gives F to A's rounding only (Lambda / rho is
-// several times F - I in a stiff phase), so F is the closed form's point again.
+// F and Lambda of the cells whose last iteration left them implicit
 template <typename T>
-__global__ __launch_bounds__(kThreads) void k_explicit(KernelArgs a, IterParams ip) {
+__global__ __launch_bounds__(kThreads) void k_explicit(KernelArgs a) {
   const int blk = xcd_remap(blockIdx.x, gridDim.x);
   const int r = find_rve(a.blk_v, a.n_rve, blk);
   const auto &D = *const_view(a.desc + r);
@@ -741,34 +787,17 @@ __global__ __launch_bounds__(kThreads) void k_explicit(KernelArgs a, IterParams 
   const int x3 = fdiv(row, D.f_n2), x2 = row - x3 * n2;
   const Stencil sn = stencil(n1, n2, n3, x1, x2, x3);
   const auto Ap = global_view(static_cast<const T *>(D.Ai[1 - st->cur]));
-  const auto Qg = global_view(static_cast<const T *>(D.Qi));
   const auto Eg = global_view(static_cast<T *>(D.E));
   const auto Lg = global_view(static_cast<T *>(D.Lam));
-  double g[9];
-  T Q[9], A[9];
-#pragma unroll
-  for (int c = 0; c < 9; ++c) {
-    Q[c] = Qg[c * V + idx];
-    A[c] = Ap[c * V + idx];
-  }
+  double g[9], Q[9];
+  load_q<T>(D, V, idx, Q);
   grad_u(global_view(static_cast<const T *>(D.du)), V, sn, g);
   const double rho = st->rho_used;
 #pragma unroll
-  for (int c = 0; c < 9; ++c)
-    Lg[c * V + idx] = (T)(rho * (g[c] + (st->Ebar[c] - st->Ebar_prev[c]) - (double)Q[c]));
-  T E[9];
-#pragma unroll
-  for (int c = 0; c < 9; ++c) E[c] = (T)((double)Q[c] + (double)A[c]);
-  const int ph = global_view(D.phase)[idx];
-  if (kDefect<T> && ph < a.n_mat) {
-    const Material m = a.mats[ph];
-    double q[9];
-    if (neo_closed<T>(q, A, warm_code(warm_jm1(E)), m.mu, m.lam, rho, ip.newton_max, 2e-3) >= 0)
-#pragma unroll
-      for (int c = 0; c < 9; ++c) E[c] = (T)((double)A[c] + q[c]);
+  for (int c = 0; c < 9; ++c) {
+    Lg[c * V + idx] = (T)(rho * (g[c] + (st->Ebar[c] - st->Ebar_prev[c]) - Q[c]));
+    Eg[c * V + idx] = (T)((double)Ap[c * V + idx] + Q[c]);
   }
-#pragma unroll
-  for (int c = 0; c < 9; ++c) Eg[c * V + idx] = E[c];
 }
 
 // Frank term: the directors of the previous iteration, copied before Step 1
@@ -1828,11 +1857,17 @@ __global__ __launch_bounds__(kThreads) void k_update(KernelArgs a) {
         E[c] = *at(Eg, V, c, off);
         L[c] = *at(Lg, V, c, off);
       }
+      unsigned long long qw = 0;
+      if (IMP && kDefect<T>) qw = *at(global_view(D.Ri), V, 0, idx * 8u);
+      const auto q_at = [&](int c) {
+        if constexpr (kDefect<T>) return q_value(E[c], q_bits(qw, c));
+        else return (double)E[c];
+      };
       float jw = 0.0f;
       if (IMP == 1) {
         T F[9];
 #pragma unroll
-        for (int c = 0; c < 9; ++c) F[c] = (T)((double)E[c] + (double)L[c]);
+        for (int c = 0; c < 9; ++c) F[c] = (T)(q_at(c) + (double)L[c]);
         jw = warm_code(warm_jm1(F));
       }
       // component c = 3 i + j: Dn = grad u_{i+1}, Dd its change over the
@@ -1853,8 +1888,8 @@ __global__ __launch_bounds__(kThreads) void k_update(KernelArgs a) {
           const double dd = Dd + (st->Ebar[c] - st->Ebar_prev[c]);
           double e;
           if (IMP) {
-            const double q = (double)E[c], s = dd - q;  // s: Lambda / rho
-            const double f = IMP == 1 ? q + (double)L[c] : (double)L[c];
+            const double q = q_at(c), s = dd - q;  // s: Lambda / rho
+            const double f = IMP == 1 ? (double)(T)(q + (double)L[c]) : (double)L[c];
             e = st->Ebar[c] + Dn - f;
             // (through Lambda as it is stored, so that a call that reads it back
             // forms the same data at this penalty, bit for bit)
@@ -2286,7 +2321,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
       break;
     }
     case Part::Explicit: {
-      hipLaunchKernelGGL((k_explicit<T>), dim3(L.nblk_v), blk, 0, L.stream, a, ip);
+      hipLaunchKernelGGL((k_explicit<T>), dim3(L.nblk_v), blk, 0, L.stream, a);
       break;
     }
     case Part::StripNull: {
