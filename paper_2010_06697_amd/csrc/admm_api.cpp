@@ -486,6 +486,94 @@ int set_plan(admm_ctx *c, const Plan1D &p) {
   return ADMM_OK;
 }
 
+// the sums of the null-mode removal (cells whose Step 2 solves for corrections)
+hipError_t alloc_null(admm_ctx *c) {
+  hipError_t e = hipSuccess;
+  if (!c->nullpart_d) e = hipMalloc(&c->nullpart_d, sizeof(double) * 25 * (size_t)c->L.nblk_m);
+  if (e == hipSuccess && !c->nullc_d)
+    e = hipMalloc(&c->nullc_d, sizeof(double) * 25 * (size_t)c->n_rve);
+  c->A.nullpart = c->nullpart_d;
+  c->A.nullc = c->nullc_d;
+  return e;
+}
+
+// The fields that pass between the steps besides the caller's, and the planes
+// a workgroup of the update walks; between calls only. ENOMEM where the card
+// has no room for them (nothing is kept then).
+//   implicit iterations: A - I twice, F - A and one float; the float form also
+//     the bits of F - A beyond its floats, the double form its correction du
+//     (the float form's lies in the workspace);
+//   explicit ones, in the float form without the full LCE model's terms or
+//     dissipation of F: F - A as the local step leaves it (9 floats per voxel),
+//     read by Step 2 instead of F, Lambda and u; without LCE phases also Step
+//     1's data as the update forms it (9 floats) and det F - 1 of the local
+//     step's warm start (one float), read by the next local step at the same
+//     penalty instead of the stencil gradient of u, Lambda and F.
+int set_iterations(admm_ctx *c, bool implicit) {
+  HIP_TRY(hipStreamSynchronize(c->stream));
+  drop_graphs(c);
+  if (c->at_d) (void)hipFree(c->at_d);
+  c->at_d = nullptr;
+  c->implicit = false;
+  c->L.any_at = false;
+  for (RveDesc &D : c->desc_h) {
+    D.Ai[0] = D.Ai[1] = D.Qi = D.At = D.Q = nullptr;
+    D.Ri = nullptr;
+    D.Wi = nullptr;
+    if (c->fp64) D.du = nullptr;
+  }
+  const bool at = !implicit && !c->fp64 && c->L.lce_kind == 0;  // Step 1's data
+  const size_t si = c->fp64 ? 8 : 4;
+  const size_t per = implicit ? 27 * si + 4 + (c->fp64 ? 3 * si : 8)
+                     : at     ? 76
+                              : (!c->fp64 && c->L.lce_kind == 1 ? 36 : 0);
+  size_t tot = 0;
+  for (const RveDesc &D : c->desc_h) tot += align_up(per * (size_t)D.V, 256);
+  if (tot) {
+    hipError_t e = hipMalloc(&c->at_d, tot);
+    if (e == hipSuccess && implicit) e = alloc_null(c);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      if (c->at_d) (void)hipFree(c->at_d);
+      c->at_d = nullptr;
+      return e == hipErrorOutOfMemory ? ADMM_ENOMEM : ADMM_EHIP;
+    }
+  }
+  c->implicit = implicit;
+  c->L.any_at = at;
+  char *base = static_cast<char *>(c->at_d);
+  for (RveDesc &D : c->desc_h) {
+    const size_t V = (size_t)D.V, f = 9 * V * si;
+    if (implicit) {
+      D.Ai[0] = base;
+      D.Ai[1] = base + f;
+      D.Qi = base + 2 * f;
+      if (c->fp64) D.du = base + 3 * f;
+      else D.Ri = reinterpret_cast<unsigned long long *>(base + 3 * f);  // (V is a multiple of 4)
+      D.Wi = reinterpret_cast<float *>(base + (per - 4) * V);
+    } else if (per) {
+      if (at) D.At = base;
+      D.Q = base + (at ? 40 * V : 0);
+    }
+    if (base) base += align_up(per * V, 256);
+  }
+  // planes a workgroup of the update walks, over the context's cells (one part
+  // each in explicit iterations)
+  int *bu = c->blk_h.data() + 3 * (c->n_rve + 1);
+  for (int walk = kZSeg;; walk /= 2) {
+    for (int r = 0; r < c->n_rve; ++r) {
+      RveDesc &D = c->desc_h[r];
+      D.zseg = std::max(walk, D.zpart);
+      bu[r + 1] = bu[r] + ((D.n2 + D.rows - 1) / D.rows) * ((D.n3 + D.zseg - 1) / D.zseg);
+    }
+    if (walk == 1 || (implicit && bu[c->n_rve] >= kWalkTarget)) break;
+  }
+  c->L.nblk_u = bu[c->n_rve];
+  HIP_TRY(hipMemcpy(c->desc_d, c->desc_h.data(), sizeof(RveDesc) * c->n_rve, hipMemcpyHostToDevice));
+  HIP_TRY(hipMemcpy(c->blk_d, c->blk_h.data(), sizeof(int) * c->blk_h.size(), hipMemcpyHostToDevice));
+  return ADMM_OK;
+}
+
 // points per workgroup of the forward x1 transforms (0: each cell's default): lines per
 // workgroup of every cell, prefix table, grid size and LDS
 int set_xpoints(admm_ctx *c, int points) {
@@ -1069,82 +1157,20 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     n3max = std::max(n3max, D.n3);
     lds_x = std::max(lds_x, 2 * ((3 * D.rows_f + 1) / 2) * D.n1);
   }
-  c->implicit = !any_lce && !any_ext && !(p.local_ratio > 0.0) && !(p.local_fraction > 0.0);
-  // Implicit iterations (exact local step, no LCE phase): A - I twice, F - A
-  // and one float; the float form also the bits of F - A beyond its floats,
-  // the double form its correction du (the float form's lies in the
-  // workspace). Where the card has no room for them, iterations are explicit.
-  const size_t si = fp64 ? 8 : 4, per = 27 * si + 4 + (fp64 ? 3 * si : 8);
-  if (c->implicit) {
-    size_t tot = 0;
-    for (const RveDesc &D : c->desc_h) tot += align_up(per * (size_t)D.V, 256);
-    const hipError_t e = hipMalloc(&c->at_d, tot);
-    if (e == hipErrorOutOfMemory) {
-      (void)hipGetLastError();
-      c->at_d = nullptr;
-      c->implicit = false;
-    } else {
-      INIT_TRY(e);
-    }
-  }
-  // planes a workgroup of the update walks, over the context's cells (one part
-  // each in explicit iterations)
-  for (int walk = kZSeg;; walk /= 2) {
-    for (int r = 0; r < n_rve; ++r) {
-      RveDesc &D = c->desc_h[r];
-      D.zseg = std::max(walk, D.zpart);
-      bu[r + 1] = bu[r] + ((D.n2 + D.rows - 1) / D.rows) * ((D.n3 + D.zseg - 1) / D.zseg);
-    }
-    if (walk == 1 || (c->implicit && bu[n_rve] >= kWalkTarget)) break;
-  }
   // the spectra's padding columns stay zero: no kernel writes them but the
   // x3 pass, which maps zero to zero there
   INIT_TRY(hipMemset(c->workspace, 0, spec_off));
-  // float form without the full LCE model's terms or dissipation of F:
-  // F - A as the local step leaves it (9 floats per voxel), read by Step 2
-  // instead of F, Lambda and u; without LCE phases also Step 1's data as the
-  // update forms it (9 floats) and det F - 1 of the local step's warm start
-  // (one float), read by the next local step at the same penalty instead of
-  // the stencil gradient of u, Lambda and F
-  if (c->implicit) {
-    size_t off = 0;
-    for (RveDesc &D : c->desc_h) {
-      char *base = static_cast<char *>(c->at_d) + off;
-      const size_t f = 9 * (size_t)D.V * si;
-      D.Ai[0] = base;
-      D.Ai[1] = base + f;
-      D.Qi = base + 2 * f;
-      if (fp64) D.du = base + 3 * f;
-      else D.Ri = reinterpret_cast<unsigned long long *>(base + 3 * f);  // (V is a multiple of 4)
-      D.Wi = reinterpret_cast<float *>(base + (per - 4) * (size_t)D.V);
-      off += align_up(per * (size_t)D.V, 256);
-    }
-  } else if (!fp64 && !any_ext) {
-    const size_t nq = any_lce ? 9 : 19;
-    size_t tot = 0;
-    for (const RveDesc &D : c->desc_h) tot += nq * (size_t)D.V;
-    INIT_TRY(hipMalloc(&c->at_d, tot * sizeof(float)));
-    size_t off = 0;
-    for (RveDesc &D : c->desc_h) {
-      float *base = static_cast<float *>(c->at_d) + off;
-      if (!any_lce) D.At = base;
-      D.Q = base + (any_lce ? 0 : 10 * (size_t)D.V);
-      off += nq * (size_t)D.V;
-    }
-  }
   const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);
   c->L.timer = nullptr;
   c->L.any_lce = any_lce;
   c->L.lce_kind = any_ext ? 2 : (any_lce ? 1 : 0);
   c->L.any_frank = any_frank;
-  c->L.any_at = c->desc_h[0].At != nullptr;
   c->L.any_free = false;
   c->L.stream = c->stream;
   c->L.nblk_x = bx[n_rve];
   c->L.tile_y = B;
   c->L.tile_z = Bz;
   c->L.plane = plane;
-  c->L.nblk_u = bu[n_rve];
   c->L.nblk_m = bm[n_rve];
   c->L.nblk_v = bv[n_rve];
   c->L.thr_u = thr_u;
@@ -1221,9 +1247,9 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   INIT_TRY(hipMemset(c->newton_part_d, 0, sizeof(int2) * (size_t)bp[n_rve]));
   INIT_TRY(hipMalloc(&c->retry_d, sizeof(unsigned) * (kThreads / 32) * (size_t)c->L.nblk_x));
   INIT_TRY(hipMemset(c->retry_d, 0, sizeof(unsigned) * (kThreads / 32) * (size_t)c->L.nblk_x));
-  if (!fp64 || c->implicit) {  // cells whose Step 2 solves for corrections
-    INIT_TRY(hipMalloc(&c->nullpart_d, sizeof(double) * 25 * (size_t)c->L.nblk_m));
-    INIT_TRY(hipMalloc(&c->nullc_d, sizeof(double) * 25 * (size_t)n_rve));
+  if (!fp64 && alloc_null(c) != hipSuccess) {
+    free_ctx(c);
+    return ADMM_EHIP;
   }
 
   c->state_h.assign(n_rve, RveState{});
@@ -1263,13 +1289,18 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   A.hist = c->hist_d;
   A.newton_part = c->newton_part_d;
   A.retry_mask = c->retry_d;
-  A.nullpart = c->nullpart_d;
-  A.nullc = c->nullc_d;
   A.lpart = c->lpart_d;
   A.fpart = c->fpart_d;
   A.n_rve = n_rve;
   A.n_mat = n_mat;
-  if (set_tiles(c, c->L.tile_y, c->L.tile_z) != ADMM_OK || snapshot_step(c) != ADMM_OK || hipStreamSynchronize(c->stream) != hipSuccess) {
+  // exact local step, no LCE phase: implicit iterations, whose fields come last
+  // and only where there is room for them beside all the rest
+  const bool want = !any_lce && !any_ext && !(p.local_ratio > 0.0) && !(p.local_fraction > 0.0);
+  int rc = want ? set_iterations(c, true) : ADMM_ENOMEM;
+  if (rc == ADMM_ENOMEM) rc = set_iterations(c, false);
+  if (rc == ADMM_OK) rc = set_tiles(c, c->L.tile_y, c->L.tile_z);
+  if (rc == ADMM_OK) rc = snapshot_step(c);
+  if (rc != ADMM_OK || hipStreamSynchronize(c->stream) != hipSuccess) {
     free_ctx(c);
     return ADMM_EHIP;
   }
