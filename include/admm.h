@@ -269,7 +269,9 @@ int admm_get_fbar(admm_ctx *ctx, int32_t rve, double Fbar_out[9]);
  *      rho sigma of the last Step 2' (equals beta at the fixed point);
  *   iters_out, status_out (may be NULL): iterations, ADMM_OK or
  *      ADMM_NOT_CONVERGED.
- * Allocates its work buffers (about 960 bytes per voxel) for the call.
+ * Allocates its work buffers (about 960 bytes per voxel) for the call; where
+ * the card has no room for them beside the fields that admm_init adds for the
+ * iterations, those are given back for good (see admm_init).
  * Errors: EINVAL, EUNSUPPORTED (float context, full LCE model terms),
  * EDOMAIN (L + rho I not positive definite), ENOMEM, EHIP. */
 int admm_bloch(admm_ctx *ctx, int32_t rve, const double omega[3], double rho, double tol,

@@ -1382,9 +1382,15 @@ static int bloch_call(admm_ctx *ctx, int32_t rve, const double omega[3], double 
   // call, and F, the director hold the last iterate
   double beta = 0.0, sr = 0.0;
   int it = 0, status = 1;
-  const int rc = bloch_solve(ctx->stream, ctx->desc_h[rve], ctx->mats_d, ctx->n_mat, ctx->tw_d,
-                             omega, rho, tol, max_iter, static_cast<double *>(p), work, &beta,
-                             &sr, &it, &status);
+  const auto solve = [&]() {
+    return bloch_solve(ctx->stream, ctx->desc_h[rve], ctx->mats_d, ctx->n_mat, ctx->tw_d, omega,
+                       rho, tol, max_iter, static_cast<double *>(p), work, &beta, &sr, &it,
+                       &status);
+  };
+  int rc = solve();
+  // no room for the work buffers: the implicit iterations' fields go (between
+  // calls they hold nothing), and the context's iterations are explicit from here
+  if (rc == -4 && ctx->implicit && set_iterations(ctx, false) == ADMM_OK) rc = solve();
   if (rc == -3) return ADMM_EDOMAIN;
   if (rc == -2) return ADMM_EINVAL;
   if (rc != 0) return ADMM_EHIP;

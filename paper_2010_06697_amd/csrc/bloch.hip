@@ -652,7 +652,13 @@ int bloch_solve(hipStream_t st, const RveDesc &D, const Material *mats_d, int n_
   a.k2min = k2min;
   // work buffers
   void *buf = work;
-  if (!buf && hipMalloc(&buf, bloch_work_bytes(D)) != hipSuccess) return -1;
+  if (!buf) {
+    const hipError_t e = hipMalloc(&buf, bloch_work_bytes(D));
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      return e == hipErrorOutOfMemory ? -4 : -1;
+    }
+  }
   char *q = static_cast<char *>(buf);
   a.Lf = reinterpret_cast<double *>(q);
   q += V * 54 * 8;

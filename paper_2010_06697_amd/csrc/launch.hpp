@@ -90,7 +90,7 @@ enum class Part { Local, Project, Update, MeanStress, ComposeU, StripNull, Expli
 // Bloch-wave stability modulus of one cell (double precision; bloch.hip).
 // p: 3V complex (interleaved) start in, unit mode out. Returns 0, -1 (HIP
 // error), -2 (a zero start or right-hand side), -3 (L + rho I not positive
-// definite); status 0 converged, 1 iteration cap.
+// definite), -4 (no room for the work buffers, nothing run); status 0 converged, 1 iteration cap.
 // work: device buffer of bloch_work_bytes(D) bytes, or null to allocate one
 // for the call.
 int bloch_solve(hipStream_t st, const RveDesc &D, const Material *mats_d, int n_mat,

@@ -29,6 +29,7 @@ int hipMalloc(void **p, size_t n) {
   for (int k = 0; k < MAX_BLOCKS; ++k)
     if (!blocks[k].p) {
       if (posix_memalign(p, 256, n ? n : 1)) return last_error = OUT_OF_MEMORY;
+      memset(*p, 0, n);
       blocks[k].p = *p;
       blocks[k].n = n;
       used += n;
