@@ -153,7 +153,10 @@ typedef struct {
                            first use, kept by the context); 0: launch every
                            kernel. Profiling (admm_profile_enable) launches
                            every kernel. (1) */
-  int32_t reserved;
+  int32_t explicit_fields; /* not 0: F and Lambda pass between the steps of every
+                           iteration, as on a card without room for the fields
+                           that admm_init adds otherwise: the same iterates up
+                           to rounding, less memory, more traffic. (0) */
   /* Inexact local step (Sec. 2.1, local residual r_l; Sec. 4, the two
    * strategies compared there). Step 1 runs in passes of at most local_chunk
    * Newton iterations per voxel, each pass continuing from the previous
@@ -220,11 +223,13 @@ size_t admm_workspace_bytes(const admm_rve *rves, int32_t n_rve, int32_t precisi
  * the iterations of a call then pass the local step's data and result and
  * the correction of u between the steps in place of F and Lambda, which the
  * call's end writes (every call reads the fields afresh, so the caller may
- * write them between calls); where the card has no room for it, F and Lambda
- * pass between the steps as well. Otherwise, in ADMM_FP32_FP64RED without
- * nu_F or the full LCE model's terms, it allocates 36 bytes per voxel for
- * F - A as the local step leaves it for Step 2, and without LCE materials 40
- * more for the local step's data as the multiplier update forms it. Errors: EINVAL, EUNSUPPORTED, ENOMEM, EHIP, ENOGPU. */
+ * write them between calls). Where the card has no room for it, or
+ * params->explicit_fields is set, F and Lambda pass between the steps. Then,
+ * and with LCE materials or inexact local steps, ADMM_FP32_FP64RED without
+ * nu_F or the full LCE model's terms takes 36 bytes per voxel for F - A as the
+ * local step leaves it for Step 2, and without LCE materials 40 more for the
+ * local step's data as the multiplier update forms it. Errors: EINVAL,
+ * EUNSUPPORTED, ENOMEM, EHIP, ENOGPU. */
 int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve,
               const admm_material *mats, int32_t n_mat, const admm_params *params,
               int32_t precision, void *workspace, size_t workspace_bytes,

@@ -71,7 +71,7 @@ class Params(ctypes.Structure):
                 ("newton_gtol", ctypes.c_double), ("newton_step_tol", ctypes.c_double),
                 ("adapt_rho", ctypes.c_int32), ("max_iter", ctypes.c_int32),
                 ("check_every", ctypes.c_int32), ("newton_max", ctypes.c_int32),
-                ("use_graph", ctypes.c_int32), ("reserved", ctypes.c_int32),
+                ("use_graph", ctypes.c_int32), ("explicit_fields", ctypes.c_int32),
                 ("local_ratio", ctypes.c_double), ("local_chunk", ctypes.c_int32),
                 ("local_passes", ctypes.c_int32), ("local_fraction", ctypes.c_double),
                 ("dt", ctypes.c_double), ("div_growth", ctypes.c_double),

@@ -1295,7 +1295,8 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   A.n_mat = n_mat;
   // exact local step, no LCE phase: implicit iterations, whose fields come last
   // and only where there is room for them beside all the rest
-  const bool want = !any_lce && !any_ext && !(p.local_ratio > 0.0) && !(p.local_fraction > 0.0);
+  const bool want = !any_lce && !any_ext && !(p.local_ratio > 0.0) && !(p.local_fraction > 0.0) &&
+                    !p.explicit_fields;
   int rc = want ? set_iterations(c, true) : ADMM_ENOMEM;
   if (rc == ADMM_ENOMEM) rc = set_iterations(c, false);
   if (rc == ADMM_OK) rc = set_tiles(c, c->L.tile_y, c->L.tile_z);
