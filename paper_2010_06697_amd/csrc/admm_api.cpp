@@ -404,8 +404,10 @@ bool col16_ok(const admm_ctx *c, int axis) {
   return true;
 }
 
-// a tile width of the x2 (axis 2) or x3 (axis 3) pass: a compiled width
-// within 64 KiB of LDS, or kTileCol16 where every cell's length is 256
+// a tile width of the x2 (axis 2) or x3 (axis 3) pass: kTileCol16 where every
+// cell's length allows it, or a compiled width at which two copies of the
+// longest line's columns take up to 64 KiB (cols_log2 keeps what a workgroup
+// takes within that, also in plane strain, where the x3 width serves lines of n2)
 bool tile_ok(const admm_ctx *c, int axis, int B) {
   if (B == kTileCol16) return col16_ok(c, axis);
   const size_t csz = c->fp64 ? sizeof(double2) : sizeof(float2);

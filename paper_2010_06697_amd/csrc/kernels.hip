@@ -2383,6 +2383,9 @@ int cols_log2(bool fp64, int n, int B) {
   // the workgroup, up to the LDS of four workgroups per CU (narrower tiles are
   // for launches of few columns)
   while (B >= tile_b(fp64) && (items << (lcb + 1)) <= kThreads && cols_lds(fp64, n, lcb + 1) <= 40960) ++lcb;
+  // and at most 64 KiB (256 points at twice the default width, which tile_ok
+  // admits in plane strain, would take 66)
+  while (lcb > 0 && cols_lds(fp64, n, lcb) > 65536) --lcb;
   return lcb;
 }
 size_t cols_lds(bool fp64, int n, int lcb) {
