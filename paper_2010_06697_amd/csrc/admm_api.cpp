@@ -145,12 +145,13 @@ int planes_per_segment(int ny, int n3, int target) {
 // fewer need less LDS); the autotuner picks `points`
 int rows_per_fft_block(int n1, int points) { return std::max(1, points / n1); }
 int default_fft_points(bool fp64) { return fp64 ? 512 : 1024; }
-// The default for one cell: halved while the cell gives fewer than 1024
-// workgroups (64^3 float: divergence 13.9 -> 9.8 us at 256 points; 256^3 double
-// 466 -> 399 us at 512 against 256). By the cell alone: which lines share a complex transform, and so their
-// rounding, depends on it, and a cell has the same bits in any batch.
-int cell_fft_points(bool fp64, int n1, int n2, int n3) {
-  int p = default_fft_points(fp64);
+// What one cell takes of them: halved down to 256 while the cell gives fewer than
+// 1024 workgroups (64^3 float: divergence 13.9 -> 9.8 us at 256 points; 256^3 double
+// 466 -> 399 us at 512 against 256). By the cell and the context's number alone:
+// which lines share a complex transform, and so their rounding, depends on it, and
+// a cell has the same bits in any batch.
+int cell_fft_points(int points, int n1, int n2, int n3) {
+  int p = points;
   while (p > 256 && (n2 * n3 + rows_per_fft_block(n1, p) - 1) / rows_per_fft_block(n1, p) < 1024)
     p /= 2;
   return p;
@@ -310,7 +311,7 @@ struct admm_ctx {
   hipStream_t cap_stream = nullptr;
   // per-cell workgroup counts of the x2 / x3 passes depend on the tile widths
   std::vector<int> blk_h;
-  int xpoints = 0;  // points per workgroup of the x1 transforms; 0: each cell's default
+  int xpoints = 0;  // points per workgroup of the forward x1 transforms, at most
   // exact local step, no LCE phase: iterations run implicitly (RveDesc::Ai);
   // the single-part entry points read and write F and Lambda
   bool implicit = false;
@@ -576,8 +577,8 @@ int set_iterations(admm_ctx *c, bool implicit) {
   return ADMM_OK;
 }
 
-// points per workgroup of the forward x1 transforms (0: each cell's default): lines per
-// workgroup of every cell, prefix table, grid size and LDS
+// points per workgroup of the forward x1 transforms, at most (cell_fft_points): lines
+// per workgroup of every cell, prefix table, grid size and LDS
 int set_xpoints(admm_ctx *c, int points) {
   const int n = c->n_rve;
   int *bf = c->blk_h.data() + 4 * (n + 1);
@@ -585,8 +586,7 @@ int set_xpoints(admm_ctx *c, int points) {
   int lds = 0;
   for (int r = 0; r < n; ++r) {
     RveDesc &D = c->desc_h[r];
-    D.rows_f = rows_per_fft_block(
-        D.n1, points ? points : cell_fft_points(c->fp64, D.n1, D.n2, D.n3));
+    D.rows_f = rows_per_fft_block(D.n1, cell_fft_points(points, D.n1, D.n2, D.n3));
     D.f_rows_f = make_fastdiv((unsigned)D.rows_f);
     bf[r + 1] = bf[r] + (D.n2 * D.n3 + D.rows_f - 1) / D.rows_f;
     lds = std::max(lds, 2 * ((3 * D.rows_f + 1) / 2) * D.n1);
@@ -788,7 +788,7 @@ std::vector<int> lengths_of(const admm_ctx *c) {
 void report_tuning(const admm_ctx *c, admm_tuning *out) {
   out->tile_y = c->L.tile_y;
   out->tile_z = c->L.tile_z;
-  out->x_points = c->xpoints ? c->xpoints : default_fft_points(c->fp64);
+  out->x_points = c->xpoints;
   const std::vector<int> n = lengths_of(c);
   out->n_len = (int32_t)std::min<size_t>(n.size(), 24);
   for (int k = 0; k < out->n_len; ++k) {
@@ -815,18 +815,15 @@ int tune(admm_ctx *c, int reps, admm_tuning *out) {
   const int cand[4] = {d / 4, d / 2, d, 2 * d};
   // points per workgroup of the x1 transforms (LDS <= 64 KiB)
   {
-    // (a tuned context has one number for all its cells, so that the number
-    // reported reproduces it)
     int keep = c->xpoints;
     for (int pts : {256, 512, 1024}) {
-      if (keep && pts == keep) continue;
-      if (2 * ((3 * (size_t)std::max(1, pts / 4) + 1) / 2) * 4 * csz > 65536)
+      if (pts == keep || 2 * ((3 * (size_t)std::max(1, pts / 4) + 1) / 2) * 4 * csz > 65536)
         continue;
       rc = set_xpoints(c, pts);
       double t = 0.0;
       if (rc == ADMM_OK) rc = time_project(c, reps, &t);
       if (rc != ADMM_OK) return rc;
-      if (!keep || t < best) {
+      if (t < best) {
         best = t;
         keep = pts;
       }
@@ -1118,7 +1115,8 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     D.V = (long long)D.n1 * D.n2 * D.n3;
     D.S = (long long)D.n3 * D.n2 * D.m1s;
     D.rows = rows_per_block(D.n1);
-    D.rows_f = rows_per_fft_block(D.n1, cell_fft_points(fp64, D.n1, D.n2, D.n3));
+    D.rows_f = rows_per_fft_block(
+        D.n1, cell_fft_points(default_fft_points(fp64), D.n1, D.n2, D.n3));
     D.f_n1 = make_fastdiv((unsigned)D.n1);
     D.f_n2 = make_fastdiv((unsigned)D.n2);
     D.f_m1 = make_fastdiv((unsigned)D.m1);
@@ -1178,7 +1176,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   c->L.thr_u = thr_u;
   c->L.nblk_f = bf[n_rve];
   c->L.nblk_i = bi[n_rve];
-  c->xpoints = 0;
+  c->xpoints = default_fft_points(fp64);
   c->L.n2max = n2max;
   c->L.n3max = n3max;
   c->L.lds_x = (size_t)lds_x * csz;
@@ -1790,8 +1788,7 @@ int admm_get_state(admm_ctx *ctx, void *blob, size_t *bytes) {
   h.flags = state_flags(ctx);
   h.tile_y = ctx->L.tile_y;
   h.tile_z = ctx->L.tile_z;
-  h.xpoints = ctx->xpoints ? ctx->xpoints : default_fft_points(ctx->fp64);
-  h.reserved = ctx->xpoints ? 0 : 1;  // 1: each cell's default
+  h.xpoints = ctx->xpoints;
   std::memcpy(q, &h, sizeof(h));
   q += sizeof(h);
   for (int r = 0; r < ctx->n_rve; ++r) {
@@ -1869,7 +1866,7 @@ int admm_set_state(admm_ctx *ctx, const void *blob, size_t bytes) {
       plan_divisors(*pl[k]);
     }
   }
-  int rc = set_xpoints(ctx, h.reserved == 1 ? 0 : h.xpoints);  // also uploads the descriptors
+  int rc = set_xpoints(ctx, h.xpoints);  // also uploads the descriptors
   if (rc == ADMM_OK) rc = set_tiles(ctx, h.tile_y, h.tile_z);
   if (rc != ADMM_OK) return rc;
   q += sizeof(h);

@@ -13,12 +13,22 @@ enum { OUT_OF_MEMORY = 2, MAX_BLOCKS = 4096 };
 static size_t budget = (size_t)-1, used = 0, largest = 0, lds_most = 0;
 static struct { void *p; size_t n; } blocks[MAX_BLOCKS];
 static int last_error = 0, launches = 0;
+static uint64_t shape_hash = 0;
+static double event_ms = 1.0, event_factor = 1.0;
 
 void fake_reset(size_t b) {
   budget = b;
   largest = lds_most = 0;
   launches = 0;
+  shape_hash = 0;
 }
+/* the next timing, and by what factor each one after it is longer */
+void fake_event_ms(double ms, double factor) {
+  event_ms = ms;
+  event_factor = factor;
+}
+/* of the launches' grids, blocks and LDS sizes, in order */
+uint64_t fake_shape_hash(void) { return shape_hash; }
 size_t fake_used(void) { return used; }
 size_t fake_largest(void) { return largest; }
 size_t fake_lds_most(void) { return lds_most; }
@@ -76,7 +86,11 @@ int hipEventCreate(void **e) { return *e = (void *)1, 0; }
 int hipEventDestroy(void *e) { return (void)e, 0; }
 int hipEventRecord(void *e, void *s) { return (void)e, (void)s, 0; }
 int hipEventSynchronize(void *e) { return (void)e, 0; }
-int hipEventElapsedTime(float *ms, void *a, void *b) { return *ms = 1.0f, (void)a, (void)b, 0; }
+int hipEventElapsedTime(float *ms, void *a, void *b) {
+  *ms = (float)event_ms;
+  event_ms *= event_factor;
+  return (void)a, (void)b, 0;
+}
 
 void **__hipRegisterFatBinary(const void *data) { return (void)data, (void **)1; }
 void __hipUnregisterFatBinary(void **m) { (void)m; }
@@ -97,8 +111,10 @@ int __hipPopCallConfiguration(dim3_ *g, dim3_ *b, size_t *lds, void **st) {
   return 0;
 }
 int hipLaunchKernel(const void *f, dim3_ g, dim3_ b, void **args, size_t lds, void *st) {
-  (void)f, (void)g, (void)b, (void)args, (void)st;
+  const uint64_t w[7] = {g.x, g.y, g.z, b.x, b.y, b.z, lds};
+  (void)f, (void)args, (void)st;
   ++launches;
+  for (int k = 0; k < 7; ++k) shape_hash = (shape_hash ^ w[k]) * 0x100000001b3ull;
   if (lds > lds_most) lds_most = lds;
   return 0;
 }

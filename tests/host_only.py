@@ -13,8 +13,9 @@ PRELUDE = """
 import ctypes, sys
 sys.path.insert(0, {root!r})
 fake = ctypes.CDLL({lib!r}, mode=ctypes.RTLD_GLOBAL)
-for f in ("fake_used", "fake_largest", "fake_lds_most"):
+for f in ("fake_used", "fake_largest", "fake_lds_most", "fake_shape_hash"):
     getattr(fake, f).restype = ctypes.c_size_t
+fake.fake_event_ms.argtypes = [ctypes.c_double, ctypes.c_double]
 fake.fake_reset.argtypes = [ctypes.c_size_t]
 from paper_2010_06697_amd import admm
 UNLIMITED = (1 << 64) - 1
