@@ -410,8 +410,9 @@ typedef struct {
  * the forward x1 transforms, then the fastest tile width of the x2 pass, then of
  * the x3 pass (a quarter, half, default or double width, LDS <= 64 KiB, or
  * ADMM_TILE_REG16 where every cell's length along that axis is supported), then the
- * fastest radix sequence of each transform length in turn (every order of
- * the radix-8/4/2/3 splits, at most 24 per length). Results change only by
+ * fastest radix sequence of each length along x1 in turn (every order of
+ * the radix-8/4/2/3 splits, at most 24 per length; lengths of the other axes
+ * keep theirs). Results change only by
  * rounding (the transforms' operation order). Step 2 writes each cell's
  * second displacement buffer (u_prev) and the workspace; u, F, Lambda, the
  * director and the iteration state are unchanged. reps = 0 only reports the

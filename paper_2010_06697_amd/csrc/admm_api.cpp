@@ -832,8 +832,9 @@ int tune(admm_ctx *c, int reps, admm_tuning *out) {
     if (rc != ADMM_OK) return rc;
   }
   // tile width of the x2 pass, then of the x3 pass (LDS <= 64 KiB), and the
-  // register-resident pass where every cell's length along the axis is 256
-  for (int pass = 0; pass < 2 && rc == ADMM_OK; ++pass) {
+  // register-resident pass where every cell's length along the axis allows it
+  // (plane strain has one of the two, at the x3 pass's width)
+  for (int pass = c->L.plane ? 1 : 0; pass < 2 && rc == ADMM_OK; ++pass) {
     int keep = pass == 0 ? c->L.tile_y : c->L.tile_z;
     std::vector<int> cands(cand, cand + 4);
     cands.push_back(kTileCol16);
@@ -851,17 +852,16 @@ int tune(admm_ctx *c, int reps, admm_tuning *out) {
     if (rc == ADMM_OK)
       rc = pass == 0 ? set_tiles(c, keep, c->L.tile_z) : set_tiles(c, c->L.tile_y, keep);
   }
-  // radix plan of each transform length in turn
+  // radix plan of each length along x1 in turn: of Step 2's passes the forward x1
+  // transform alone takes it (a length of another axis keeps its default, which
+  // the Bloch wave's transforms run)
   for (int n : lengths_of(c)) {
     if (rc != ADMM_OK) break;
-    const std::vector<Plan1D> cands = plan_candidates(n);
     Plan1D keep{};
-    for (const auto &D : c->desc_h) {
+    for (const auto &D : c->desc_h)
       if (D.p1.n == n) keep = D.p1;
-      else if (D.p2.n == n) keep = D.p2;
-      else if (D.p3.n == n) keep = D.p3;
-      if (keep.n == n) break;
-    }
+    if (keep.n != n) continue;
+    const std::vector<Plan1D> cands = plan_candidates(n);
     for (const Plan1D &p : cands) {
       if (p.nst == keep.nst && std::equal(p.rad, p.rad + p.nst, keep.rad)) continue;
       rc = set_plan(c, p);
