@@ -1625,7 +1625,9 @@ __global__ __launch_bounds__(kThreads) void k_inv_x(KernelArgs a) {
 // them from u: k_null_sums (per workgroup, the 24 sums of u_i chi_s and the
 // sum of |u|^2), k_null_final (per cell, fixed order, coefficients / V, zero
 // where they are below the rounding of u itself, 1e-15 of its RMS), k_null_sub
-// (nothing where every coefficient is zero: a call after a call).
+// (nothing where every coefficient is zero: a call after a call). idle: cells
+// that the call does not iterate too (the float form); the double form leaves
+// their u alone.
 constexpr int kNullSums = 25;
 __device__ __forceinline__ double chi(int s, int k1, int k2, int k3) {
   const int e = ((s & 1) ? k1 : 0) + ((s & 2) ? k2 : 0) + ((s & 4) ? k3 : 0);
@@ -1665,7 +1667,7 @@ __global__ __launch_bounds__(kThreads) void k_null_sums(KernelArgs a) {
     for (int k = 0; k < kNullSums; ++k) a.nullpart[(size_t)blk * kNullSums + k] = v[k];
 }
 
-__global__ __launch_bounds__(kThreads) void k_null_final(KernelArgs a) {
+__global__ __launch_bounds__(kThreads) void k_null_final(KernelArgs a, int idle) {
   __shared__ double red[kNullSums * (kThreads / 64)];
   const int r = blockIdx.x;
   const int p0 = a.blk_m[r], nb = a.blk_m[r + 1] - p0;
@@ -1688,7 +1690,7 @@ __global__ __launch_bounds__(kThreads) void k_null_final(KernelArgs a) {
       any |= c != 0.0;
       a.nullc[(size_t)r * kNullSums + k] = c;
     }
-    a.nullc[(size_t)r * kNullSums + 24] = (double)any;
+    a.nullc[(size_t)r * kNullSums + 24] = idle || a.state[r].active ? (double)any : 0.0;
   }
 }
 
@@ -2327,7 +2329,7 @@ static hipError_t launch_iteration_part(const LaunchCfg &L, const KernelArgs &a,
     case Part::StripNull: {
       if (kDefect<T> || a.implicit) {
         hipLaunchKernelGGL(k_null_sums, dim3(L.nblk_m), blk, 0, L.stream, a);
-        hipLaunchKernelGGL(k_null_final, dim3(a.n_rve), blk, 0, L.stream, a);
+        hipLaunchKernelGGL(k_null_final, dim3(a.n_rve), blk, 0, L.stream, a, kDefect<T> ? 1 : 0);
         hipLaunchKernelGGL(k_null_sub, dim3(L.nblk_m), blk, 0, L.stream, a);
       }
       break;
