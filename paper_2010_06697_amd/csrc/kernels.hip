@@ -444,8 +444,8 @@ __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass
         // Newton where that form does not apply (in the retry pass when the
         // closed form is compiled alone).
         rc = -3;
+        double Qd[9];
         if (MODE == kLocalExact) {
-          double Qd[9];
           rc = neo_closed<T>(Qd, At, jw, m.mu, m.lam, rho, cap, 2e-3);
           if (rc >= 0)
 #pragma unroll
@@ -459,8 +459,8 @@ __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass
             rc = 0;
           }
         } else {
-          if (rc == -3)
-            rc = newton<T, T>(E, At, M, (T)rho, cap, ip.gtol, ip.step_tol,
+          if (rc == -3 || rc == kRough)
+            rc = neo_newton<T>(E, At, Qd, rc == kRough, M, (T)rho, cap, ip.gtol, ip.step_tol,
                                MODE == kLocalExact || MODE == kLocalRetry ? nullptr : &lsum[0]);
         }
         n_its = rc >= 0 ? rc : cap;
@@ -712,15 +712,19 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
       NeoHooke<T> M;
       M.mu = (T)m.mu;
       M.lam = (T)m.lam;
-      if (!RETRY) rc = neo_closed<T>(Q, At, jw, m.mu, m.lam, rho, ip.newton_max, 2e-3);
-      if (KIND == kFirstI && rc == -3) {
+      T E[9];
+      if (RETRY) warm(E);
+      if (RETRY && !kDefect<T>) jw = warm_code(warm_jm1(E));  // (as the first pass had it)
+      if (!RETRY || !kDefect<T>)
+        rc = neo_closed<T>(Q, At, jw, m.mu, m.lam, rho, ip.newton_max, 2e-3);
+      if (KIND == kFirstI && (rc == -3 || rc == kRough)) {
         atomicOr(&retry[t >> 5], 1u << (t & 31));
         atomicAdd(&st->n_retry, 1);
+        rc = -3;
       }
-      if (RETRY || (KIND == kInlineI && rc == -3)) {
-        T E[9];
-        warm(E);
-        rc = newton<T, T>(E, At, M, (T)rho, ip.newton_max, ip.gtol, ip.step_tol);
+      if (RETRY || (KIND == kInlineI && (rc == -3 || rc == kRough))) {
+        if (!RETRY) warm(E);
+        rc = neo_newton<T>(E, At, Q, rc == kRough, M, (T)rho, ip.newton_max, ip.gtol, ip.step_tol);
 #pragma unroll
         for (int c = 0; c < 9; ++c) Q[c] = (double)E[c] - (double)At[c];
         newton_ran = true;

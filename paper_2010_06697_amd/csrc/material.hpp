@@ -464,7 +464,9 @@ __device__ int newton(TG *E, const TG *A, const M &m, TG rho, int maxit, double 
 // P - I are formed without subtracting numbers near one. Returns the Newton
 // count; -2 when the warm start has det F <= 0 (as newton()); -3 where the
 // form does not apply (det A <= 0, no root below the bracket's upper end, no
-// convergence, in double det A too small), for the caller to run the nine-component Newton instead.
+// convergence), for the caller to run the nine-component Newton instead; in
+// double kRough where Q is written but det A too small for its accuracy, for the
+// caller to run that Newton from there (neo_newton).
 // ---------------------------------------------------------------------------
 // reciprocal and square root in double from the hardware approximations
 // (v_rcp_f64, v_rsq_f64), each refined by Newton's method: two steps for
@@ -533,7 +535,8 @@ __device__ __forceinline__ float warm_code(double jm1) {
   return f > -1.0f ? f : -0x1.fffffep-1f;
 }
 
-// Q: F - A out (written only when the return value is >= 0; At: A - I); jw:
+constexpr int kRough = -5;
+// Q: F - A out (written only when the return value is >= 0 or kRough; At: A - I); jw:
 // warm_code of det F - 1 of the warm start
 template <typename TG>
 __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double lam, double rho,
@@ -596,9 +599,9 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
   const double x1 = 1.0 + e1, x2 = 1.0 + e2, x3 = 1.0 + e3;
   if (!(x3 > 0.0)) return -3;
   // x_3 carries e_3's rounding, a few 1e-16 of x_1: where its share exceeds a
-  // few 1e-14 of x_3 the double form leaves the voxel to Newton's method (data
-  // with det A near zero; F was off by 1e-10 there)
-  if (sizeof(TG) == 8 && !(x3 * 256.0 > x1)) return -3;
+  // few 1e-14 of x_3 the double form's point is Newton's start (data with det A
+  // near zero; F was off by 1e-10 there)
+  const bool rough = sizeof(TG) == 8 && !(x3 * 256.0 > x1);
   const double m = mu + rho, r2 = rho * rho;
   const double es[3] = {e1, e2, e3};
   const double x12 = x1 * x2, ix123 = rcp_nr(x12 * x3), ix12 = ix123 * x3;
@@ -719,7 +722,31 @@ __device__ int neo_closed(double *Q, const TG *At, float jw, double mu, double l
     for (int j = 0; j < 3; ++j)
       Q[3 * i + j] = Pm[3 * i + j] +
                      (Pm[3 * i] * a[j] + Pm[3 * i + 1] * a[3 + j] + Pm[3 * i + 2] * a[6 + j]);
+  if (rough) return kRough;
   return sizeof(TG) == 4 ? it : it + 1;  // (with the double form's second step)
+}
+
+// The nine-component Newton where neo_closed returned -3, from the warm start in
+// E, or kRough (rough), first from its point A + Q: the warm start may be so far
+// away that Newton's method stops short of the minimum (singular values of A
+// beyond 16 to 1 with lambda / mu >= 1e3: 730 voxels of 4096, against none). E:
+// the result, or the last iterate from the warm start where both gave up.
+template <typename TG, typename M>
+__device__ __forceinline__ int neo_newton(TG *E, const TG *A, const double *Q, bool rough,
+                                          const M &m, TG rho, int maxit, double gtol,
+                                          double step_tol, double *g2 = nullptr) {
+  TG P[9];
+  int rc = -3;
+#pragma unroll 1
+  for (int s = sizeof(TG) == 8 && rough ? 0 : 1; s < 2; ++s) {
+#pragma unroll
+    for (int c = 0; c < 9; ++c) P[c] = s ? E[c] : (TG)((double)A[c] + Q[c]);
+    rc = newton<TG, TG>(P, A, m, rho, maxit, gtol, step_tol, g2);
+    if (rc >= 0) break;
+  }
+#pragma unroll
+  for (int c = 0; c < 9; ++c) E[c] = P[c];
+  return rc;
 }
 
 // ---------------------------------------------------------------------------
