@@ -383,9 +383,9 @@ typedef struct {
                                or ADMM_TILE_REG16 (below) */
   int32_t n_len;            /* distinct edge lengths of the context's cells */
   int32_t x_points;         /* points per workgroup of the forward x1
-                               transforms at most (256, 512 or 1024; lines =
-                               points / n1): a cell takes half or a quarter
-                               of it where it has few lines */
+                               transforms (256, 512 or 1024; lines =
+                               points / n1); 0: each cell's default, where
+                               the cells' defaults differ */
   int32_t len[24];          /* those lengths, ascending */
   int32_t radix[24][8];     /* radix sequence of each length (2, 3, 4, 8),
                                0-terminated: the stages of the forward x1

@@ -145,13 +145,14 @@ int planes_per_segment(int ny, int n3, int target) {
 // fewer need less LDS); the autotuner picks `points`
 int rows_per_fft_block(int n1, int points) { return std::max(1, points / n1); }
 int default_fft_points(bool fp64) { return fp64 ? 512 : 1024; }
-// What one cell takes of them: halved down to 256 while the cell gives fewer than
-// 1024 workgroups (64^3 float: divergence 13.9 -> 9.8 us at 256 points; 256^3 double
-// 466 -> 399 us at 512 against 256). By the cell and the context's number alone:
-// which lines share a complex transform, and so their rounding, depends on it, and
-// a cell has the same bits in any batch.
-int cell_fft_points(int points, int n1, int n2, int n3) {
-  int p = points;
+// The default for one cell: halved down to 256 while the cell gives fewer than 1024
+// workgroups (64^3 float: divergence 13.9 -> 9.8 us at 256 points; 256^3 double
+// 466 -> 399 us at 512 against 256). By the cell alone: which lines share a complex
+// transform, and so their rounding, depends on it, and a cell has the same bits in
+// any batch. A tuned context has one number for all its cells, for which a batch
+// may have workgroups enough (16 cells of edges 32 to 96: 123 us, 102 at 1024).
+int cell_fft_points(bool fp64, int n1, int n2, int n3) {
+  int p = default_fft_points(fp64);
   while (p > 256 && (n2 * n3 + rows_per_fft_block(n1, p) - 1) / rows_per_fft_block(n1, p) < 1024)
     p /= 2;
   return p;
@@ -311,7 +312,7 @@ struct admm_ctx {
   hipStream_t cap_stream = nullptr;
   // per-cell workgroup counts of the x2 / x3 passes depend on the tile widths
   std::vector<int> blk_h;
-  int xpoints = 0;  // points per workgroup of the forward x1 transforms, at most
+  int xpoints = 0;  // points per workgroup of the x1 transforms; 0: each cell's default
   // exact local step, no LCE phase: iterations run implicitly (RveDesc::Ai);
   // the single-part entry points read and write F and Lambda
   bool implicit = false;
@@ -577,8 +578,8 @@ int set_iterations(admm_ctx *c, bool implicit) {
   return ADMM_OK;
 }
 
-// points per workgroup of the forward x1 transforms, at most (cell_fft_points): lines
-// per workgroup of every cell, prefix table, grid size and LDS
+// points per workgroup of the forward x1 transforms (0: each cell's default): lines per
+// workgroup of every cell, prefix table, grid size and LDS
 int set_xpoints(admm_ctx *c, int points) {
   const int n = c->n_rve;
   int *bf = c->blk_h.data() + 4 * (n + 1);
@@ -586,7 +587,8 @@ int set_xpoints(admm_ctx *c, int points) {
   int lds = 0;
   for (int r = 0; r < n; ++r) {
     RveDesc &D = c->desc_h[r];
-    D.rows_f = rows_per_fft_block(D.n1, cell_fft_points(points, D.n1, D.n2, D.n3));
+    D.rows_f = rows_per_fft_block(
+        D.n1, points ? points : cell_fft_points(c->fp64, D.n1, D.n2, D.n3));
     D.f_rows_f = make_fastdiv((unsigned)D.rows_f);
     bf[r + 1] = bf[r] + (D.n2 * D.n3 + D.rows_f - 1) / D.rows_f;
     lds = std::max(lds, 2 * ((3 * D.rows_f + 1) / 2) * D.n1);
@@ -788,7 +790,13 @@ std::vector<int> lengths_of(const admm_ctx *c) {
 void report_tuning(const admm_ctx *c, admm_tuning *out) {
   out->tile_y = c->L.tile_y;
   out->tile_z = c->L.tile_z;
+  // the cells' defaults as the one number they agree on, else 0
   out->x_points = c->xpoints;
+  for (int pts : {256, 512, 1024}) {
+    bool same = !out->x_points;
+    for (const auto &D : c->desc_h) same = same && D.rows_f == rows_per_fft_block(D.n1, pts);
+    if (same) out->x_points = pts;
+  }
   const std::vector<int> n = lengths_of(c);
   out->n_len = (int32_t)std::min<size_t>(n.size(), 24);
   for (int k = 0; k < out->n_len; ++k) {
@@ -1115,8 +1123,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     D.V = (long long)D.n1 * D.n2 * D.n3;
     D.S = (long long)D.n3 * D.n2 * D.m1s;
     D.rows = rows_per_block(D.n1);
-    D.rows_f = rows_per_fft_block(
-        D.n1, cell_fft_points(default_fft_points(fp64), D.n1, D.n2, D.n3));
+    D.rows_f = rows_per_fft_block(D.n1, cell_fft_points(fp64, D.n1, D.n2, D.n3));
     D.f_n1 = make_fastdiv((unsigned)D.n1);
     D.f_n2 = make_fastdiv((unsigned)D.n2);
     D.f_m1 = make_fastdiv((unsigned)D.m1);
@@ -1176,7 +1183,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
   c->L.thr_u = thr_u;
   c->L.nblk_f = bf[n_rve];
   c->L.nblk_i = bi[n_rve];
-  c->xpoints = default_fft_points(fp64);
+  c->xpoints = 0;
   c->L.n2max = n2max;
   c->L.n3max = n3max;
   c->L.lds_x = (size_t)lds_x * csz;
@@ -1654,9 +1661,10 @@ int admm_set_tuning(admm_ctx *ctx, const admm_tuning *t) {
   if (!ctx || !t) return ADMM_EINVAL;
   const size_t csz = ctx->fp64 ? sizeof(double2) : sizeof(float2);
   if (!tile_ok(ctx, 2, t->tile_y) || !tile_ok(ctx, 3, t->tile_z)) return ADMM_EINVAL;
-  if (t->x_points != 256 && t->x_points != 512 && t->x_points != 1024) return ADMM_EINVAL;
+  if (t->x_points != 0 && t->x_points != 256 && t->x_points != 512 && t->x_points != 1024)
+    return ADMM_EINVAL;
   for (const auto &D : ctx->desc_h)
-    if (2 * (size_t)((3 * rows_per_fft_block(D.n1, t->x_points) + 1) / 2) * D.n1 * csz > 65536)
+    if (t->x_points && 2 * (size_t)((3 * rows_per_fft_block(D.n1, t->x_points) + 1) / 2) * D.n1 * csz > 65536)
       return ADMM_EINVAL;
   if (t->n_len < 0 || t->n_len > 24) return ADMM_EINVAL;
   const std::vector<int> lens = lengths_of(ctx);
@@ -1788,7 +1796,8 @@ int admm_get_state(admm_ctx *ctx, void *blob, size_t *bytes) {
   h.flags = state_flags(ctx);
   h.tile_y = ctx->L.tile_y;
   h.tile_z = ctx->L.tile_z;
-  h.xpoints = ctx->xpoints;
+  h.xpoints = ctx->xpoints ? ctx->xpoints : default_fft_points(ctx->fp64);
+  h.reserved = ctx->xpoints ? 0 : 1;  // 1: each cell's default
   std::memcpy(q, &h, sizeof(h));
   q += sizeof(h);
   for (int r = 0; r < ctx->n_rve; ++r) {
@@ -1866,7 +1875,7 @@ int admm_set_state(admm_ctx *ctx, const void *blob, size_t bytes) {
       plan_divisors(*pl[k]);
     }
   }
-  int rc = set_xpoints(ctx, h.xpoints);  // also uploads the descriptors
+  int rc = set_xpoints(ctx, h.reserved == 1 ? 0 : h.xpoints);  // also uploads the descriptors
   if (rc == ADMM_OK) rc = set_tiles(ctx, h.tile_y, h.tile_z);
   if (rc != ADMM_OK) return rc;
   q += sizeof(h);
