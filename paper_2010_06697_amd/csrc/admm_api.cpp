@@ -1164,8 +1164,7 @@ int admm_init(admm_ctx **out, const admm_rve *rves, int32_t n_rve, const admm_ma
     n3max = std::max(n3max, D.n3);
     lds_x = std::max(lds_x, 2 * ((3 * D.rows_f + 1) / 2) * D.n1);
   }
-  // the spectra's padding columns stay zero: no kernel writes them but the
-  // x3 pass, which maps zero to zero there
+  // (the spectra's padding columns: no kernel writes or uses them)
   INIT_TRY(hipMemset(c->workspace, 0, spec_off));
   const size_t csz = fp64 ? sizeof(double2) : sizeof(float2);
   c->L.timer = nullptr;

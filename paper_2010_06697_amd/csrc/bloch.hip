@@ -277,7 +277,7 @@ __global__ __launch_bounds__(kThreads) void k_bl_fft(double2 *data, int ncomp, i
     A[l * N + k] = gl < nlines ? data[gidx(gl, k)] : double2{0.0, 0.0};
   }
   __syncthreads();
-  double2 *res = fft_lines<INV>(A, Bf, pl, tw, B, N, 1, false, t, nt);
+  double2 *res = fft_lines<INV>(A, Bf, pl, tw, B, N, t, nt);
   for (int e = t; e < B * N; e += nt) {
     int l, k;
     if (axis == 0) {

@@ -72,8 +72,9 @@ struct RveDesc {
   const uint8_t *phase;
   void *u[2];               // displacement fluctuation (double in both
                             // precisions), ping-pong
-  void *du;                 // float form: the correction u_{i+1} - u_i of
-                            // Step 2 (3V float, in the workspace), else null
+  void *du;                 // the correction u_{i+1} - u_i of Step 2 (3V): float
+                            // form (in the workspace) and implicit iterations of
+                            // the double form, else null
   void *E;                  // F - I
   void *Lam;                // multiplier
   void *dir;                // director (LCE) or null
@@ -81,15 +82,16 @@ struct RveDesc {
   void *dir_lag;            // directors of the previous iteration (Frank) or null
   void *dir_step;           // directors at the start of the load step (nu_n) or null
   void *E_step;             // F - I at the start of the load step (nu_F) or null
-  void *spec;               // 9 spectral components, layout [c][x3][x2][m1]
-  void *At;                 // float form without LCE phases: Step 1's data
+  void *spec;               // 3 spectral components, layout [c][x3][x2][m1s]
+  void *At;                 // explicit iterations of the float form without LCE
+                            // phases: Step 1's data
                             // A - I = grad u + Ebar + Lambda/rho of the next
                             // iteration as the update formed it (9V float),
                             // then the warm start's det F - 1 (V float, in
                             // warm_code's form), valid while RveState::at_rho
                             // is the penalty; else null
-  void *Q;                  // float form without the full LCE model's terms:
-                            // F - A of the last local pass (9V float), whose
+  void *Q;                  // explicit iterations of the float form without the
+                            // full LCE model's terms: F - A of the last local pass (9V float), whose
                             // D_h^T is Step 2's defect; else null
   // Implicit iterations (exact local step, no LCE phase; both forms): A - I
   // of Step 1 (9V, ping-pong with u), F - A (9V) and warm_code of the warm
@@ -114,7 +116,7 @@ struct RveState {
   int domain_err;    // set when det F <= 0 or NaN met
   int local_done;    // inexact local step: r_l reached its target (or the pass cap)
   int implicit;      // 1: F and Lambda of this cell are held as A, F - A and
-                     // du (see k_update_i); every state upload clears it
+                     // du (see k_update); every state upload clears it
   unsigned long long newton_iters;  // Newton iterations summed over voxels and iterations
   double rl;         // local residual after the last inexact pass
   double Ebar[9];       // <F> - I of the current iterate (free components move)
@@ -157,9 +159,10 @@ __host__ __device__ inline bool divergence_watch(double rp, double rd, double to
 }
 
 constexpr int kZSeg = 16;  // most planes per workgroup of the update tiling (k_update walks them)
-// tile width that selects the register-resident x2 / x3 pass of length 256
-// (16 columns per workgroup, 16 points per thread, one LDS exchange per
-// transform); open to an axis when every cell's length along it is 256
+// tile width that selects the register-resident x2 / x3 passes (k_col16: length
+// 256, 16 columns per workgroup, 16 points per thread; k_colreg: float, also
+// lengths 32, 48, 64, 96 and 128); open to an axis when every cell's length
+// along it is one of theirs
 constexpr int kTileCol16 = -16;
 constexpr int kLocalPassGrid = 2048;  // workgroups of the later inexact local passes
 

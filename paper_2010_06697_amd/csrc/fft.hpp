@@ -202,35 +202,23 @@ __device__ __forceinline__ void dft_split(C *v, const double *wc, const double *
   }
 }
 
-// One radix-R stage over `nlines` lines. Element k of line l lives at
-// buf[l*ls + k*es]. lfast: consecutive threads take consecutive lines (for the
-// [k][line] layouts) instead of consecutive butterflies of one line.
+// One radix-R stage over `nlines` lines, element k of line l at buf[l*ls + k];
+// consecutive threads take consecutive butterflies of a line.
 template <int R, bool INV, typename C, typename FD>
 __device__ __forceinline__ void fft_stage(const C *__restrict__ src, C *__restrict__ dst, int N,
                                           int Ns, const FD &fnb, const FD &fns, int nlines, int ls,
-                                          int es, bool lfast, const C *__restrict__ tw, int tid,
-                                          int nthr) {
+                                          const C *__restrict__ tw, int tid, int nthr) {
   const int nb = N / R;
   const int total = nb * nlines;
   const int twstep = N / (Ns * R);
   for (int w = tid; w < total; w += nthr) {
-    int l, j;
-    if (lfast) {
-      l = w % nlines;
-      j = w / nlines;
-    } else {
-      l = fdiv(w, fnb);
-      j = w - l * nb;
-    }
+    const int l = fdiv(w, fnb), j = w - l * nb;
     const C *s = src + l * ls;
     C *d = dst + l * ls;
-    // the multiply-high division pays in the x1 transforms (lines along the
-    // workgroup, issue bound); in the column layouts it costs registers and
-    // occupancy instead
-    const int jm = lfast ? j % Ns : j - fdiv(j, fns) * Ns;
+    const int jm = j - fdiv(j, fns) * Ns;
     C v[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = s[(j + r * nb) * es];
+    for (int r = 0; r < R; ++r) v[r] = s[j + r * nb];
     if (Ns > 1) {
 #pragma unroll
       for (int r = 1; r < R; ++r) {
@@ -241,7 +229,7 @@ __device__ __forceinline__ void fft_stage(const C *__restrict__ src, C *__restri
     dftR<R, INV>(v);
     const int o = (j - jm) * R + jm;
 #pragma unroll
-    for (int r = 0; r < R; ++r) d[(o + r * Ns) * es] = v[r];
+    for (int r = 0; r < R; ++r) d[o + r * Ns] = v[r];
   }
 }
 
@@ -250,23 +238,23 @@ __device__ __forceinline__ void fft_stage(const C *__restrict__ src, C *__restri
 // (PL: Plan1D, in any address space)
 template <bool INV, typename C, typename PL>
 __device__ C *fft_lines(C *a, C *b, const PL &p, const C *__restrict__ twpool, int nlines,
-                        int ls, int es, bool lfast, int tid, int nthr) {
+                        int ls, int tid, int nthr) {
   const C *tw = twpool + p.tw;
   int Ns = 1;
   for (int s = 0; s < p.nst; ++s) {
     const int R = p.rad[s];
     switch (R) {
       case 2:
-        fft_stage<2, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, es, lfast, tw, tid, nthr);
+        fft_stage<2, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, tw, tid, nthr);
         break;
       case 3:
-        fft_stage<3, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, es, lfast, tw, tid, nthr);
+        fft_stage<3, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, tw, tid, nthr);
         break;
       case 4:
-        fft_stage<4, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, es, lfast, tw, tid, nthr);
+        fft_stage<4, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, tw, tid, nthr);
         break;
       default:
-        fft_stage<8, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, es, lfast, tw, tid, nthr);
+        fft_stage<8, INV>(a, b, p.n, Ns, p.nb[s], p.ns[s], nlines, ls, tw, tid, nthr);
         break;
     }
     __syncthreads();

@@ -1106,7 +1106,7 @@ void k_div_fwdx(KernelArgs a) {
   }
   __syncthreads();
   const C *tw = static_cast<const C *>(a.tw);
-  C *res = fft_lines<false>(za, zb, D.p1, tw, ncl, n1, 1, false, t, nthr);
+  C *res = fft_lines<false>(za, zb, D.p1, tw, ncl, n1, t, nthr);
   C *spec = static_cast<C *>(D.spec);
   for (int w = t; w < ncl * m1; w += nthr) {
     const int p = fdiv(w, D.f_m1), m = w - p * m1;
