@@ -71,7 +71,7 @@ struct BlochArgs {
                       // (0 iterating, 1 converged, 2 error), [8] iterations run
   double tol;         // on r_p and r_d
   const double *k2t;  // sin^2(2 pi m/n_j + w_j): n1 + n2 + n3 entries
-  double k2min;
+  double k2min, sigma_max;  // sigma_max: the last double below k2min
 };
 
 // the iterations enqueued after the one that converged (or failed) do nothing
@@ -301,7 +301,9 @@ __device__ __forceinline__ double k2_at(const BlochArgs &a, int x) {
 // V^2, for sigma < k2min. 1/sqrt(f) is concave and nearly linear in sigma, so
 // Newton's method on 1/sqrt(f) - 1/V (the trust-region form) converges from
 // above without overshoot: at most 7 sums from
-//     hi = k2min - sqrt(sum of |b^|^2 where |K|^2 = k2min) / V   (f >= V^2)
+//     hi = k2min - sqrt(sum of |b^|^2 where |K|^2 = k2min) / V   (f >= V^2),
+// at most sigma_max (no mode has |K|^2 = sigma; where b has nothing but rounding
+// at k2min, f may stay below V^2 up to there, and that end is the answer),
 // and 3 to 5 from the previous iteration's root, to the rounding of f, where
 // bisection took about 55. Steps outside the bracket [lo, hi], lo = k2min -
 // sqrt(sum |b^|^2) / V (f <= V^2), become bisections.
@@ -351,12 +353,12 @@ __device__ __forceinline__ SecState sec_start(const BlochArgs &a, double s, doub
   const double V = (double)a.V;
   SecState q;
   q.lo = a.k2min - sqrt(s) / V;
-  q.hi = a.k2min - sqrt(smin) / V;
+  q.hi = fmin(a.k2min - sqrt(smin) / V, a.sigma_max);
   // the previous iteration's root (scal[8]: iterations run), else the bracket's
-  // end from which Newton's method is monotone, where a mode is there
+  // end from which Newton's method is monotone
   const double prev = a.scal[0];
   if (a.scal[8] > 0.0 && prev > q.lo && prev < q.hi) q.sigma = prev;
-  else q.sigma = q.hi < a.k2min ? q.hi : 0.5 * (q.lo + q.hi);
+  else q.sigma = q.hi;
   q.done = 0.0;
   return q;
 }
@@ -650,6 +652,8 @@ int bloch_solve(hipStream_t st, const RveDesc &D, const Material *mats_d, int n_
     k2min += mn;
   }
   a.k2min = k2min;
+  // (at k2min = 0 far enough from it that 1 / sigma^3 is finite)
+  a.sigma_max = std::min(std::nextafter(k2min, -1.0), -1e-100 + k2min);
   // work buffers
   void *buf = work;
   if (!buf) {
