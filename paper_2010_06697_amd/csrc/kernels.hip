@@ -707,12 +707,12 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
     int rc = -4;
     bool newton_ran = false;  // (its last iterate is kept where it gave up)
     double Q[9];
+    T E[9];
     if (ph < a.n_mat) {
       const Material m = a.mats[ph];
       NeoHooke<T> M;
       M.mu = (T)m.mu;
       M.lam = (T)m.lam;
-      T E[9];
       if (RETRY) warm(E);
       if (RETRY && !kDefect<T>) jw = warm_code(warm_jm1(E));  // (as the first pass had it)
       if (!RETRY || !kDefect<T>)
@@ -737,7 +737,6 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
     }
     if (rc != -3) {
       if (rc < 0 && !newton_ran) {  // no point: F stays as it was
-        T E[9];
         warm(E);
 #pragma unroll
         for (int c = 0; c < 9; ++c) Q[c] = (double)E[c] - (double)At[c];
@@ -750,8 +749,11 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
         if constexpr (kDefect<T>) w |= (unsigned long long)q_code(Q[c], q) << (7 * c);
       }
       if (kDefect<T>) *at(global_view(D.Ri), V, 0, (unsigned)idx * 8u) = w;
-      if (a.implicit == 2) {  // the call's last iteration: F itself
-        const auto Eo = global_view(static_cast<T *>(D.E));
+      const auto Eo = global_view(static_cast<T *>(D.E));
+      if (rc < 0) {  // F whatever the data (k_explicit keeps it where A is not finite)
+#pragma unroll
+        for (int c = 0; c < 9; ++c) *at(Eo, V, c, off) = E[c];
+      } else if (a.implicit == 2) {  // the call's last iteration: F itself
 #pragma unroll
         for (int c = 0; c < 9; ++c) {
           double q = Q[c];
@@ -797,11 +799,16 @@ __global__ __launch_bounds__(kThreads) void k_explicit(KernelArgs a) {
   load_q<T>(D, V, idx, Q);
   grad_u(global_view(static_cast<const T *>(D.du)), V, sn, g);
   const double rho = st->rho_used;
+  double F[9], sum = 0.0;
 #pragma unroll
   for (int c = 0; c < 9; ++c) {
     Lg[c * V + idx] = (T)(rho * (g[c] + (st->Ebar[c] - st->Ebar_prev[c]) - Q[c]));
-    Eg[c * V + idx] = (T)((double)Ap[c * V + idx] + Q[c]);
+    F[c] = (double)Ap[c * V + idx] + Q[c];
+    sum += F[c] - F[c];
   }
+  if (sum != 0.0) return;  // (not finite: the local step kept F)
+#pragma unroll
+  for (int c = 0; c < 9; ++c) Eg[c * V + idx] = (T)F[c];
 }
 
 // Frank term: the directors of the previous iteration, copied before Step 1

@@ -6,6 +6,9 @@ One voxel holds a phase index without a material: the first iteration marks
 the cell, keeps that voxel's F and runs to its end, so five iterations have to
 leave what one iteration leaves. The two take different kernels for the end of
 a call: the bound is rounding, a few units of the type.
+
+A voxel whose data is not finite keeps the F it had, as in explicit iterations,
+however the call ends.
 """
 import numpy as np
 import pytest
@@ -62,3 +65,23 @@ def test_failed_cell_keeps_its_last_iterate(precision, graph, shape):
         say("  ", f, err, same)
         assert err <= tol, f
         assert same, f
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32"])
+@pytest.mark.parametrize("form", [0, 1])
+@pytest.mark.parametrize("shape", [(8, 12, 16), (36, 48, 48)])
+def test_voxel_without_finite_data_keeps_its_F(precision, form, shape):
+    say("a multiplier that is not a number", precision, "explicit" if form else "implicit", shape)
+    u, F, L = random_state(shape, seed=6)
+    L[0, 1, 2, 3] = np.nan
+    phase = M.random_two_phase(shape, 0.4, seed=3)
+    for call in (lambda s: s.step(1), lambda s: s.step(4), lambda s: s.solve()):
+        s = gpu_solver([phase], MATS, [M.random_fbar(0.03, seed=5)], precision, rho0=8.0, mu_ref=4.0,
+                       explicit_fields=form)
+        s.set_state(0, u=u, F=F, Lambda=L)
+        before = s.state(0)["F"][:, 1, 2, 3]
+        rc, after = call(s)[0], s.state(0)["F"]
+        s.close()
+        assert rc == admm.EDOMAIN
+        kept = bool(np.array_equal(after[:, 1, 2, 3], before)) and bool(np.isfinite(after).all())
+        assert kept
