@@ -46,18 +46,20 @@ def kernel_bytes_per_voxel(s, c):
     costs 2 c s per voxel). The cell's iterations (neo-Hookean, exact local
     step) keep F and Lambda implicit but in a call's first and last one: the
     local step reads its data A - I and the code of its warm start's
-    det F - 1 (one float) and writes Q = F - A; Step 2 solves for the
-    correction du from D_h^T Q; the update forms u_{i+1} and the next A - I
-    from u, du, Q and A. u is double in both forms."""
+    det F - 1 (one float) and writes Q = F - A (in float with 8 bytes of
+    further bits); Step 2 solves for the correction du from D_h^T Q; the
+    update forms u_{i+1} and the next A - I from u, du, Q and A. u is double
+    in both forms."""
+    q = 8 if s == 4 else 0
     return {
-        "local": 18 * s + 4 + 1,         # A 9, warm start, phase in; Q 9 out
+        "local": 18 * s + q + 4 + 1,     # A 9, warm start, phase in; Q 9 out
         "div_fwdx": 9 * s + 6 * c * s,   # Q 9 in; 3 half spectra out
         "fft_y_fwd": 12 * c * s,         # 3 components in and out
         "poisson_z": 12 * c * s,
         "fft_y_inv": 12 * c * s,
         "inv_x": 6 * c * s + 3 * s,      # spectra in; du out
         # u_i 3 (double), du 3, Q 9, A 9 in; u_{i+1} 3, A 9, warm start out
-        "update": 6 * 8 + 30 * s + 4,
+        "update": 6 * 8 + 30 * s + q + 4,
         "finalize": 0.0,
         "mean_stress": 18 * s + 1,
     }

@@ -1310,8 +1310,15 @@ __global__ __launch_bounds__(kThreads) void k_cols(KernelArgs a) {
 // ----------------------------------------------------------------------------
 // x2 and x3 passes of length 256 at the tile width kTileCol16, register
 // resident (k_col16; where a float launch also holds shorter lengths it is
-// k_colreg below, which covers 256 the same way): a workgroup takes 16 columns (flattened over the cell's (x3, m1)
-// for x2, (m2, m1) for x3, padding columns excluded); thread (c, j) =
+// k_colreg below, which covers 256 the same way). k_cols with every point of a
+// column's two steps in one thread's registers: one set of 16 x 16 points per
+// workgroup, no loops over items, 16 points per thread. That pays in double along
+// x3 (256^3: 212 us, k_cols at its best width 267), where k_cols keeps the columns'
+// exchange in LDS over two barriers more, and about equals it in float (x2 86 / 60
+// us against 89 / 60, x3 87 against 82); along x2 in double k_cols is faster (159 /
+// 164 us against 177 / 191). The autotuner chooses per axis.
+// A workgroup takes 16 columns (flattened over the cell's (x3, m1) for x2,
+// (m2, m1) for x3, padding columns excluded); thread (c, j) =
 // (t % 16, t / 16) holds elements j + 16 r (r = 0..15) of column c. With
 // n = j + 16 r and k = 16 k1 + k2,
 //     X[16 k1 + k2] = sum_j w16^(j k1) w256^(j k2) sum_r x[j + 16 r] w16^(r k2):
@@ -1401,7 +1408,9 @@ __global__ __launch_bounds__(kThreads) void k_col16(KernelArgs a) {
 
 // Register-resident x2 / x3 passes in float for the lengths 32, 48, 64, 96,
 // 128 and 256 (cells of different lengths in one launch, each workgroup in
-// one cell): a length N = T P is taken by T threads per column, P points each;
+// one cell). What it gains on k_cols is small: 16 cells of edges 32 to 96, x2
+// forward 45 us against 49, inverse 37 against 34, x3 57 against 47; 128^3 x2 15.5
+// / 16.1 against 15.3 / 15.3, x3 21.4 against 21.6. A length N = T P is taken by T threads per column, P points each;
 // a workgroup takes 256 / T columns. Thread (c, j) loads points j + T r
 // (r < P) of column c; with n = j + T r and k = k2 + P k1,
 //     X[P k1 + k2] = sum_j w_T^(j k1) w_N^(j k2) sum_r x[j + T r] w_P^(r k2):
