@@ -750,7 +750,11 @@ __device__ __forceinline__ void local_tile_i(const KernelArgs &a, const IterPara
       }
       if (kDefect<T>) *at(global_view(D.Ri), V, 0, (unsigned)idx * 8u) = w;
       const auto Eo = global_view(static_cast<T *>(D.E));
-      if (rc < 0) {  // F whatever the data (k_explicit keeps it where A is not finite)
+      double nan = 0.0;
+      if (rc < 0)
+#pragma unroll
+        for (int c = 0; c < 9; ++c) nan += Q[c] - Q[c];
+      if (nan != 0.0) {  // A is not finite: F as it was, which k_explicit keeps
 #pragma unroll
         for (int c = 0; c < 9; ++c) *at(Eo, V, c, off) = E[c];
       } else if (a.implicit == 2) {  // the call's last iteration: F itself
