@@ -71,7 +71,7 @@ struct BlochArgs {
                       // (0 iterating, 1 converged, 2 error), [8] iterations run
   double tol;         // on r_p and r_d
   const double *k2t;  // sin^2(2 pi m/n_j + w_j): n1 + n2 + n3 entries
-  double k2min, sigma_max;  // sigma_max: the last double below k2min
+  double k2min;
 };
 
 // the iterations enqueued after the one that converged (or failed) do nothing
@@ -302,8 +302,9 @@ __device__ __forceinline__ double k2_at(const BlochArgs &a, int x) {
 // Newton's method on 1/sqrt(f) - 1/V (the trust-region form) converges from
 // above without overshoot: at most 7 sums from
 //     hi = k2min - sqrt(sum of |b^|^2 where |K|^2 = k2min) / V   (f >= V^2),
-// at most sigma_max (no mode has |K|^2 = sigma; where b has nothing but rounding
-// at k2min, f may stay below V^2 up to there, and that end is the answer),
+// at most the last double below k2min (no mode has |K|^2 = sigma; where b has
+// nothing but rounding at k2min, f may stay below V^2 up to there, and that end is
+// the answer),
 // and 3 to 5 from the previous iteration's root, to the rounding of f, where
 // bisection took about 55. Steps outside the bracket [lo, hi], lo = k2min -
 // sqrt(sum |b^|^2) / V (f <= V^2), become bisections.
@@ -353,7 +354,9 @@ __device__ __forceinline__ SecState sec_start(const BlochArgs &a, double s, doub
   const double V = (double)a.V;
   SecState q;
   q.lo = a.k2min - sqrt(s) / V;
-  q.hi = fmin(a.k2min - sqrt(smin) / V, a.sigma_max);
+  // (at k2min = 0 so far below that 1 / sigma^3 is finite)
+  const double smax = a.k2min > 0.0 ? __longlong_as_double(__double_as_longlong(a.k2min) - 1) : -1e-100;
+  q.hi = fmin(a.k2min - sqrt(smin) / V, smax);
   // the previous iteration's root (scal[8]: iterations run), else the bracket's
   // end from which Newton's method is monotone
   const double prev = a.scal[0];
@@ -652,8 +655,6 @@ int bloch_solve(hipStream_t st, const RveDesc &D, const Material *mats_d, int n_
     k2min += mn;
   }
   a.k2min = k2min;
-  // (at k2min = 0 far enough from it that 1 / sigma^3 is finite)
-  a.sigma_max = std::min(std::nextafter(k2min, -1.0), -1e-100 + k2min);
   // work buffers
   void *buf = work;
   if (!buf) {

@@ -459,7 +459,7 @@ __device__ __forceinline__ void local_tile(KernelArgs a, IterParams ip, int pass
             rc = 0;
           }
         } else {
-          if (rc == -3 || rc == kRough)
+          if (rc == -3 || (!kDefect<T> && rc == kRough))
             rc = neo_newton<T>(E, At, Qd, rc == kRough, M, (T)rho, cap, ip.gtol, ip.step_tol,
                                MODE == kLocalExact || MODE == kLocalRetry ? nullptr : &lsum[0]);
         }

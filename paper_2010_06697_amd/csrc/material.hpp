@@ -735,18 +735,22 @@ template <typename TG, typename M>
 __device__ __forceinline__ int neo_newton(TG *E, const TG *A, const double *Q, bool rough,
                                           const M &m, TG rho, int maxit, double gtol,
                                           double step_tol, double *g2 = nullptr) {
-  TG P[9];
-  int rc = -3;
+  if constexpr (sizeof(TG) == 4) {
+    return newton<TG, TG>(E, A, m, rho, maxit, gtol, step_tol, g2);
+  } else {
+    TG P[9];
+    int rc = -3;
 #pragma unroll 1
-  for (int s = sizeof(TG) == 8 && rough ? 0 : 1; s < 2; ++s) {
+    for (int s = rough ? 0 : 1; s < 2; ++s) {
 #pragma unroll
-    for (int c = 0; c < 9; ++c) P[c] = s ? E[c] : (TG)((double)A[c] + Q[c]);
-    rc = newton<TG, TG>(P, A, m, rho, maxit, gtol, step_tol, g2);
-    if (rc >= 0) break;
+      for (int c = 0; c < 9; ++c) P[c] = s ? E[c] : (TG)((double)A[c] + Q[c]);
+      rc = newton<TG, TG>(P, A, m, rho, maxit, gtol, step_tol, g2);
+      if (rc >= 0) break;
+    }
+#pragma unroll
+    for (int c = 0; c < 9; ++c) E[c] = P[c];
+    return rc;
   }
-#pragma unroll
-  for (int c = 0; c < 9; ++c) E[c] = P[c];
-  return rc;
 }
 
 // ---------------------------------------------------------------------------
